@@ -131,65 +131,116 @@ __global__ void __launch_bounds__(256) k_aggregate_cols(const int64_t *__restric
     if (wv == 0 && col < n_cols) agg[col] = s0 + red[0][lane] + red[1][lane] + red[2][lane];
 }
 
-// Layer-local LPT (Alg. 1), one layer per workgroup of one wave.
-// Experts are ranked by (-L_{l,e}, e) (ranking by counting: the rank of e
-// is the number of experts that precede it), then E greedy steps each pick
-// the rank minimising (G_p, p) among ranks with fewer than H experts.
-__global__ void __launch_bounds__(64) k_lpt_place(const int64_t *__restrict__ agg, int32_t E,
-                                                  int32_t P, int32_t *__restrict__ slot_of,
-                                                  int64_t *__restrict__ rank_load,
-                                                  int32_t *__restrict__ expert_at_slot) {
-    extern __shared__ char smem[];
-    int64_t *Ll = reinterpret_cast<int64_t *>(smem);           // [E]
+constexpr int kLptThreads = 512;
+
+// Lane i's value becomes lane i + 1's; lane 63's becomes 0.
+__device__ inline int32_t wave_shl1(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xF, 0xF, true); }
+
+// Orders a wave's LDS writes before its later reads by other lanes.
+__device__ inline void lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Layer-local LPT (Alg. 1), one layer per workgroup.  Experts are ranked by
+// (-L_{l,e}, e) (ranking by counting: the rank of e is the number of experts
+// that precede it; every wave counts), then E greedy steps of the first wave
+// each pick the rank minimising (G_p, p) among ranks with fewer than H
+// experts.  The E steps are one serial chain, so its length in cycles bounds
+// the kernel.  Up to 64 ranks the lanes hold the open ranks sorted by
+// (G_p, p) in one 64-bit key: lane 0 is the pick, and its new load goes back
+// in behind the lanes that precede it (one compare, whose mask is a run of
+// lanes from 0 on) by a one-lane shift of that run; a rank that is full
+// leaves by shifting every lane.  A step has no reduction over the wave and
+// no store (a block's slots are stored together).  64 layers of 512 experts
+// on 64 ranks: 249 us with a wave minimum per step and one wave ranking,
+// 70 us now; 24 layers of 256 experts on 16 ranks: 100 us, 36 us now.
+__global__ void __launch_bounds__(kLptThreads) k_lpt_place(const int64_t *__restrict__ agg, int32_t E,
+                                                           int32_t P, int32_t *__restrict__ slot_of,
+                                                           int64_t *__restrict__ rank_load,
+                                                           int32_t *__restrict__ expert_at_slot) {
+    extern __shared__ __align__(16) char smem[];
+    int64_t *Ll = reinterpret_cast<int64_t *>(smem);             // [E]
     int64_t *G = Ll + E;                                          // [P]
     int32_t *order = reinterpret_cast<int32_t *>(G + P);          // [E]
     int32_t *nfill = order + E;                                   // [P]
-    const int l = blockIdx.x, lane = lane_id();
+    const int l = blockIdx.x, lane = lane_id(), tid = threadIdx.x, nt = blockDim.x;
     const int32_t H = E / P;
-    for (int e = lane; e < E; e += kWave) Ll[e] = agg[(int64_t)l * E + e];
+    for (int e = tid; e < E; e += nt) Ll[e] = agg[(int64_t)l * E + e];
+    __syncthreads();
+    for (int e = tid; e < E; e += nt) {
+        const int64_t v = Ll[e];
+        int32_t rank = 0;
+#pragma unroll 4
+        for (int f = 0; f + 1 < E; f += 2) {
+            const longlong2 w = *reinterpret_cast<const longlong2 *>(Ll + f);
+            rank += (w.x > v) || (w.x == v && f < e);
+            rank += (w.y > v) || (w.y == v && f + 1 < e);
+        }
+        if (E & 1) rank += Ll[E - 1] > v;  // (an equal last expert precedes none)
+        order[rank] = e;
+    }
+    __syncthreads();
+    if (tid >= kWave) return;  // (no barrier follows)
+    // the largest partial load: the key below holds it in 58 bits
+    int64_t part = 0, low = 0;
+    for (int e = lane; e < E; e += kWave) {
+        part += Ll[e] < (int64_t)1 << 50 ? Ll[e] : (int64_t)1 << 50;
+        low = Ll[e] < low ? Ll[e] : low;
+    }
+    const bool keyed = P <= kWave && E <= (1 << 20) && wave_min(low) >= 0 && wave_sum(part) < (int64_t)1 << 50;
+    if (keyed) {
+        // lane x < open ranks: the x-th open rank in (G_p, p) order, as the
+        // key (2^58 - 1 - G_p) 2^6 + 63 - p (a larger key comes first; the
+        // lanes past the open ranks hold 0) and its (p | fill << 6)
+        uint64_t key = lane < P ? ~(uint64_t)0 - (uint64_t)lane : 0;
+        int32_t rf = lane;
+        uint64_t fin = ~(uint64_t)0;  // lane p: rank p's key once it is full
+        int32_t oe = order[lane < E ? lane : 0];
+        uint64_t ol = (uint64_t)Ll[oe] << 6;
+        for (int kb = 0; kb < E; kb += kWave) {
+            const int32_t kn = kb + kWave + lane;
+            const int32_t noe = order[kn < E ? kn : 0];  // the next block's experts and loads
+            const uint64_t nol = (uint64_t)Ll[noe] << 6;
+            const int cnt = E - kb < kWave ? E - kb : kWave;
+            int32_t sv = 0;
+            for (int x = 0; x < cnt; ++x) {
+                const uint64_t nk = readlane64(key, 0) - readlane64(ol, x);
+                const int32_t r0 = __builtin_amdgcn_readlane(rf, 0);
+                const uint64_t upk = (uint64_t)(uint32_t)wave_shl1((int32_t)(uint32_t)key) |
+                                     (uint64_t)(uint32_t)wave_shl1((int32_t)(uint32_t)(key >> 32)) << 32;
+                const int32_t uprf = wave_shl1(rf);
+                const bool full = (r0 >> 6) + 1 == H;
+                const uint64_t before = __ballot(key > nk) | 1;  // lanes 0 .. the new place
+                const bool shift = __builtin_amdgcn_inverse_ballot_w64(full ? ~(uint64_t)0 : before >> 1);
+                const bool here = __builtin_amdgcn_inverse_ballot_w64(full ? 0 : before ^ (before >> 1));
+                const bool mine = __builtin_amdgcn_inverse_ballot_w64((uint64_t)1 << x);
+                const bool done = __builtin_amdgcn_inverse_ballot_w64(full ? (uint64_t)1 << (r0 & (kWave - 1)) : 0);
+                sv = mine ? r0 : sv;
+                fin = done ? nk : fin;
+                key = here ? nk : key;
+                rf = here ? r0 + kWave : rf;
+                key = shift ? upk : key;
+                rf = shift ? uprf : rf;
+            }
+            if (lane < cnt) {
+                const int32_t v = (sv & (kWave - 1)) * H + (sv >> 6);
+                slot_of[(int64_t)l * E + oe] = v;
+                if (expert_at_slot) expert_at_slot[(int64_t)l * E + v] = oe;
+            }
+            oe = noe;
+            ol = nol;
+        }
+        if (lane < P) rank_load[(int64_t)l * P + lane] = (int64_t)((~fin) >> 6);
+        return;
+    }
+    // more than 64 ranks, or loads past the key's range
     for (int p = lane; p < P; p += kWave) {
         G[p] = 0;
         nfill[p] = 0;
     }
-    __syncthreads();
-    for (int e = lane; e < E; e += kWave) {
-        const int64_t v = Ll[e];
-        int32_t rank = 0;
-        for (int f = 0; f < E; ++f) {
-            const int64_t w = Ll[f];
-            rank += (w > v) || (w == v && f < e);
-        }
-        order[rank] = e;
-    }
-    __syncthreads();
-    if (P <= kWave) {
-        // lane p holds rank p's load and fill; a step is a wave minimum of
-        // the loads of ranks with room, then the lowest such lane (the
-        // order of the next 64 experts is held one per lane)
-        int64_t g = 0;
-        int32_t nf = 0, oe = 0;
-        int64_t ol = 0;
-        for (int k = 0; k < E; ++k) {
-            if ((k & (kWave - 1)) == 0) {
-                oe = k + lane < E ? order[k + lane] : 0;
-                ol = Ll[oe];
-            }
-            const int e = __builtin_amdgcn_readlane(oe, k & (kWave - 1));
-            const int64_t le = (int64_t)readlane64((uint64_t)ol, k & (kWave - 1));
-            const bool avail = lane < P && nf < H;
-            const int64_t mn = wave_min(avail ? g : LLONG_MAX);
-            const int bp = first_lane(__ballot(avail && g == mn));
-            if (lane == bp) {
-                const int32_t v = bp * H + nf;
-                slot_of[(int64_t)l * E + e] = v;
-                if (expert_at_slot) expert_at_slot[(int64_t)l * E + v] = e;
-                g += le;
-                ++nf;
-            }
-        }
-        if (lane < P) rank_load[(int64_t)l * P + lane] = g;
-        return;
-    }
+    lds_order();
     for (int k = 0; k < E; ++k) {
         const int e = order[k];
         int64_t bg = LLONG_MAX;
@@ -216,7 +267,7 @@ __global__ void __launch_bounds__(64) k_lpt_place(const int64_t *__restrict__ ag
             G[bp] += Ll[e];
             nfill[bp] += 1;
         }
-        __syncthreads();
+        lds_order();
     }
     for (int p = lane; p < P; p += kWave) rank_load[(int64_t)l * P + p] = G[p];
 }
@@ -441,7 +492,9 @@ extern "C" int routepack_place_experts(const routepack_problem *prob, const int6
     if (scr.failed()) return ROUTEPACK_E_DEVICE;
     const size_t lds = (size_t)E * 8 + (size_t)P * 8 + (size_t)E * 4 + (size_t)P * 4;
     if (lds > 160 * 1024) return ROUTEPACK_E_UNSUPPORTED;
-    hipLaunchKernelGGL(k_lpt_place, dim3(L), dim3(64), lds, stream, agg, E, P, slot_of, rank_load,
+    // a thread per expert to rank, up to 512 (the greedy steps use one wave)
+    const int nt = E >= kLptThreads ? kLptThreads : (E + kWave - 1) / kWave * kWave;
+    hipLaunchKernelGGL(k_lpt_place, dim3(L), dim3(nt), lds, stream, agg, E, P, slot_of, rank_load,
                        eas);
     if (want_q) RP_TRY(launch_project(demand, eas, q, N, L, E, P, stream));
     return hipGetLastError() == hipSuccess ? ROUTEPACK_OK : ROUTEPACK_E_DEVICE;
