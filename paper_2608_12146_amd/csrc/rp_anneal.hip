@@ -36,7 +36,7 @@ namespace rp {
 int eval_layouts(const routepack_problem *p, const Topology &topo, const DeviceProblem &dp,
                  const int32_t *t, const int32_t *q, int32_t R, int64_t n, const int32_t *layouts,
                  int64_t *scores, int32_t *status, int64_t *J, double *diag,
-                 const int64_t *rank_load, hipStream_t stream);
+                 const int64_t *rank_load, bool sum32, hipStream_t stream);
 __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v);
 
 template <bool WLDS>
@@ -1088,7 +1088,7 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
     } else {
         // The given x* must be feasible and carry its own score.
         RP_TRY(eval_layouts(prob, topo, dp, lengths, q, n_rows, 1, best_layout, chk_score, status,
-                            nullptr, nullptr, nullptr, stream));
+                            nullptr, nullptr, nullptr, sums_fit32(ws), stream));
         hipLaunchKernelGGL(k_compare_score, dim3(1), dim3(64), 0, stream, chk_score, best_score,
                            status, chk);
         int32_t ok = 0;
@@ -1253,7 +1253,7 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
                            slab_final, N, population, (const int32_t *)run.err);
         RP_HIP(hipGetLastError());
         RP_TRY(eval_layouts(prob, topo, dp, lengths, q, n_rows, 1, best_layout, chk_score, status, nullptr,
-                            nullptr, nullptr, stream));
+                            nullptr, nullptr, sums_fit32(ws), stream));
         hipLaunchKernelGGL(k_compare_score, dim3(1), dim3(64), 0, stream, chk_score, best_score, status, chk);
         int32_t ok = 0, err = 0;
         RP_HIP(hipMemcpyAsync(&ok, chk, sizeof(ok), hipMemcpyDeviceToHost, stream));
@@ -1331,7 +1331,7 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
     RP_HIP(hipGetLastError());
     // Validate x* and the non-regression guarantee.
     RP_TRY(eval_layouts(prob, topo, dp, lengths, q, n_rows, 1, best_layout, chk_score, status,
-                        nullptr, nullptr, nullptr, stream));
+                        nullptr, nullptr, nullptr, sums_fit32(ws), stream));
     hipLaunchKernelGGL(k_compare_score, dim3(1), dim3(64), 0, stream, chk_score, best_score, status, chk);
     int32_t ok = 0;
     RP_HIP(hipMemcpyAsync(&ok, chk, sizeof(ok), hipMemcpyDeviceToHost, stream));

@@ -76,6 +76,8 @@ struct WindowStats {
 };
 int window_stats(const routepack_problem *p, const int32_t *lengths, const int32_t *q,
                  WindowStats *out, hipStream_t stream);
+// Every sum of q entries of one layer (of any layout) is below 2^32.
+inline bool sums_fit32(const WindowStats &ws) { return ws.w_bound < ((int64_t)1 << 32); }
 // Bound of every W entry of a capacity-feasible layout: min(w_bound, q_rate * maxD * C).
 int64_t w_entry_bound(const routepack_problem *p, const WindowStats &ws);
 

@@ -3,13 +3,14 @@
 // feasibility status (Eqs. sample-bijection .. token-capacity) and the online
 // load diagnostics (Eqs. global-ep-cv and ep-efficiency).
 //
-// Pass 1, one workgroup per (layout, row-shard h = r*G + g): scan the layout
-// in 256-sample chunks, collect the chunk's members of h, add their q rows
-// into the row-shard table W_h[L][P] (int64 in LDS; each thread owns fixed
-// entries, so no atomics), and accumulate the cell statistics of h's cells.
-// Then A(h), E(h) = 2^F sum_l max_p W_h, J(h), and per-layer max/sum of W_h
-// for the diagnostics.  Pass 2, one workgroup per layout: the score tuple,
-// status and diagnostics.
+// k_eval_lists, one workgroup per layout: the cell statistics in LDS, from
+// them A of every row-shard h = r*G + g and the status, and the samples
+// grouped by row-shard.  k_eval_rows, one wave per (layout, row-shard, up to
+// 256 entries of whole layers): adds the members' q rows into W_h, then
+// J(h) = A(h) + 2^F sum_l max_p W_h and the per-layer max/sum of W_h for the
+// diagnostics.  k_eval_finalize, one workgroup per layout: the score tuple,
+// status and diagnostics.  k_eval_rowshard does the first two steps for the
+// remaining shapes (see eval_layouts).
 #include <math.h>
 
 #include "rp_device.h"
@@ -127,6 +128,198 @@ __global__ void __launch_bounds__(256) k_eval_rowshard(EvalArgs a) {
         a.Abuf[lay_idx * RG + h] = A;
         a.Jbuf[lay_idx * RG + h] = A + (e << a.F);
     }
+}
+
+struct ListArgs {
+    const int32_t *t, *layouts;
+    int32_t N, D, G, R, S;
+    int64_t C;
+    const int32_t *slots, *count, *slot_shard;
+    const int64_t *alpha, *beta;
+    int32_t *status;       // [n]
+    int64_t *Jbuf, *Abuf;  // [n][R*G], both set to A
+    int32_t *list;         // [n][N] samples grouped by row-shard
+    int32_t *hstart;       // [n][R*G + 1] where each row-shard's samples begin
+};
+
+// LDS of k_eval_lists: sum t, sum t^2 and member count of every cell, member
+// count of every row-shard, the status.
+__host__ __device__ inline size_t eval_lists_lds(int64_t B, int64_t RG) { return (size_t)(B * 20 + RG * 4 + 4); }
+
+__global__ void __launch_bounds__(1024) k_eval_lists(ListArgs a) {
+    // (a name of its own: every declaration of one name shares its alignment,
+    // and the 64-bit LDS atomics need theirs)
+    extern __shared__ __align__(16) char slists[];
+    const int32_t B = a.R * a.D, RG = a.R * a.G, N = a.N, D = a.D, G = a.G;
+    int64_t *cT = reinterpret_cast<int64_t *>(slists);  // [B]
+    int64_t *cQ = cT + B;                             // [B]
+    int32_t *cN = reinterpret_cast<int32_t *>(cQ + B);  // [B]
+    int32_t *hc = cN + B;                             // [RG] counts, then the next free place
+    int32_t *s_stat = hc + RG;                        // [1]
+    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id();
+    const int64_t lay = blockIdx.x;
+    const int32_t *cells = a.layouts + lay * N;
+    int32_t *list = a.list + lay * N, *hstart = a.hstart + lay * (RG + 1);
+    for (int32_t c = tid; c < B; c += nt) {
+        cT[c] = 0;
+        cQ[c] = 0;
+        cN[c] = 0;
+    }
+    for (int32_t h = tid; h < RG; h += nt) hc[h] = 0;
+    if (tid == 0) *s_stat = 0;
+    __syncthreads();
+    int32_t st = 0;
+    for (int32_t i = tid; i < N; i += nt) {
+        const int32_t c = cells[i];
+        if (c < 0 || c >= B) {
+            st = 1;
+            continue;
+        }
+        const int64_t ti = a.t[i];
+        const int32_t r = c / D;
+        atomicAdd(reinterpret_cast<unsigned long long *>(&cT[c]), (unsigned long long)ti);
+        atomicAdd(reinterpret_cast<unsigned long long *>(&cQ[c]), (unsigned long long)(ti * ti));
+        atomicAdd(&cN[c], 1);
+        atomicAdd(&hc[r * G + (G == 1 ? 0 : a.slot_shard[c - r * D])], 1);
+    }
+    __syncthreads();
+    // where each row-shard's list begins (first wave), A and the status (all)
+    if (tid < kWave) {
+        int32_t carry = 0;
+        for (int32_t hb = 0; hb < RG; hb += kWave) {
+            const int32_t h = hb + lane;
+            const int32_t v = h < RG ? hc[h] : 0;
+            const int32_t incl = (int32_t)wave_incl_scan(v);
+            if (h < RG) {
+                hc[h] = carry + incl - v;
+                hstart[h] = carry + incl - v;
+            }
+            carry += __builtin_amdgcn_readlane(incl, kWave - 1);
+        }
+        if (lane == 0) hstart[RG] = carry;
+    }
+    for (int32_t c = tid; c < B; c += nt) st |= (cT[c] > a.C ? 2 : 0) | (cN[c] == 0 ? 4 : 0);
+    for (int32_t h = tid; h < RG; h += nt) {
+        const int32_t r = h / G, g = h - r * G, m = a.count[g];
+        int64_t A = 0;
+        for (int s = 0; s < a.S; ++s) {
+            int64_t mx = 0;
+            for (int x = 0; x < m; ++x) {
+                const int32_t c = r * D + a.slots[g * D + x];
+                const int64_t cost = a.alpha[s] * cT[c] + a.beta[s] * cQ[c];
+                if (x == 0 || cost > mx) mx = cost;
+            }
+            A += mx;
+        }
+        a.Abuf[lay * RG + h] = A;
+        a.Jbuf[lay * RG + h] = A;
+    }
+    if (st) atomicOr(s_stat, st);
+    __syncthreads();
+    if (tid == 0) a.status[lay] = *s_stat;
+    for (int32_t i = tid; i < N; i += nt) {
+        const int32_t c = cells[i];
+        if (c < 0 || c >= B) continue;
+        const int32_t r = c / D;
+        list[atomicAdd(&hc[r * G + (G == 1 ? 0 : a.slot_shard[c - r * D])], 1)] = i;
+    }
+}
+
+struct RowArgs {
+    const int32_t *q, *list, *hstart;
+    int32_t N, L, P, RG, F;
+    int32_t lay_piece, n_pieces;  // whole layers per piece, at most 256 entries
+    int32_t spread;               // consecutive workgroups take different pieces
+    int64_t items;                // layouts * row-shards
+    int64_t *Jbuf;                // [n][RG], holds A on entry
+    int64_t *wmax, *wsum;         // [n][RG][L] or null
+};
+
+constexpr int kEvalWaves = 4;
+
+// Bound by reading q rows (each of the n layouts reads all of q) from
+// wherever they are kept: a lane holds four ranks of one layer, eight rows
+// are in flight, and the pieces (whole layers) are laid out so that the
+// slice of q that an XCD reads stays in its L2 when it fits, and in the last
+// level cache otherwise (see eval_layouts).  A piece narrower than half a
+// wave (ONE false) is read by several groups of lanes, each taking every
+// ng-th member.  Sum is uint32_t when no sum of q entries passes 2^32.
+template <bool ONE, typename Sum>
+__global__ void __launch_bounds__(kEvalWaves *kWave) k_eval_rows(RowArgs a) {
+    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const uint32_t per = (uint32_t)((a.items + kEvalWaves - 1) / kEvalWaves);  // workgroups per piece
+    const uint32_t b = blockIdx.x, np = (uint32_t)a.n_pieces;
+    const int32_t piece = (int32_t)(a.spread ? b % np : b / per);
+    const uint32_t it = (a.spread ? b / np : b % per) * kEvalWaves + wv;
+    if (it >= (uint32_t)a.items) return;
+    const uint32_t lay = it / (uint32_t)a.RG;
+    const int32_t h = (int32_t)(it - lay * (uint32_t)a.RG);
+    const int32_t *list = a.list + (int64_t)lay * a.N, *hs = a.hstart + (int64_t)lay * (a.RG + 1) + h;
+    const int32_t lo = hs[0], n = hs[1] - lo;
+    const int32_t l0 = piece * a.lay_piece, nl = a.lay_piece < a.L - l0 ? a.lay_piece : a.L - l0;
+    const int32_t g4 = a.P >> 2, w4 = nl * g4;  // 16-byte words of a layer, of the piece
+    const int32_t ng = ONE ? 1 : kWave / w4, grp = ONE ? 0 : lane / w4, col = lane - grp * w4;
+    const bool act = ONE ? lane < w4 : grp < ng;
+    const int64_t stride = (int64_t)a.L * a.P;
+    const int32_t *base = a.q + (int64_t)l0 * a.P + 4 * (act ? col : 0);
+    Sum acc[4] = {0, 0, 0, 0};
+    constexpr int U = 8;
+    for (int32_t mb = 0; mb < n; mb += kWave) {
+        const int32_t lim = n - mb < kWave ? n - mb : kWave;
+        const int32_t ids = list[lo + (mb + lane < n ? mb + lane : 0)];
+        for (int32_t m = 0; m < lim; m += U * ng) {
+            int4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t x = m + u * ng + grp;
+                if (ONE) {
+                    const int32_t i = __builtin_amdgcn_readlane(ids, x < lim ? x : 0);
+                    v[u] = *reinterpret_cast<const int4 *>(base + i * stride);
+                } else {
+                    const int32_t i = __shfl(ids, x < lim ? x : 0, kWave);
+                    v[u] = *reinterpret_cast<const int4 *>(base + i * stride);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (m + u * ng + grp < lim) {
+                    acc[0] += (Sum)v[u].x;
+                    acc[1] += (Sum)v[u].y;
+                    acc[2] += (Sum)v[u].z;
+                    acc[3] += (Sum)v[u].w;
+                }
+            }
+        }
+    }
+    int64_t s4[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s4[c] = (int64_t)acc[c];
+    if (!ONE)
+        for (int32_t k = 1; k < ng; ++k) {
+            const int src = lane + k * w4;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int64_t o = (int64_t)__shfl(acc[c], src < kWave ? src : lane, kWave);
+                s4[c] += lane < w4 ? o : 0;
+            }
+        }
+    int64_t mx = s4[0], sm = s4[0] + s4[1] + s4[2] + s4[3];
+#pragma unroll
+    for (int c = 1; c < 4; ++c) mx = s4[c] > mx ? s4[c] : mx;
+    int64_t o;
+    if (g4 >= 2) { o = dpp64<kDppXor1>(mx, mx); mx = o > mx ? o : mx; sm += dpp64<kDppXor1>(sm, 0); }
+    if (g4 >= 4) { o = dpp64<kDppXor2>(mx, mx); mx = o > mx ? o : mx; sm += dpp64<kDppXor2>(sm, 0); }
+    if (g4 >= 8) { o = dpp64<kDppHalfMirror>(mx, mx); mx = o > mx ? o : mx; sm += dpp64<kDppHalfMirror>(sm, 0); }
+    if (g4 >= 16) { o = dpp64<kDppMirror>(mx, mx); mx = o > mx ? o : mx; sm += dpp64<kDppMirror>(sm, 0); }
+    const bool head = lane < w4 && (lane & (g4 - 1)) == 0;
+    if (a.wmax && head) {
+        const int64_t at = (int64_t)it * a.L + l0 + lane / g4;
+        a.wmax[at] = mx;
+        a.wsum[at] = sm;
+    }
+    const int64_t esum = wave_sum(head ? mx : 0);
+    if (lane == 0)
+        atomicAdd(reinterpret_cast<unsigned long long *>(a.Jbuf + it), (unsigned long long)esum << a.F);
 }
 
 __device__ inline double wave_sum_d(double v) {
@@ -283,11 +476,12 @@ __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v) {
 }
 
 // Scores `n` layouts already on the device; used by the public entry point
-// and by the packing path.  status must hold n int32.
+// and by the packing and annealing paths.  status must hold n int32; sum32:
+// every layer's total of q is below 2^32 (so is any sum of its entries).
 int eval_layouts(const routepack_problem *p, const Topology &topo, const DeviceProblem &dp,
                  const int32_t *t, const int32_t *q, int32_t R, int64_t n, const int32_t *layouts,
                  int64_t *scores, int32_t *status, int64_t *J, double *diag,
-                 const int64_t *rank_load, hipStream_t stream) {
+                 const int64_t *rank_load, bool sum32, hipStream_t stream) {
     if (n == 0) return ROUTEPACK_OK;
     const int64_t RG = (int64_t)R * topo.G, LP = (int64_t)p->n_layers * p->n_ranks;
     if (LP > 16384) return ROUTEPACK_E_UNSUPPORTED;
@@ -297,18 +491,74 @@ int eval_layouts(const routepack_problem *p, const Topology &topo, const DeviceP
     int64_t *wmax = scr.get<int64_t>(n * RG * (p->n_layers ? p->n_layers : 1));
     int64_t *wsum = scr.get<int64_t>(n * RG * (p->n_layers ? p->n_layers : 1));
     if (scr.failed()) return ROUTEPACK_E_DEVICE;
-    hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024)),
-                       dim3(256), 0, stream, status, n, 0);
-    EvalArgs a;
-    a.t = t; a.q = q; a.layouts = layouts;
-    a.N = p->n_samples; a.L = p->n_layers; a.P = p->n_ranks; a.D = topo.D; a.G = topo.G; a.R = R;
-    a.S = p->n_stages; a.F = p->frac_bits; a.C = p->capacity;
-    a.slots = dp.slots; a.count = dp.count; a.slot_shard = dp.slot_shard;
-    a.alpha = dp.alpha; a.beta = dp.beta;
-    a.status = status; a.Jbuf = Jbuf; a.Abuf = Abuf; a.wmax = wmax; a.wsum = wsum;
-    const size_t lds = (size_t)LP * 8 + (size_t)topo.D * 20 + 256 * 4 + 64 + 64;
-    if (lds > 160 * 1024) return ROUTEPACK_E_UNSUPPORTED;
-    hipLaunchKernelGGL(k_eval_rowshard, dim3((unsigned)(n * RG)), dim3(256), lds, stream, a);
+    const int64_t B = (int64_t)R * topo.D, L = p->n_layers, P = p->n_ranks, N = p->n_samples;
+    // The list path: a power-of-two rank count from 4 to 64 (a layer's ranks
+    // on up to 16 adjacent lanes), 16-byte rows and cell statistics that fit
+    // LDS next to a second workgroup's.  1024 layouts of 3971 samples (24 x
+    // 16, 112 row-shards): 2.3 ms with a scan of the layout per row-shard,
+    // 0.62 ms with lists; 16 layouts of 32768 samples (64 x 64, 62): 21.5 ms
+    // and 2.1 ms.
+    const bool lists = L > 0 && P >= 4 && P <= 64 && (P & (P - 1)) == 0 && ((uintptr_t)q & 15) == 0 &&
+                       eval_lists_lds(B, RG) <= 60 * 1024;
+    if (lists) {
+        ListArgs la;
+        la.t = t; la.N = (int32_t)N; la.D = topo.D; la.G = topo.G; la.R = R; la.S = p->n_stages; la.C = p->capacity;
+        la.slots = dp.slots; la.count = dp.count; la.slot_shard = dp.slot_shard;
+        la.alpha = dp.alpha; la.beta = dp.beta;
+        RowArgs ra;
+        ra.q = q; ra.N = (int32_t)N; ra.L = (int32_t)L; ra.P = (int32_t)P; ra.RG = (int32_t)RG; ra.F = p->frac_bits;
+        // Workgroups go round the 8 XCDs: with 2, 4 or 8 pieces and
+        // consecutive workgroups on different ones, an XCD reads only its
+        // piece's slice of q, worth it when that slice stays in a 4 MiB L2
+        // (up to 2 MiB: the lists pass through it too); else one piece at a
+        // time, whose slice all XCDs share in the last level cache.
+        const int64_t most = 256 / P;
+        int32_t np = 1;
+        while (np <= 8 && ((L + np - 1) / np > most || N * ((L + np - 1) / np) * P * 4 > (int64_t)2 << 20)) np *= 2;
+        ra.spread = np <= 8 ? 1 : 0;
+        if (!ra.spread) np = (int32_t)((L + most - 1) / most);
+        ra.lay_piece = (int32_t)((L + np - 1) / np);
+        ra.n_pieces = (int32_t)((L + ra.lay_piece - 1) / ra.lay_piece);
+        // the sample lists of at most 64 Mi entries at a time
+        int64_t nb = ((int64_t)64 << 20) / N;
+        nb = nb < 1 ? 1 : (nb > n ? n : nb);
+        nb = nb * RG * ra.n_pieces < ((int64_t)1 << 31) ? nb : ((int64_t)1 << 31) / (RG * ra.n_pieces);
+        int32_t *list = scr.get<int32_t>((size_t)(nb * N)), *hstart = scr.get<int32_t>((size_t)(nb * (RG + 1)));
+        if (scr.failed()) return ROUTEPACK_E_DEVICE;
+        la.list = list; la.hstart = hstart;
+        ra.list = list; ra.hstart = hstart;
+        for (int64_t l0 = 0; l0 < n; l0 += nb) {
+            const int64_t m = nb < n - l0 ? nb : n - l0;
+            la.layouts = layouts + l0 * N;
+            la.status = status + l0;
+            la.Jbuf = Jbuf + l0 * RG;
+            la.Abuf = Abuf + l0 * RG;
+            // few layouts: more threads for each
+            const int threads = m >= 512 || N <= 1024 ? 256 : 1024;
+            hipLaunchKernelGGL(k_eval_lists, dim3((unsigned)m), dim3(threads), eval_lists_lds(B, RG), stream, la);
+            ra.items = m * RG;
+            ra.Jbuf = Jbuf + l0 * RG;
+            ra.wmax = diag ? wmax + l0 * RG * L : nullptr;
+            ra.wsum = diag ? wsum + l0 * RG * L : nullptr;
+            const int64_t wgs = (ra.items + kEvalWaves - 1) / kEvalWaves * ra.n_pieces;
+            auto rows = ra.lay_piece * P > 128 ? (sum32 ? k_eval_rows<true, uint32_t> : k_eval_rows<true, int64_t>)
+                                               : (sum32 ? k_eval_rows<false, uint32_t> : k_eval_rows<false, int64_t>);
+            hipLaunchKernelGGL(rows, dim3((unsigned)wgs), dim3(kEvalWaves * kWave), 0, stream, ra);
+        }
+    } else {
+        hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024)),
+                           dim3(256), 0, stream, status, n, 0);
+        EvalArgs a;
+        a.t = t; a.q = q; a.layouts = layouts;
+        a.N = p->n_samples; a.L = p->n_layers; a.P = p->n_ranks; a.D = topo.D; a.G = topo.G; a.R = R;
+        a.S = p->n_stages; a.F = p->frac_bits; a.C = p->capacity;
+        a.slots = dp.slots; a.count = dp.count; a.slot_shard = dp.slot_shard;
+        a.alpha = dp.alpha; a.beta = dp.beta;
+        a.status = status; a.Jbuf = Jbuf; a.Abuf = Abuf; a.wmax = wmax; a.wsum = wsum;
+        const size_t lds = (size_t)LP * 8 + (size_t)topo.D * 20 + 256 * 4 + 64 + 64;
+        if (lds > 160 * 1024) return ROUTEPACK_E_UNSUPPORTED;
+        hipLaunchKernelGGL(k_eval_rowshard, dim3((unsigned)(n * RG)), dim3(256), lds, stream, a);
+    }
     FinalArgs f;
     f.L = p->n_layers; f.P = p->n_ranks; f.G = topo.G; f.R = R;
     f.scale = ldexp((double)p->capacity, p->frac_bits);
@@ -341,7 +591,7 @@ extern "C" int routepack_eval_objective(const routepack_problem *prob, const int
     DeviceProblem dp;
     RP_TRY(upload_problem(prob, topo, scr, &dp, stream));
     RP_TRY(eval_layouts(prob, topo, dp, lengths, q, n_rows, n_layouts, layouts, scores, status, J,
-                        diag, rank_load, stream));
+                        diag, rank_load, sums_fit32(ws), stream));
     RP_HIP(hipStreamSynchronize(stream));
     return ROUTEPACK_OK;
 }

@@ -33,7 +33,7 @@ namespace rp {
 int eval_layouts(const routepack_problem *p, const Topology &topo, const DeviceProblem &dp,
                  const int32_t *t, const int32_t *q, int32_t R, int64_t n, const int32_t *layouts,
                  int64_t *scores, int32_t *status, int64_t *J, double *diag,
-                 const int64_t *rank_load, hipStream_t stream);
+                 const int64_t *rank_load, bool sum32, hipStream_t stream);
 __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v);
 
 constexpr int kMaxCells = 4096;
@@ -1241,7 +1241,7 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
     // Score every candidate (failed trials leave garbage layouts: their
     // status is nonzero or they are ignored by the selection).
     RP_TRY(eval_layouts(prob, topo, dp, lengths, q, (int32_t)R, M, cand, cscore, cstat, nullptr,
-                        nullptr, nullptr, stream));
+                        nullptr, nullptr, sums_fit32(ws), stream));
     hipLaunchKernelGGL(k_canonical, dim3(M), dim3(256), 0, stream, cand, M, N, (int32_t)R, D, G,
                        dp.slots, dp.count, dp.slot_shard, cmin, newc, rkey, canon);
     hipLaunchKernelGGL(k_pack_select, dim3(1), dim3(256), 0, stream, canon, cscore, okv, cstat, M, N, keep,
