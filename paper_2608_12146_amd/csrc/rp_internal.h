@@ -97,6 +97,7 @@ struct DeviceProblem {
     int32_t *count = nullptr;   // [G]
     int32_t *slot_shard = nullptr;  // [D] = dp_to_edp
     int64_t *alpha = nullptr, *beta = nullptr;  // [S]
+    std::vector<char> host;  // their source, kept until the call's stream work is done
 };
 int upload_problem(const routepack_problem *p, const Topology &topo, Scratch &scr,
                    DeviceProblem *dp, hipStream_t stream);
