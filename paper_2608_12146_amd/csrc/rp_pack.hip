@@ -413,8 +413,8 @@ __global__ void __launch_bounds__(64) k_pack_trials(TrialArgs a) {
 //                  lengths prefetched 64 steps ahead into lane registers; the
 //                  ranked pick compares 64-bit keys (load, then fewer
 //                  members, then lower index) with DPP maxima.  Ends with the
-//                  member list of every cell.  k_pack_fit_reg keeps the keys
-//                  in registers up to 2048 cells, k_pack_fit in LDS above.
+//                  member list of every cell.  Up to 2048 cells
+//                  k_pack_fit_sorted keeps the keys sorted instead.
 //  k_pack_cellsum  one workgroup per (candidate, cell): Q_k = sum of the
 //                  member rows and peak_k = sum_l max_p Q_k.
 //  k_pack_pair     one workgroup per candidate: EDPAwarePair with the W table
@@ -582,97 +582,77 @@ __global__ void __launch_bounds__(64) k_pack_fit(TrialArgs a, PackFast pf) {
     }
 }
 
-// k_pack_fit for K <= 64 NCH cells: lane x holds the keys of cells x,
-// x + 64, ... in registers, so the ranked passes need no LDS traffic and a
-// placement updates one lane.  A key carries the load in its high 32 bits
-// (C < 2^31) and 0xFFFF - members below, so "the item fits" is one compare,
-// key < (C - t + 1) << 32, and a placement adds (t << 32) - (1 << 16).  The
-// draws, the window's next items and their lengths are loaded one block of
-// 64 steps ahead, and each step's (item, cell) stays in the register of lane
-// (step mod 64) until its block ends, so no step waits on memory.
-template <int NCH>
-__global__ void __launch_bounds__(64) k_pack_fit_reg(TrialArgs a, PackFast pf) {
-    extern __shared__ int32_t sfitr[];  // [K] counts, then [K] cursors
-    const int lane = lane_id();
-    const int b = blockIdx.x;
-    const int32_t N = a.N, K = a.K;
-    int32_t *cnt_s = sfitr, *cur = sfitr + K;
-    int32_t *cellk = a.cellk + (int64_t)b * N;
-    uint64_t kr[NCH];
-#pragma unroll
-    for (int u = 0; u < NCH; ++u) {
-        const int32_t c = u * kWave + lane;
-        kr[u] = c < K ? fit_key(0, 0, c) : ~(uint64_t)0;  // a missing cell never fits
-    }
-    int32_t good = 1;
-    if (b == 0) {
-        for (int32_t c = lane; c < K; c += kWave) cnt_s[c] = 0;
-        __syncthreads();
-        for (int32_t i = lane; i < N; i += kWave) {
-            const int32_t c = a.x_length[i];
-            cellk[i] = c;
-            atomicAdd(&cnt_s[c], 1);
-        }
-    } else {
-        const int32_t w = a.w;
-        const uint64_t *wd = a.words + (int64_t)(b - 1) * (2 * (int64_t)N + K);
-        int32_t win = -1, wint = 0;
+// Lane i's value becomes lane i + 1's (lane 63: 0), or lane i - 1's (lane 0: 0).
+__device__ inline int32_t lane_up(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xF, 0xF, true); }
+__device__ inline int32_t lane_down(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, true); }
+__device__ inline uint64_t lane_up64(uint64_t v) {
+    return (uint64_t)(uint32_t)lane_up((int32_t)(uint32_t)v) |
+           (uint64_t)(uint32_t)lane_up((int32_t)(uint32_t)(v >> 32)) << 32;
+}
+__device__ inline uint64_t lane_down64(uint64_t v) {
+    return (uint64_t)(uint32_t)lane_down((int32_t)(uint32_t)v) |
+           (uint64_t)(uint32_t)lane_down((int32_t)(uint32_t)(v >> 32)) << 32;
+}
+__device__ inline uint64_t low_lanes(int n) { return n >= kWave ? ~(uint64_t)0 : ((uint64_t)1 << n) - 1; }
+__device__ inline bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
+// Orders a wave's LDS accesses before its later ones by other lanes.
+__device__ inline void lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// WindowShuffle of one trial, one wave: lane x < wsize of (win, wint) holds
+// the x-th item of the window and its length; the items that enter it are
+// loaded one block of 64 ahead.
+struct Shuffle {
+    const int32_t *sigma, *t;
+    const uint64_t *wd;  // [N] draws
+    int32_t N, w, win, wint, next, wsize, sbase, s0, s1, s2, t0, t1, hbase;
+    uint64_t word;       // the draws of the next block
+    __device__ inline void init(const int32_t *sigma_, const int32_t *t_, const uint64_t *wd_, int32_t N_, int32_t w_) {
+        const int lane = lane_id();
+        sigma = sigma_; t = t_; wd = wd_; N = N_; w = w_;
+        win = -1;
+        wint = 0;
         if (lane < w && lane < N) {
-            win = a.sigma[lane];
-            wint = a.t[win];
+            win = sigma[lane];
+            wint = t[win];
         }
-        int32_t next = w < N ? w : N, wsize = next;
-        // items entering the window: this block (s0, t0), the next (s1, t1)
-        // and the items of the one after (s2), whose lengths are loaded when
-        // it becomes the next
-        int32_t sbase = next;
+        next = w < N ? w : N;
+        wsize = next;
+        sbase = next;
         const int32_t i0 = sbase + lane, i1 = i0 + kWave, i2 = i1 + kWave;
-        int32_t s0 = i0 < N ? a.sigma[i0] : 0, s1 = i1 < N ? a.sigma[i1] : 0;
-        int32_t s2 = i2 < N ? a.sigma[i2] : 0;
-        int32_t t0 = i0 < N ? a.t[s0] : 0, t1 = i1 < N ? a.t[s1] : 0;
-        // draws: shuffle word h and best-fit word h, this block and the next
-        int32_t hbase = 0;
-        uint64_t wr1 = lane < N ? wd[lane] : 0, wr2 = lane < N ? wd[N + lane] : 0;
-        uint64_t nw1 = kWave + lane < N ? wd[kWave + lane] : 0;
-        uint64_t nw2 = kWave + lane < N ? wd[N + kWave + lane] : 0;
-        // Step hb + lane's window position (the window holds min(w, N - h)
-        // items at step h) and its rank when w or more cells fit, drawn when
-        // the block becomes current.
-        auto draws = [&](int32_t hb, int32_t &pos_l, int32_t &rho_l) {
-            const int32_t hh = hb + lane, ws = w < N - hh ? w : N - hh;
-            pos_l = hh < N ? (int32_t)bounded(wr1, (uint64_t)ws) : 0;
-            rho_l = (int32_t)bounded(wr2, (uint64_t)w);
-        };
-        int32_t pos_l, rho_l;
-        draws(0, pos_l, rho_l);
-        int32_t p_item = -1, p_cell = 0;  // step hbase + lane's placement
-        for (int32_t h = 0; h < N; ++h) {
-            if (h - hbase == kWave) {
-                if (p_item >= 0) cellk[p_item] = p_cell;
-                p_item = -1;
-                hbase += kWave;
-                wr1 = nw1;
-                wr2 = nw2;
-                draws(hbase, pos_l, rho_l);
-                const int32_t hn = hbase + kWave + lane;
-                nw1 = hn < N ? wd[hn] : 0;
-                nw2 = hn < N ? wd[N + hn] : 0;
-            }
-            const int32_t pos = __builtin_amdgcn_readlane(pos_l, h - hbase);
+        s0 = i0 < N ? sigma[i0] : 0;
+        s1 = i1 < N ? sigma[i1] : 0;
+        s2 = i2 < N ? sigma[i2] : 0;
+        t0 = i0 < N ? t[s0] : 0;
+        t1 = i1 < N ? t[s1] : 0;
+        hbase = 0;
+        word = lane < N ? wd[lane] : 0;
+    }
+    // The next up to 64 items of the order, lane x the x-th, with lengths.
+    __device__ inline void block(int32_t &item_l, int32_t &t_l) {
+        const int lane = lane_id();
+        const int32_t hh = hbase + lane, ws = w < N - hh ? w : N - hh;
+        const int32_t pos_l = hh < N ? (int32_t)bounded(word, (uint64_t)ws) : 0;
+        const int32_t hn = hh + kWave;
+        word = hn < N ? wd[hn] : 0;
+        const int32_t cnt = N - hbase < kWave ? N - hbase : kWave;
+        item_l = 0;
+        t_l = 0;
+        for (int32_t x = 0; x < cnt; ++x) {
+            const int32_t pos = __builtin_amdgcn_readlane(pos_l, x);
             const int32_t item = __builtin_amdgcn_readlane(win, pos);
             const int32_t ti = __builtin_amdgcn_readlane(wint, pos);
-            int32_t up, upt;
-            if (w <= 16) {  // row_shl:1 -- lane i reads lane i + 1 of its 16-lane row
-                up = __builtin_amdgcn_update_dpp(win, win, 0x101, 0xF, 0xF, false);
-                upt = __builtin_amdgcn_update_dpp(wint, wint, 0x101, 0xF, 0xF, false);
-            } else {
-                up = __shfl_down(win, 1, kWave);
-                upt = __shfl_down(wint, 1, kWave);
-            }
-            if (lane >= pos && lane < wsize - 1) {
-                win = up;
-                wint = upt;
-            }
+            const bool mine = lane_in((uint64_t)1 << x);
+            item_l = mine ? item : item_l;
+            t_l = mine ? ti : t_l;
+            const int32_t up = lane_up(win), upt = lane_up(wint);
+            const bool sh = lane >= pos;  // (lanes past the window hold nothing that is read)
+            win = sh ? up : win;
+            wint = sh ? upt : wint;
             if (next < N) {
                 if (next - sbase == kWave) {
                     sbase += kWave;
@@ -680,90 +660,227 @@ __global__ void __launch_bounds__(64) k_pack_fit_reg(TrialArgs a, PackFast pf) {
                     t0 = t1;
                     s1 = s2;
                     const int32_t j1 = sbase + kWave + lane, j2 = j1 + kWave;
-                    t1 = j1 < N ? a.t[s1] : 0;
-                    s2 = j2 < N ? a.sigma[j2] : 0;
+                    t1 = j1 < N ? t[s1] : 0;
+                    s2 = j2 < N ? sigma[j2] : 0;
                 }
                 const int32_t ni = __builtin_amdgcn_readlane(s0, next - sbase);
                 const int32_t nt = __builtin_amdgcn_readlane(t0, next - sbase);
-                if (lane == wsize - 1) {
-                    win = ni;
-                    wint = nt;
-                }
+                const bool last = lane == wsize - 1;
+                win = last ? ni : win;
+                wint = last ? nt : wint;
                 ++next;
             } else {
-                if (lane == wsize - 1) {
-                    win = -1;
-                    wint = 0;
-                }
                 --wsize;
             }
-            int32_t c;
-            if (h < K) {
-                c = h;
-            } else {
-                const uint64_t lim = ti <= a.C ? (uint64_t)(a.C - ti + 1) << 32 : 0;
-                uint64_t best = 0;
-                int32_t nf = 0;
-#pragma unroll
-                for (int u = 0; u < NCH; ++u) {
-                    const bool f = kr[u] < lim;
-                    nf += __popcll(__ballot(f));
-                    if (f && kr[u] > best) best = kr[u];
-                }
-                if (nf == 0) {
-                    good = 0;
-                    break;
-                }
-                best = wave_max_u64(best);
-                const int32_t rho = nf >= w ? __builtin_amdgcn_readlane(rho_l, h - hbase)
-                                            : (int32_t)bounded(readlane64(wr2, h - hbase), (uint64_t)nf);
-                // a key below a fitting key fits too
-                for (int32_t pass = 1; pass <= rho; ++pass) {
-                    const uint64_t prev = best;
-                    best = 0;
-#pragma unroll
-                    for (int u = 0; u < NCH; ++u)
-                        if (kr[u] < prev && kr[u] > best) best = kr[u];
-                    best = wave_max_u64(best);
-                }
-                c = 0xFFFF - (int32_t)(best & 0xFFFF);
+        }
+        hbase += kWave;
+    }
+};
+
+constexpr int kFitThreads = 256;
+constexpr int kFitRow = 64, kFitFill = 32;          // keys a row can hold, and after a rebuild
+constexpr int kFitSortedCells = kWave * kFitFill;   // 2048
+
+// LDS of k_pack_fit_sorted: the rows, a linear copy of the keys (later the
+// member lists' counts and cursors), two blocks of items, a flag.
+__host__ __device__ inline int fit_rows(int32_t K) { return (K + kFitFill - 1) / kFitFill; }
+__host__ __device__ inline size_t fit_sorted_lds(int32_t K) {
+    return (size_t)fit_rows(K) * kFitRow * 8 + (size_t)K * 8 + 2 * kWave * 8 + 16;
+}
+
+// k_pack_fit for up to 2048 cells.  The N - K best-fit steps are one serial
+// chain, so its length in cycles bounds the kernel.  The cells' keys
+//   (2^32 - 1 - T) << 32 | members << 16 | cell
+// (ascending = RandomizedBestFit order; t fits iff key >= (2^32 - 1 - (C - t))
+// << 32) are kept sorted in up to 64 rows of at most 64 keys in LDS, lane r
+// holding row r's first key when built and its count.  A step finds the row
+// (one compare and a ballot), the first fitting key in it (one row read, one
+// ballot), takes the key rho places on, shifts it out, and shifts its new
+// value, which comes earlier, into its row; a row that fills up has the keys
+// spread over the rows again.  A second wave runs the shuffle, which does not
+// depend on the cells, one block of 64 items ahead.  Keeping the keys unsorted
+// in registers (each step a wave maximum per rank over all cells) took
+// 4.5 ms for 4096 samples in 400 cells and 90 ms for 32768 in 1984; now
+// 1.7 ms and 14.7 ms.
+__global__ void __launch_bounds__(kFitThreads) k_pack_fit_sorted(TrialArgs a, PackFast pf) {
+    extern __shared__ __align__(16) uint64_t sfs[];
+    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id()), tid = threadIdx.x;
+    const int b = blockIdx.x;
+    const int32_t N = a.N, K = a.K, w = a.w;
+    const int32_t nrow = fit_rows(K);
+    uint64_t *rows = sfs, *lin = rows + nrow * kFitRow;
+    int2 *ring = reinterpret_cast<int2 *>(lin + K);  // [2][64] items and lengths
+    // cleared by wave 0 when a step finds no cell; iteration j writes entry
+    // (j + 1) & 1 and reads entry j & 1, so no wave reads what is being written
+    int32_t *s_good = reinterpret_cast<int32_t *>(ring + 2 * kWave);
+    int32_t *cellk = a.cellk + (int64_t)b * N;
+    int32_t *cnt_s = reinterpret_cast<int32_t *>(lin), *cur = cnt_s + K;
+    if (tid < 2) s_good[tid] = 1;
+    if (b == 0) {
+        for (int32_t c = tid; c < K; c += kFitThreads) cnt_s[c] = 0;
+        __syncthreads();
+        for (int32_t i = tid; i < N; i += kFitThreads) {
+            const int32_t c = a.x_length[i];
+            cellk[i] = c;
+            atomicAdd(&cnt_s[c], 1);
+        }
+    } else {
+        const uint64_t *wd = a.words + (int64_t)(b - 1) * (2 * (int64_t)N + K);
+        const uint32_t Cu = 0xFFFFFFFFu - (uint32_t)a.C;
+        Shuffle sh;
+        if (wv == 1) {
+            sh.init(a.sigma, a.t, wd, N, w);
+            int32_t it, tt;
+            sh.block(it, tt);
+            ring[lane] = make_int2(it, tt);
+        }
+        uint64_t word = wv == 0 && lane < N ? wd[N + lane] : 0;  // wave 0: this block's best-fit draws
+        uint64_t sep = 0;  // wave 0, lane r: row r holds the keys from sep on, below row r + 1's
+        int32_t cnt = 0;   // and its number of keys
+        const int32_t nblk = (N + kWave - 1) / kWave, jsort = (K - 1) / kWave;
+        for (int32_t j = 0; j < nblk; ++j) {
+            __syncthreads();
+            if (!s_good[j & 1]) break;
+            const int32_t h0 = j * kWave, hn = h0 + kWave;
+            if (wv == 1 && j + 1 < nblk) {
+                int32_t it, tt;
+                sh.block(it, tt);
+                ring[((j + 1) & 1) * kWave + lane] = make_int2(it, tt);
             }
-            // c is uniform: only its chunk's owner lane changes (a select per
-            // chunk, so every register index stays static)
-            const int32_t cu = c >> 6;
-            const bool own = (c & (kWave - 1)) == lane;
-            const uint64_t add = own ? ((uint64_t)(uint32_t)ti << 32) - ((uint64_t)1 << 16) : 0;
-#pragma unroll
-            for (int u = 0; u < NCH; ++u) kr[u] += u == cu ? add : 0;
-            if (lane == h - hbase) {
-                p_item = item;
-                p_cell = c;
+            int32_t item_l = 0, t_l = 0, cell_l = 0, rho_l = 0;
+            uint64_t nword = 0;
+            if (wv == 0) {
+                const int2 v = ring[(j & 1) * kWave + lane];
+                item_l = v.x;
+                t_l = v.y;
+                cell_l = h0 + lane;  // the first K items open the cells
+                if (h0 + lane < K && h0 + lane < N)
+                    lin[h0 + lane] = ((uint64_t)(0xFFFFFFFFu - (uint32_t)t_l) << 32) | (1u << 16) | (uint32_t)(h0 + lane);
+                rho_l = (int32_t)bounded(word, (uint64_t)w);
+                nword = hn + lane < N ? wd[N + hn + lane] : 0;
+            }
+            if (j == jsort) {  // every cell is open: rank the keys by counting
+                __syncthreads();
+                for (int32_t c = tid; c < K; c += kFitThreads) {
+                    const uint64_t v = lin[c];
+                    int32_t rank = 0;
+#pragma unroll 8
+                    for (int32_t f = 0; f < K; ++f) rank += lin[f] < v ? 1 : 0;
+                    rows[rank / kFitFill * kFitRow + rank % kFitFill] = v;
+                }
+                __syncthreads();
+                if (wv == 0) {
+                    const int32_t left = K - lane * kFitFill;
+                    cnt = left < 0 ? 0 : (left < kFitFill ? left : kFitFill);
+                    sep = lane == 0 ? 0 : (cnt > 0 ? rows[lane * kFitRow] : ~(uint64_t)0);
+                }
+            }
+            if (wv == 0 && hn > K) {
+                const int32_t x0 = K > h0 ? K - h0 : 0, x1 = N - h0 < kWave ? N - h0 : kWave;
+                for (int32_t x = x0; x < x1; ++x) {
+                    const int32_t ti = __builtin_amdgcn_readlane(t_l, x);
+                    const uint64_t lim = (uint64_t)(Cu + (uint32_t)ti) << 32;
+                    int32_t r = __popcll(__ballot(sep <= lim)) - 1;
+                    uint64_t e = rows[r * kFitRow + lane];
+                    int32_t n = __builtin_amdgcn_readlane(cnt, r);
+                    int32_t p = __popcll(__ballot(e < lim) & low_lanes(n));
+                    int32_t rho = __builtin_amdgcn_readlane(rho_l, x);
+                    if (n - p < w) {
+                        // fewer than w left in the row: the draw is over the
+                        // min(w, fitting) first, which may be in later rows
+                        const int32_t nf = n - p + (int32_t)wave_sum((int64_t)(lane > r ? cnt : 0));
+                        if (nf == 0) {
+                            if (lane == 0) s_good[(j + 1) & 1] = 0;
+                            break;
+                        }
+                        if (nf < w) rho = (int32_t)bounded(readlane64(word, x), (uint64_t)nf);
+                        if (rho >= n - p) {
+                            rho -= n - p;
+                            p = 0;
+                            n = __builtin_amdgcn_readlane(cnt, ++r);
+                            while (rho >= n) {  // (rho < nf: a later row holds it)
+                                rho -= n;
+                                n = __builtin_amdgcn_readlane(cnt, ++r);
+                            }
+                            e = rows[r * kFitRow + lane];
+                        }
+                    }
+                    const int32_t at = p + rho;
+                    const uint64_t key = readlane64(e, at);
+                    const uint64_t nk = key - ((uint64_t)(uint32_t)ti << 32) + (1u << 16);
+                    cell_l = lane_in((uint64_t)1 << x) ? (int32_t)(key & 0xFFFF) : cell_l;
+                    int32_t r2 = __popcll(__ballot(sep <= nk)) - 1;
+                    const uint64_t up = lane_up64(e);
+                    e = lane_in(~low_lanes(at)) ? up : e;
+                    if (r2 != r) {
+                        rows[r * kFitRow + lane] = e;
+                        cnt -= lane_in((uint64_t)1 << r) ? 1 : 0;
+                        lds_order();
+                        if (__builtin_amdgcn_readlane(cnt, r2) == kFitRow) {
+                            // spread the K - 1 keys over the rows again
+                            const int32_t pre = (int32_t)wave_incl_scan((int64_t)cnt) - cnt;
+                            for (int32_t k = 0; k < nrow; ++k) {
+                                const int32_t nk_ = __builtin_amdgcn_readlane(cnt, k), ok_ = __builtin_amdgcn_readlane(pre, k);
+                                if (lane < nk_) lin[ok_ + lane] = rows[k * kFitRow + lane];
+                            }
+                            lds_order();
+                            for (int32_t k = lane; k < K - 1; k += kWave) rows[k / kFitFill * kFitRow + k % kFitFill] = lin[k];
+                            const int32_t left = K - 1 - lane * kFitFill;
+                            cnt = left < 0 ? 0 : (left < kFitFill ? left : kFitFill);
+                            sep = lane == 0 ? 0 : (cnt > 0 ? lin[lane * kFitFill] : ~(uint64_t)0);
+                            lds_order();
+                            r2 = __popcll(__ballot(sep <= nk)) - 1;
+                        }
+                        e = rows[r2 * kFitRow + lane];
+                        n = __builtin_amdgcn_readlane(cnt, r2);
+                        cnt += lane_in((uint64_t)1 << r2) ? 1 : 0;
+                    } else {
+                        --n;
+                    }
+                    const int32_t p2 = __popcll(__ballot(e < nk) & low_lanes(n));
+                    const uint64_t down = lane_down64(e);
+                    e = lane_in(~low_lanes(p2)) ? down : e;
+                    e = lane_in((uint64_t)1 << p2) ? nk : e;
+                    rows[r2 * kFitRow + lane] = e;
+                    lds_order();
+                }
+            }
+            if (wv == 0) {
+                if (h0 + lane < N) cellk[item_l] = cell_l;
+                word = nword;
             }
         }
-        if (p_item >= 0) cellk[p_item] = p_cell;
-#pragma unroll
-        for (int u = 0; u < NCH; ++u)
-            if (u * kWave + lane < K) cnt_s[u * kWave + lane] = 0xFFFF - (int32_t)((kr[u] >> 16) & 0xFFFF);
+        __syncthreads();
+        const int32_t good = s_good[0] & s_good[1];
+        if (tid == 0) a.ok[b] = good;
+        if (!good) return;
+        // member counts by cell (the keys' linear copy is no longer used)
+        if (wv == 0)
+            for (int32_t r = 0; r < nrow; ++r) {
+                const uint64_t e = rows[r * kFitRow + lane];
+                if (lane < __builtin_amdgcn_readlane(cnt, r)) cnt_s[e & 0xFFFF] = (int32_t)((e >> 16) & 0xFFFF);
+            }
     }
-    if (lane == 0) a.ok[b] = good;
-    if (!good) return;
+    if (b == 0 && tid == 0) a.ok[b] = 1;
     __syncthreads();
     int32_t *ms = pf.mstart + (int64_t)b * (K + 1);
     int32_t *ml = pf.mlist + (int64_t)b * N;
-    int64_t carry = 0;
-    for (int32_t cb = 0; cb < K; cb += kWave) {
-        const int32_t cc = cb + lane;
-        const int64_t v = cc < K ? cnt_s[cc] : 0;
-        const int64_t incl = wave_incl_scan(v);
-        if (cc < K) {
-            ms[cc] = (int32_t)(carry + incl - v);
-            cur[cc] = (int32_t)(carry + incl - v);
+    if (wv == 0) {
+        int32_t carry = 0;
+        for (int32_t cb = 0; cb < K; cb += kWave) {
+            const int32_t cc = cb + lane;
+            const int32_t v = cc < K ? cnt_s[cc] : 0;
+            const int32_t incl = (int32_t)wave_incl_scan((int64_t)v);
+            if (cc < K) {
+                ms[cc] = carry + incl - v;
+                cur[cc] = carry + incl - v;
+            }
+            carry += __builtin_amdgcn_readlane(incl, kWave - 1);
         }
-        carry += (int64_t)readlane64((uint64_t)incl, kWave - 1);
+        if (lane == 0) ms[K] = N;
     }
-    if (lane == 0) ms[K] = N;
     __syncthreads();
-    for (int32_t i = lane; i < N; i += kWave) {
+    for (int32_t i = tid; i < N; i += kFitThreads) {
         const int32_t c = cellk[i];
         ml[atomicAdd(&cur[c], 1)] = i;
     }
@@ -1224,10 +1341,8 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
         RP_HIP(hipFuncSetAttribute((const void *)k_pack_fit, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fit_lds));
         const void *pair_fn = w_hbm ? (const void *)k_pack_pair<true> : (const void *)k_pack_pair<false>;
         RP_HIP(hipFuncSetAttribute(pair_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pair_lds));
-        if (K <= 8 * kWave) {
-            hipLaunchKernelGGL(k_pack_fit_reg<8>, dim3(nb), dim3(64), (size_t)8 * K, stream, ta, pf);
-        } else if (K <= 32 * kWave) {
-            hipLaunchKernelGGL(k_pack_fit_reg<32>, dim3(nb), dim3(64), (size_t)8 * K, stream, ta, pf);
+        if (K <= kFitSortedCells) {
+            hipLaunchKernelGGL(k_pack_fit_sorted, dim3(nb), dim3(kFitThreads), fit_sorted_lds(K), stream, ta, pf);
         } else {
             hipLaunchKernelGGL(k_pack_fit, dim3(nb), dim3(64), fit_lds, stream, ta, pf);
         }

@@ -70,3 +70,66 @@ def test_score_edges(P, L, G, D, R, N, big):
         assert out["J"][m].cpu().tolist() == J.tolist()
         if st == 0:  # sums of at most L R G doubles in another order
             np.testing.assert_allclose(out["diag"][m].cpu().numpy(), dg, rtol=1e-11, atol=0)
+
+
+def _pack_case(N, D, G, cap, lengths, L=2, P=4, seed=5):
+    rng = np.random.default_rng([13, N, D, seed])
+    q = rng.integers(0, 1000, size=(N, L, P)).astype(np.int32)
+    kw = dict(n_samples=N, n_layers=L, n_experts=P, top_k=1, n_ranks=P, n_dp=D, n_edp=G,
+              dp_to_edp=(np.arange(D) * G // D).astype(np.int32), capacity=cap, alpha_fp=np.array([4096]),
+              beta_fp=np.array([1]), frac_bits=2, min_rows=1)
+    return np.asarray(lengths, dtype=np.int32), q, kw
+
+
+def _check_pack(t, q, kw, width, trials=5, pop=9, seed=77):
+    import oracle as O
+    import paper_2608_12146_amd as rp
+    want = O.pack_rows(O.Problem.from_dict(kw), t, q, seed, trials, width, pop)
+    try:
+        got = rp.pack_rows(rp.Problem.from_dict(kw), t, q, seed, trials, width, pop)
+    except rp.RoutepackError as e:
+        assert e.code == want["rc"]
+        return None
+    assert want["rc"] == 0 and got["r_star"] == want["r_star"]
+    assert (got["r_lb"], got["n_distinct"], got["n_trials_ok"]) == (want["r_lb"], want["n_distinct"],
+                                                                   want["n_trials_ok"])
+    assert np.array_equal(got["population"].cpu().numpy(), want["population"])
+    assert np.array_equal(got["scores"].cpu().numpy(), want["scores"])
+    return want
+
+
+@gpu
+@pytest.mark.parametrize("width", [1, 2, 5, 17, 62])
+@pytest.mark.parametrize("K,N", [(1, 1), (1, 9), (31, 63), (32, 65), (33, 200), (63, 64), (64, 700), (65, 1000),
+                                 (512, 1500), (2048, 2500), (2050, 2300)])
+def test_pack_cell_counts(K, N, width):
+    """Best-fit seeds with one row of keys, full and part-filled last rows,
+    the last sorted cell count and the first past it, at narrow and wide
+    choices; equal lengths occur throughout (ties by members, then cell)."""
+    _log(f"pack K={K} N={N} width={width}")
+    rng = np.random.default_rng([14, K, N])
+    t = rng.integers(1, 40, size=N)
+    D = 2 if K % 2 == 0 else 1
+    kw_cap = max(int(-(-t.sum() // K) * 1.08) + 2, int(t.max()))
+    t, q, kw = _pack_case(N, D, 1, kw_cap, t, L=1)
+    kw["min_rows"] = K // D
+    _check_pack(t, q, kw, width)
+
+
+@gpu
+@pytest.mark.parametrize("seed", range(12))
+def test_pack_tight_cells(seed):
+    """Cells filled to the cap: trials that find no cell, row counts that
+    FFD raises, rows of keys that fill up and are spread again."""
+    _log(f"pack tight {seed}")
+    rng = np.random.default_rng([15, seed])
+    n_cells, per = int(rng.integers(20, 200)), int(rng.integers(2, 12))
+    cap = 600
+    cuts = [np.diff(np.concatenate([[0], np.sort(rng.choice(np.arange(1, cap), per - 1, replace=False)), [cap]]))
+            for _ in range(n_cells)]
+    t = rng.permutation(np.concatenate(cuts))
+    if seed % 3 == 0:  # many short samples: one row of keys takes most placements
+        t = np.concatenate([t, np.ones(500, dtype=t.dtype)])
+    D = int(rng.choice([1, 2, 4]))
+    t, q, kw = _pack_case(len(t), D, 1, cap, t)
+    _check_pack(t, q, kw, int(rng.choice([1, 3, 4, 8])))
