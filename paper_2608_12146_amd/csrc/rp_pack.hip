@@ -23,6 +23,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <type_traits>
 #include <vector>
 
 #include "rp_device.h"
@@ -417,7 +418,9 @@ __global__ void __launch_bounds__(64) k_pack_trials(TrialArgs a) {
 //                  k_pack_fit_sorted keeps the keys sorted instead.
 //  k_pack_cellsum  one workgroup per (candidate, cell): Q_k = sum of the
 //                  member rows and peak_k = sum_l max_p Q_k.
-//  k_pack_pair     one workgroup per candidate: EDPAwarePair with the W table
+//  k_pair_*        EDPAwarePair in batches of cells (see there);
+//  k_pack_pair     the shapes those do not take, one workgroup per candidate:
+//                  EDPAwarePair with the W table
 //                  in LDS when it fits (else in the trial's slice of HBM),
 //                  threads over 4 consecutive entries of W + Q_k and a DPP
 //                  maximum over each layer's ranks, and the next cell's Q
@@ -886,8 +889,9 @@ __global__ void __launch_bounds__(kFitThreads) k_pack_fit_sorted(TrialArgs a, Pa
     }
 }
 
-// Q_k and peak_k of cell k = blockIdx.x of candidate b = blockIdx.y.
-__global__ void __launch_bounds__(128) k_pack_cellsum(TrialArgs a, PackFast pf) {
+// Q_k and peak_k of cell k = blockIdx.x of candidate b = blockIdx.y; chunked:
+// Q_k as [P/4][L][4] instead of [L][P].
+__global__ void __launch_bounds__(128) k_pack_cellsum(TrialArgs a, PackFast pf, bool chunked) {
     extern __shared__ int32_t sq[];
     __shared__ int64_t spart[4];
     const int b = blockIdx.y, k = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
@@ -900,7 +904,8 @@ __global__ void __launch_bounds__(128) k_pack_cellsum(TrialArgs a, PackFast pf) 
     for (int32_t e = tid; e < LP; e += nt) {
         int32_t acc = 0;
         for (int32_t x = lo; x < hi; ++x) acc += a.q[(int64_t)ml[x] * LP + e];
-        Qk[e] = acc;
+        const int32_t l = e / P, r = e - l * P;
+        Qk[chunked ? ((r >> 2) * L + l) * 4 + (r & 3) : e] = acc;
         sq[e] = acc;
     }
     __syncthreads();
@@ -918,6 +923,395 @@ __global__ void __launch_bounds__(128) k_pack_cellsum(TrialArgs a, PackFast pf) 
         for (int w = 0; w < nt / kWave; ++w) tot += spart[w];
         a.peak[(int64_t)b * K + k] = tot;
     }
+}
+
+// ---------------------------------------------------------------------------
+// EDPAwarePair in batches of kPairBatch cells, for up to 64 layers and 64
+// ranks (a multiple of 4).  A step's choice needs sum_l max_p (W_h + Q_k) and
+// the largest entry of every open row-shard h, but it changes one W_h only:
+//  k_pair_start    the cell order, zero W;
+//  k_pair_table    those two numbers for every row-shard and each cell of
+//                  the next batch on W as it stands, on the whole chip;
+//  k_pair_resolve  the batch's choices in order, one workgroup per trial:
+//                  after each one the chosen row-shard's numbers are formed
+//                  again for the batch's remaining cells, one wave per cell
+//                  with its Q row in registers.
+// The chain of K choices bounds it (one workgroup streaming every W row in
+// every step took 3.4 ms for 400 cells of 24 x 16 on 50 row-shards and 79 ms
+// for 1984 of 64 x 64 on 62; now 0.75 ms and 8.4 ms).  A lane holds a
+// layer (two row-shards per wave up to 32 layers), so W and Q rows are
+// chunk-major, [P/4][L][4], the maximum over ranks is in-lane, and only the
+// sum and the maximum over layers cross lanes.
+
+constexpr int kPairBatch = 16;       // cells per batch: a wave of k_pair_resolve each
+constexpr int kPairMaxShards = 512;  // row-shards (k_pair_resolve's tables in LDS)
+
+struct PairArgs {
+    int64_t *after;   // [M-1][kPairBatch][RG] sum_l max_p (W_h + Q_k)
+    int32_t *pk;      // [M-1][kPairBatch][RG] the largest entry
+};
+
+// Sum and maximum over each half of the wave, in lanes 31 and 63; with FULL
+// over the wave, in lane 63.  The sum is of signed 32-bit values (split in 16
+// bits so that 64 of them fit), the maximum is of values >= 0.
+template <bool FULL>
+__device__ inline void layer_reduce(int32_t v, int64_t &sum, int32_t &mx) {
+    int32_t lo = v & 0xFFFF, hi = v >> 16;
+    mx = v > 0 ? v : 0;
+    auto step = [&](auto ctrl, auto rows) {
+        lo += dpp32<decltype(ctrl)::value, decltype(rows)::value>(lo, 0);
+        hi += dpp32<decltype(ctrl)::value, decltype(rows)::value>(hi, 0);
+        const int32_t o = dpp32<decltype(ctrl)::value, decltype(rows)::value>(mx, 0);
+        mx = o > mx ? o : mx;
+    };
+    using All = std::integral_constant<int, 0xF>;
+    step(std::integral_constant<int, kDppRowShr1>{}, All{});
+    step(std::integral_constant<int, kDppRowShr1 + 1>{}, All{});
+    step(std::integral_constant<int, kDppRowShr1 + 3>{}, All{});
+    step(std::integral_constant<int, kDppRowShr1 + 7>{}, All{});
+    step(std::integral_constant<int, kDppRowBcast15>{}, std::integral_constant<int, 0xA>{});
+    if (FULL) step(std::integral_constant<int, kDppRowBcast31>{}, std::integral_constant<int, 0xC>{});
+    sum = (int64_t)hi * 65536 + lo;
+}
+
+__device__ inline int32_t max4_sum(int32_t m, const int4 &w, const int4 &q) {
+    m = max(m, max(w.x + q.x, w.y + q.y));
+    return max(m, max(w.z + q.z, w.w + q.w));
+}
+
+// The cell order of each trial (decreasing peak, then index), W, base and
+// filled at zero.
+__global__ void __launch_bounds__(1024) k_pair_start(TrialArgs a) {
+    extern __shared__ __align__(16) int64_t spk[];  // [K]
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const int32_t K = a.K, RG = a.RG;
+    if (!a.ok[b]) return;  // uniform
+    for (int32_t k = tid; k < K; k += 1024) spk[k] = a.peak[(int64_t)b * K + k];
+    for (int32_t h = tid; h < RG; h += 1024) {
+        a.base[(int64_t)b * RG + h] = 0;
+        a.filled[(int64_t)b * RG + h] = 0;
+    }
+    int4 *W = reinterpret_cast<int4 *>(a.Wt + (int64_t)b * RG * a.LP);
+    for (int64_t x = tid; x < (int64_t)RG * a.LP / 4; x += 1024) W[x] = make_int4(0, 0, 0, 0);
+    __syncthreads();
+    for (int32_t k = tid; k < K; k += 1024) {
+        const int64_t v = spk[k];
+        int32_t rank = 0;
+#pragma unroll 8
+        for (int32_t f = 0; f < K; ++f) rank += (spk[f] > v) || (spk[f] == v && f < k);
+        a.order[(int64_t)b * K + rank] = k;
+    }
+}
+
+// A wave: two row-shards (four up to 32 layers, two in each half) and eight
+// cells of the batch.  A chunk of each Q row is reused for the row-shards and
+// a chunk of each W row for the cells.
+template <bool HALF>
+__global__ void __launch_bounds__(256) k_pair_table(TrialArgs a, PairArgs pa, int32_t pos0) {
+    constexpr int CM = kPairBatch / 2, HS = 2;
+    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const int b = blockIdx.z;
+    if (!a.ok[b]) return;
+    const int32_t RG = a.RG, L = a.L, LP = a.LP, K = a.K, p4 = a.P >> 2;
+    const int32_t c0 = (int32_t)blockIdx.y * CM;  // first cell of the batch
+    const int32_t nc = K - pos0 - c0;             // cells from there on
+    const int32_t s0 = ((int32_t)blockIdx.x * 4 + wv) * HS;  // first row-shard slot of the wave
+    if (nc <= 0 || (HALF ? 2 * s0 : s0) >= RG) return;
+    const int half = HALF ? lane >> 5 : 0, hl = HALF ? lane & 31 : lane;
+    const bool act = hl < L;
+    const int32_t ll = act ? hl : L - 1;
+    const int4 *wp[HS], *qp[CM];
+#pragma unroll
+    for (int u = 0; u < HS; ++u) {
+        const int32_t h = HALF ? 2 * (s0 + u) + half : s0 + u;
+        wp[u] = reinterpret_cast<const int4 *>(a.Wt + ((int64_t)b * RG + (h < RG ? h : RG - 1)) * LP) + ll;
+    }
+#pragma unroll
+    for (int c = 0; c < CM; ++c) {
+        const int32_t k = a.order[(int64_t)b * K + pos0 + c0 + (c < nc ? c : 0)];
+        qp[c] = reinterpret_cast<const int4 *>(a.Qc + ((int64_t)b * K + k) * LP) + ll;
+    }
+    int32_t mx[HS][CM];
+#pragma unroll
+    for (int u = 0; u < HS; ++u)
+#pragma unroll
+        for (int c = 0; c < CM; ++c) mx[u][c] = INT32_MIN;
+    for (int32_t x = 0; x < p4; ++x) {
+        int4 w[HS], q[CM];
+#pragma unroll
+        for (int u = 0; u < HS; ++u) w[u] = wp[u][x * L];
+#pragma unroll
+        for (int c = 0; c < CM; ++c) q[c] = qp[c][x * L];
+#pragma unroll
+        for (int u = 0; u < HS; ++u)
+#pragma unroll
+            for (int c = 0; c < CM; ++c) mx[u][c] = max4_sum(mx[u][c], w[u], q[c]);
+    }
+#pragma unroll
+    for (int u = 0; u < HS; ++u) {
+        const int32_t h = HALF ? 2 * (s0 + u) + half : s0 + u;
+#pragma unroll
+        for (int c = 0; c < CM; ++c) {
+            int64_t sum;
+            int32_t m;
+            layer_reduce<!HALF>(act ? mx[u][c] : 0, sum, m);
+            if (lane == 63 || (HALF && lane == 31)) {
+                if (h < RG && c < nc) {
+                    const int64_t at = ((int64_t)b * kPairBatch + c0 + c) * RG + h;
+                    pa.after[at] = sum;
+                    pa.pk[at] = m;
+                }
+            }
+        }
+    }
+}
+
+__host__ __device__ inline size_t pair_resolve_lds(int64_t RG, int64_t LP, bool wl) {
+    return (size_t)(kPairBatch * RG * 12 + RG * 16 + (wl ? RG + 2 : 2) * LP * 4 + 4 + kPairBatch * 8);
+}
+
+// A workgroup barrier for LDS only: __syncthreads also waits for the global
+// stores before it, a trip to memory and back that nothing here needs.
+__device__ inline void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The rank drawn among wp candidates with weights 2^(wp - 1 - rho): the
+// prefix up to rho is 2^wp - 2^(wp - 1 - rho), and rho is the first whose
+// prefix exceeds floor(word (2^wp - 1) / 2^64).
+__device__ inline int32_t pair_rho(uint64_t word, int32_t wp) {
+    if (wp <= 1) return 0;
+    const uint64_t all = ((uint64_t)1 << wp) - 1;
+    return wp - 64 + __clzll((long long)(all - bounded(word, all)));
+}
+
+// Unsigned minimum over the wave; uniform.
+__device__ inline uint32_t wave_min_u32(uint32_t v) {
+    auto step = [&](uint32_t o) { v = o < v ? o : v; };
+    step((uint32_t)dpp32<kDppXor1>((int32_t)v, (int32_t)v));
+    step((uint32_t)dpp32<kDppXor2>((int32_t)v, (int32_t)v));
+    step((uint32_t)dpp32<kDppHalfMirror>((int32_t)v, (int32_t)v));
+    step((uint32_t)dpp32<kDppMirror>((int32_t)v, (int32_t)v));
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int32_t)v, 0), b = (uint32_t)__builtin_amdgcn_readlane((int32_t)v, 16);
+    const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int32_t)v, 32), d = (uint32_t)__builtin_amdgcn_readlane((int32_t)v, 48);
+    const uint32_t x = a < b ? a : b, y = c < d ? c : d;
+    return x < y ? x : y;
+}
+
+// EDPAwarePair's choice (one wave): the rho-th open row-shard in the order
+// (increase, peak, index), drawn from the leading min(w, open).
+__device__ inline int32_t pair_choice(const int64_t *after, const int32_t *pk, const int64_t *base,
+                                      const int32_t *filled, const int32_t *hcnt, int32_t RG, int32_t w,
+                                      uint64_t word, int32_t rho_w) {
+    const int lane = lane_id();
+    if (RG <= kWave) {
+        const int32_t at = lane < RG ? lane : 0;
+        const int64_t inc = after[at] - base[at];
+        const int32_t peak = pk[at], fl = filled[at], hc = hcnt[at];
+        uint64_t open = __ballot(lane < RG && fl < hc);
+        if ((open & __ballot((uint64_t)inc >= 0xFFFFFFFFull)) == 0) {  // increases below 2^32 - 1, as all but always
+            const int32_t cnt = __popcll(open);
+            const int32_t rho = cnt >= w ? rho_w : pair_rho(word, cnt);
+            for (int32_t pass = 0;; ++pass) {
+                const uint32_t v = lane_in(open) ? (uint32_t)inc : 0xFFFFFFFFu;
+                uint64_t eq = __ballot(v == wave_min_u32(v));
+                if (__popcll(eq) > 1) {  // (lanes are in index order)
+                    const uint32_t p = lane_in(eq) ? (uint32_t)peak : 0xFFFFFFFFu;
+                    eq = __ballot(p == wave_min_u32(p));
+                }
+                const int src = first_lane(eq);
+                if (pass == rho) return src;
+                open &= ~((uint64_t)1 << src);
+            }
+        }
+    }
+    int32_t cnt = 0;
+    for (int32_t hb = 0; hb < RG; hb += kWave)
+        cnt += __popcll(__ballot(hb + lane < RG && filled[hb + lane] < hcnt[hb + lane]));
+    const int32_t rho = cnt >= w ? rho_w : pair_rho(word, cnt);
+    uint32_t taken = 0;  // bit x: this lane's row-shard lane + 64 x was an earlier choice
+    int32_t h = 0;
+    for (int32_t pass = 0; pass <= rho; ++pass) {
+        int64_t k0 = LLONG_MAX;
+        int32_t k1 = INT32_MAX, k2 = INT32_MAX;
+        for (int32_t hb = 0, x = 0; hb < RG; hb += kWave, ++x) {
+            const int32_t hh = hb + lane;
+            if (hh < RG && filled[hh] < hcnt[hh] && !((taken >> x) & 1)) {
+                const int64_t v0 = after[hh] - base[hh];
+                const int32_t v1 = pk[hh];
+                if (k2 == INT32_MAX || v0 < k0 || (v0 == k0 && v1 < k1)) {  // (ascending index)
+                    k0 = v0;
+                    k1 = v1;
+                    k2 = hh;
+                }
+            }
+        }
+        const int64_t m0 = wave_min(k0);
+        uint64_t eq = __ballot(k2 != INT32_MAX && k0 == m0);
+        if (__popcll(eq) > 1) {
+            const uint32_t p = lane_in(eq) ? (uint32_t)k1 : 0xFFFFFFFFu;
+            eq = __ballot(p == wave_min_u32(p));
+            if (__popcll(eq) > 1) {
+                const uint32_t i = lane_in(eq) ? (uint32_t)k2 : 0xFFFFFFFFu;
+                eq = __ballot(i == wave_min_u32(i));
+            }
+        }
+        const int src = first_lane(eq);
+        h = __builtin_amdgcn_readlane(k2, src);
+        if (lane == src) taken |= 1u << (h >> 6);
+    }
+    return h;
+}
+
+// The choices of cells pos0 .. pos0 + kPairBatch - 1.  PV: the ranks rounded
+// up to a compiled size.  WL: the trial's W is loaded into LDS first (when it
+// fits): a launch finds it in the last level cache only, 1.5 to 2 us away, so
+// a step that reads the chosen row from there takes that long.
+template <int PV, bool WL>
+__global__ void __launch_bounds__(kPairBatch *kWave) k_pair_resolve(TrialArgs a, PairArgs pa, int32_t pos0) {
+    extern __shared__ __align__(16) char sres[];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+    if (!a.ok[b]) return;  // uniform
+    const int32_t RG = a.RG, L = a.L, LP = a.LP, K = a.K, D = a.D, G = a.G, p4 = a.P >> 2;
+    const int32_t m = K - pos0 < kPairBatch ? K - pos0 : kPairBatch;
+    const int32_t n4 = LP >> 2;
+    int4 *qcur = reinterpret_cast<int4 *>(sres);                    // [n4] Q of the current cell (WL: [2][n4], by parity)
+    int4 *wl = qcur + (WL ? 2 : 1) * n4;                            // [n4] the chosen row's new W (WL: [RG][n4], W)
+    int64_t *after = reinterpret_cast<int64_t *>(wl + (WL ? RG : 1) * n4);  // [kPairBatch][RG]
+    int64_t *base = after + kPairBatch * RG;                        // [RG]
+    int32_t *pk = reinterpret_cast<int32_t *>(base + RG);           // [kPairBatch][RG]
+    int32_t *filled = pk + kPairBatch * RG, *hcnt = filled + RG;    // [RG], [RG]
+    int32_t *s_h = hcnt + RG;                                       // [1]
+    int32_t *pick_h = s_h + 1, *pick_f = pick_h + kPairBatch;       // [kPairBatch] choices, their fill before
+    for (int32_t x = tid; x < m * RG; x += kPairBatch * kWave) {
+        after[x] = pa.after[(int64_t)b * kPairBatch * RG + x];
+        pk[x] = pa.pk[(int64_t)b * kPairBatch * RG + x];
+    }
+    for (int32_t h = tid; h < RG; h += kPairBatch * kWave) {
+        base[h] = a.base[(int64_t)b * RG + h];
+        filled[h] = a.filled[(int64_t)b * RG + h];
+        hcnt[h] = a.count[h % G];
+    }
+    // wave j: Q of the batch's j-th cell, lane = layer
+    const bool act = lane < L;
+    const int32_t ll = act ? lane : L - 1;
+    int4 q[PV / 4];
+    int32_t kl = 0;  // lane j: the batch's j-th cell
+    if (lane < m) kl = a.order[(int64_t)b * K + pos0 + lane];
+    const int32_t w = b == 0 ? 1 : a.w;
+    uint64_t word = 0;  // lane j: the j-th cell's draw
+    if (b > 0 && lane < m) word = a.words[(int64_t)(b - 1) * (2 * (int64_t)a.N + K) + 2 * (int64_t)a.N + pos0 + lane];
+    const int32_t rho_w = pair_rho(word, w);  // its rank when w or more row-shards are open
+    {
+        const int32_t k = __builtin_amdgcn_readlane(kl, wv < m ? wv : 0);
+        const int4 *qp = reinterpret_cast<const int4 *>(a.Qc + ((int64_t)b * K + k) * LP) + ll;
+#pragma unroll
+        for (int x = 0; x < PV / 4; ++x) q[x] = x < p4 ? qp[x * L] : make_int4(0, 0, 0, 0);
+    }
+    int4 *W = reinterpret_cast<int4 *>(a.Wt + (int64_t)b * RG * LP);
+    if (WL)
+        for (int32_t x = tid; x < RG * n4; x += kPairBatch * kWave) wl[x] = W[x];
+    auto share_q = [&](int4 *to) {
+#pragma unroll
+        for (int x = 0; x < PV / 4; ++x)
+            if (x < p4 && act) to[x * L + ll] = q[x];
+    };
+    auto choose = [&](int32_t i) {  // (wave 0)
+        const int32_t h = pair_choice(after + i * RG, pk + i * RG, base, filled, hcnt, RG, w, readlane64(word, i),
+                                      __builtin_amdgcn_readlane(rho_w, i));
+        if (lane == 0) {
+            *s_h = h;
+            base[h] = after[i * RG + h];
+            pick_h[i] = h;
+            pick_f[i] = filled[h];
+            filled[h] += 1;
+        }
+    };
+    // row h of W takes the cell of qv; waves from w0 on (the same threads for
+    // a row in every step, so its stores to global memory stay in order
+    // without a barrier that waits for them)
+    auto apply = [&](int32_t h, const int4 *qv, int4 *to, int32_t w0) {
+        for (int32_t x = tid - w0 * kWave; x < n4; x += (kPairBatch - w0) * kWave) {
+            const int4 v = WL ? wl[h * n4 + x] : W[(int64_t)h * n4 + x], c = qv[x];
+            const int4 s = make_int4(v.x + c.x, v.y + c.y, v.z + c.z, v.w + c.w);
+            to[x] = s;
+            W[(int64_t)h * n4 + x] = s;
+        }
+    };
+    auto refresh = [&](int32_t h, int32_t mx) {
+        int64_t sum;
+        int32_t most;
+        layer_reduce<true>(act ? mx : 0, sum, most);
+        if (lane == 63) {
+            after[wv * RG + h] = sum;
+            pk[wv * RG + h] = most;
+        }
+    };
+    if (WL) {
+        // wave 0 chooses while the others add the previous cell to its row;
+        // then the later cells' waves form their numbers from the row and the
+        // current cell's Q
+        int32_t hp = 0;
+        for (int32_t i = 0; i < m; ++i) {
+            lds_barrier();
+            if (wv == i) share_q(qcur + (i & 1) * n4);
+            if (wv == 0) choose(i);
+            else if (i > 0) apply(hp, qcur + ((i - 1) & 1) * n4, wl + hp * n4, 1);
+            lds_barrier();
+            const int32_t h = hp = *s_h;
+            if (wv > i && wv < m) {
+                const int4 *row = wl + h * n4 + ll, *qv = qcur + (i & 1) * n4 + ll;
+                int32_t mx = INT32_MIN;
+#pragma unroll
+                for (int x = 0; x < PV / 4; ++x)
+                    if (x < p4) {
+                        const int4 v = row[x * L], c = qv[x * L];
+                        mx = max4_sum(mx, make_int4(v.x + c.x, v.y + c.y, v.z + c.z, v.w + c.w), q[x]);
+                    }
+                refresh(h, mx);
+            }
+        }
+        lds_barrier();
+        if (wv > 0) apply(hp, qcur + ((m - 1) & 1) * n4, wl + hp * n4, 1);
+    } else {
+        if (wv == 0) share_q(qcur);
+        for (int32_t i = 0; i < m; ++i) {
+            lds_barrier();
+            if (wv == 0) choose(i);
+            lds_barrier();
+            const int32_t h = *s_h;
+            apply(h, qcur, wl, 0);
+            lds_barrier();
+            if (wv == i + 1) share_q(qcur);
+            if (wv > i && wv < m) {
+                int32_t mx = INT32_MIN;
+#pragma unroll
+                for (int x = 0; x < PV / 4; ++x)
+                    if (x < p4) mx = max4_sum(mx, wl[x * L + ll], q[x]);
+                refresh(h, mx);
+            }
+        }
+    }
+    lds_barrier();
+    if (tid < m) {
+        const int32_t h = pick_h[tid], r = h / G, g = h - r * G;
+        a.cell_to[(int64_t)b * K + kl] = r * D + a.slots[g * D + pick_f[tid]];
+    }
+    for (int32_t h = tid; h < RG; h += kPairBatch * kWave) {
+        a.base[(int64_t)b * RG + h] = base[h];
+        a.filled[(int64_t)b * RG + h] = filled[h];
+    }
+}
+
+// The layouts of the paired trials (workgroups of a trial in blockIdx.x).
+__global__ void __launch_bounds__(256) k_pair_out(TrialArgs a) {
+    const int b = blockIdx.y;
+    if (!a.ok[b]) return;
+    for (int32_t i = blockIdx.x * 256 + threadIdx.x; i < a.N; i += gridDim.x * 256)
+        a.out[(int64_t)b * a.N + i] = a.cell_to[(int64_t)b * a.K + a.cellk[(int64_t)b * a.N + i]];
 }
 
 // EDPAwarePair of candidate b (block per candidate).
@@ -1330,8 +1724,14 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
     const char *pw_force = getenv("ROUTEPACK_PACK_W");
     const bool w_hbm = (pw_force && strcmp(pw_force, "hbm") == 0) || pair_rest + 4 * (int64_t)RG * LP > 150 * 1024;
     const int64_t pair_lds = pair_rest + (w_hbm ? 0 : 4 * (int64_t)RG * LP);
+    const int32_t P = prob->n_ranks, L = prob->n_layers;
+    // Batched pairing (k_pair_*) for layers that fit a wave and ranks that a
+    // lane holds; k_pack_pair beyond 64 layers or ranks or 512 row-shards (and
+    // on request), for power-of-two ranks whose tables fit LDS.
+    const bool batched = !pw_force && L <= kWave && P % 4 == 0 && P <= 64 && RG <= kPairMaxShards;
+    const bool one_wg = P >= 4 && P <= 256 && (P & (P - 1)) == 0 && pair_lds <= 150 * 1024;
     const bool fast = !(pk_force && strcmp(pk_force, "single") == 0) && C < ((int64_t)1 << 31) && N < 65536 &&
-                      prob->n_ranks >= 4 && LP > 0 && pair_lds <= 150 * 1024;
+                      LP > 0 && (batched || one_wg);
     if (fast) {
         PackFast pf;
         pf.mstart = scr.get<int32_t>((size_t)nb * (K + 1));
@@ -1339,16 +1739,44 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
         if (scr.failed()) return ROUTEPACK_E_DEVICE;
         const size_t fit_lds = (size_t)16 * K;
         RP_HIP(hipFuncSetAttribute((const void *)k_pack_fit, hipFuncAttributeMaxDynamicSharedMemorySize, (int)fit_lds));
-        const void *pair_fn = w_hbm ? (const void *)k_pack_pair<true> : (const void *)k_pack_pair<false>;
-        RP_HIP(hipFuncSetAttribute(pair_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pair_lds));
         if (K <= kFitSortedCells) {
             hipLaunchKernelGGL(k_pack_fit_sorted, dim3(nb), dim3(kFitThreads), fit_sorted_lds(K), stream, ta, pf);
         } else {
             hipLaunchKernelGGL(k_pack_fit, dim3(nb), dim3(64), fit_lds, stream, ta, pf);
         }
-        hipLaunchKernelGGL(k_pack_cellsum, dim3(K, nb), dim3(128), (size_t)4 * LP, stream, ta, pf);
-        if (w_hbm) hipLaunchKernelGGL(k_pack_pair<true>, dim3(nb), dim3(1024), (size_t)pair_lds, stream, ta, pf);
-        else hipLaunchKernelGGL(k_pack_pair<false>, dim3(nb), dim3(1024), (size_t)pair_lds, stream, ta, pf);
+        hipLaunchKernelGGL(k_pack_cellsum, dim3(K, nb), dim3(128), (size_t)4 * LP, stream, ta, pf, batched);
+        if (batched) {
+            PairArgs pa;
+            pa.after = scr.get<int64_t>((size_t)nb * kPairBatch * RG);
+            pa.pk = scr.get<int32_t>((size_t)nb * kPairBatch * RG);
+            if (scr.failed()) return ROUTEPACK_E_DEVICE;
+            const bool wl = pair_resolve_lds(RG, LP, true) <= 150 * 1024;
+            const size_t res_lds = pair_resolve_lds(RG, LP, wl);
+            auto pick = [&](auto with, auto without) { return wl ? with : without; };
+            auto resolve = P <= 8    ? pick(k_pair_resolve<8, true>, k_pair_resolve<8, false>)
+                           : P <= 16 ? pick(k_pair_resolve<16, true>, k_pair_resolve<16, false>)
+                           : P <= 32 ? pick(k_pair_resolve<32, true>, k_pair_resolve<32, false>)
+                                     : pick(k_pair_resolve<64, true>, k_pair_resolve<64, false>);
+            if (res_lds > 64 * 1024)
+                RP_HIP(hipFuncSetAttribute((const void *)resolve, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)res_lds));
+            const bool half = L <= 32;  // two row-shards per wave
+            const int32_t slots = half ? (RG + 1) / 2 : RG;
+            hipLaunchKernelGGL(k_pair_start, dim3(nb), dim3(1024), (size_t)8 * K, stream, ta);
+            for (int32_t pos = 0; pos < K; pos += kPairBatch) {
+                const dim3 grid((unsigned)((slots + 7) / 8), 2, (unsigned)nb);
+                if (half) hipLaunchKernelGGL(k_pair_table<true>, grid, dim3(256), 0, stream, ta, pa, pos);
+                else hipLaunchKernelGGL(k_pair_table<false>, grid, dim3(256), 0, stream, ta, pa, pos);
+                hipLaunchKernelGGL(resolve, dim3(nb), dim3(kPairBatch * kWave), res_lds, stream, ta, pa, pos);
+            }
+            hipLaunchKernelGGL(k_pair_out, dim3((unsigned)(N < 65536 / 4 ? 8 : 32), (unsigned)nb), dim3(256), 0, stream,
+                               ta);
+        } else {
+            const void *pair_fn = w_hbm ? (const void *)k_pack_pair<true> : (const void *)k_pack_pair<false>;
+            RP_HIP(hipFuncSetAttribute(pair_fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pair_lds));
+            if (w_hbm) hipLaunchKernelGGL(k_pack_pair<true>, dim3(nb), dim3(1024), (size_t)pair_lds, stream, ta, pf);
+            else hipLaunchKernelGGL(k_pack_pair<false>, dim3(nb), dim3(1024), (size_t)pair_lds, stream, ta, pf);
+        }
     } else {
         hipLaunchKernelGGL(k_pack_trials, dim3(nb), dim3(64), 0, stream, ta);
     }

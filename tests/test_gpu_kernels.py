@@ -133,3 +133,28 @@ def test_pack_tight_cells(seed):
     D = int(rng.choice([1, 2, 4]))
     t, q, kw = _pack_case(len(t), D, 1, cap, t)
     _check_pack(t, q, kw, int(rng.choice([1, 3, 4, 8])))
+
+
+@gpu
+@pytest.mark.parametrize("L,P,D,G,R", [(1, 4, 1, 1, 15), (2, 4, 4, 2, 4), (31, 8, 3, 1, 16), (32, 16, 5, 3, 7),
+                                       (33, 16, 4, 1, 17), (64, 64, 2, 1, 9), (5, 12, 4, 2, 40), (3, 48, 8, 8, 9),
+                                       (65, 4, 4, 1, 9), (24, 16, 2, 2, 140), (7, 6, 4, 2, 8), (2, 128, 2, 1, 6),
+                                       (2, 4, 8, 8, 70)])
+@pytest.mark.parametrize("width", [1, 4])
+@pytest.mark.parametrize("ties", [False, True])
+def test_pack_pairing_shapes(L, P, D, G, R, width, ties):
+    """EDPAwarePair with half and whole waves of layers, batches cut short,
+    W in LDS and in memory, one row-shard per lane and several, shards of
+    unequal size, and the shapes beyond the batched kernels (65 layers, 560
+    row-shards, 6 or 128 ranks); ties: few distinct rows, so equal increases
+    and equal peaks decide by index."""
+    _log(f"pairing L={L} P={P} D={D} G={G} R={R} width={width} ties={ties}")
+    N = R * D * 2 + 3
+    rng = np.random.default_rng([16, L, P, R])
+    t = np.full(N, 10) if ties else rng.integers(1, 40, size=N)
+    t, q, kw = _pack_case(N, D, G, int(-(-t.sum() // (R * D)) * 1.6) + 40, t, L=L, P=P)
+    if ties:
+        q[:] = q[rng.integers(0, 2, size=N)]
+    kw["min_rows"] = R
+    kw["dp_to_edp"] = np.sort(np.concatenate([np.arange(G), rng.integers(0, G, size=D - G)])).astype(np.int32)
+    _check_pack(t, q, kw, width, trials=4)
