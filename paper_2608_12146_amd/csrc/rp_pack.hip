@@ -70,73 +70,105 @@ __global__ void __launch_bounds__(256) k_rank_sort(const int32_t *__restrict__ t
     if (i < N) sigma[rank] = i;
 }
 
-// FixedRowFFD (one wave).  ok = 1 and cell_of filled on success.
+// Lane i's value becomes lane i + 1's (lane 63: 0), or lane i - 1's (lane 0: 0).
+__device__ inline int32_t lane_up(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xF, 0xF, true); }
+__device__ inline int32_t lane_down(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, true); }
+__device__ inline uint64_t lane_up64(uint64_t v) {
+    return (uint64_t)(uint32_t)lane_up((int32_t)(uint32_t)v) |
+           (uint64_t)(uint32_t)lane_up((int32_t)(uint32_t)(v >> 32)) << 32;
+}
+__device__ inline uint64_t lane_down64(uint64_t v) {
+    return (uint64_t)(uint32_t)lane_down((int32_t)(uint32_t)v) |
+           (uint64_t)(uint32_t)lane_down((int32_t)(uint32_t)(v >> 32)) << 32;
+}
+__device__ inline uint64_t low_lanes(int n) { return n >= kWave ? ~(uint64_t)0 : ((uint64_t)1 << n) - 1; }
+__device__ inline bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
+// Orders a wave's LDS accesses before its later ones by other lanes.
+__device__ inline void lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// FixedRowFFD (one wave).  ok = 1 and cell_of filled on success.  The N - K
+// steps are one serial chain, bound by its length in cycles.  Lane x keeps the
+// largest room of chunk x (cells 64x .. 64x + 63), and the rooms of the chunk
+// that took the last sample stay in the lanes: samples come longest first, so
+// the next one usually goes to the same chunk, and a step is then two compares
+// (an earlier chunk with room, a cell of this one) and a lane update.  Leaving
+// a chunk stores its rooms and forms its largest one.  4096 samples in 400
+// cells took 1.3 ms and 32768 in 1984 took 10.7 ms with the rooms in LDS and a
+// wave maximum per step; now 0.56 ms and 4.5 ms.  Room is int32 when the cap
+// fits.
+template <typename Room>
 __global__ void __launch_bounds__(64) k_ffd(const int32_t *__restrict__ t, const int32_t *__restrict__ sigma,
                                             int32_t N, int64_t C, int32_t K, int32_t *cell_of, int32_t *ok) {
-    __shared__ int64_t room[kMaxCells];
+    extern __shared__ __align__(8) char sffd[];
+    Room *room = reinterpret_cast<Room *>(sffd);  // [K]
     const int lane = lane_id();
     const int nchunk = (K + kWave - 1) / kWave;
     for (int c = lane; c < K; c += kWave) {
         const int32_t i = sigma[c];
-        room[c] = C - t[i];
+        room[c] = (Room)(C - t[i]);
         cell_of[i] = c;
     }
-    __syncthreads();
-    // lane x holds the largest room of chunk x (cells 64x .. 64x+63)
-    int64_t cmax = -1;
+    lds_order();
+    auto largest = [](Room v) -> Room {
+        if constexpr (sizeof(Room) == 4) return wave_max32(v);
+        else return wave_max(v);
+    };
+    auto chunk_rooms = [&](int x) -> Room { return x * kWave + lane < K ? room[x * kWave + lane] : -1; };
+    Room cmax = -1;
     for (int x = 0; x < nchunk; ++x) {
-        const int c = x * kWave + lane;
-        const int64_t v = wave_max(c < K ? room[c] : -1);
+        const Room v = largest(chunk_rooms(x));
         if (lane == x) cmax = v;
     }
+    int cur = 0;
+    Room row = chunk_rooms(0);
     // Items after the first K: this block's items and lengths (s0, t0), the
     // next block's (s1, t1) and the items of the one after (s2), loaded a
     // block of 64 ahead; item hb + x's cell stays in lane x until its block
-    // is stored, so no step waits on memory.  Only this wave touches the
-    // LDS rooms, so a wave-level fence orders a step's update before the
-    // next step's reads.
+    // is stored, so no step waits on memory.
     int32_t hb = K;
     const int32_t i0 = hb + lane, i1 = i0 + kWave, i2 = i1 + kWave;
     int32_t s0 = i0 < N ? sigma[i0] : 0, s1 = i1 < N ? sigma[i1] : 0, s2 = i2 < N ? sigma[i2] : 0;
     int32_t t0 = i0 < N ? t[s0] : 0, t1 = i1 < N ? t[s1] : 0;
-    int32_t p_item = -1, p_cell = 0;
     int32_t good = 1;
-    for (int32_t h = K; h < N; ++h) {
-        if (h - hb == kWave) {
-            if (p_item >= 0) cell_of[p_item] = p_cell;
-            p_item = -1;
-            hb += kWave;
-            s0 = s1;
-            t0 = t1;
-            s1 = s2;
-            const int32_t j1 = hb + kWave + lane, j2 = j1 + kWave;
-            t1 = j1 < N ? t[s1] : 0;
-            s2 = j2 < N ? sigma[j2] : 0;
+    while (hb < N && good) {
+        const int32_t cnt = N - hb < kWave ? N - hb : kWave;
+        int32_t p_cell = -1;
+        for (int32_t x = 0; x < cnt; ++x) {
+            const Room ti = (Room)__builtin_amdgcn_readlane(t0, x);
+            const uint64_t before = __ballot(cmax >= ti) & low_lanes(cur);
+            uint64_t m = before ? 0 : __ballot(row >= ti);
+            if (!m) {
+                if (cur * kWave + lane < K) room[cur * kWave + lane] = row;
+                const Room mx = largest(row);
+                cmax = lane == cur ? mx : cmax;
+                const uint64_t any = __ballot(cmax >= ti);  // (lengths are at least 1)
+                if (!any) {
+                    good = 0;
+                    break;
+                }
+                cur = first_lane(any);
+                lds_order();
+                row = chunk_rooms(cur);
+                m = __ballot(row >= ti);
+            }
+            const int at = first_lane(m);
+            row = lane_in((uint64_t)1 << at) ? (Room)(row - ti) : row;
+            p_cell = lane_in((uint64_t)1 << x) ? cur * kWave + at : p_cell;
         }
-        const int32_t i = __builtin_amdgcn_readlane(s0, h - hb);
-        const int64_t ti = __builtin_amdgcn_readlane(t0, h - hb);
-        const uint64_t m1 = __ballot(lane < nchunk && cmax >= ti);
-        if (!m1) {
-            good = 0;
-            break;
-        }
-        const int x = first_lane(m1);
-        const int c0 = x * kWave;
-        const int64_t r = (c0 + lane < K) ? room[c0 + lane] : -1;
-        const int c = c0 + first_lane(__ballot(r >= ti));
-        const int64_t nr = (c0 + lane == c) ? r - ti : r;
-        if (c0 + lane == c) room[c] = nr;
-        const int64_t nm = wave_max(nr);
-        if (lane == x) cmax = nm;
-        if (lane == h - hb) {
-            p_item = i;
-            p_cell = c;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (p_cell >= 0) cell_of[s0] = p_cell;
+        hb += kWave;
+        s0 = s1;
+        t0 = t1;
+        s1 = s2;
+        const int32_t j1 = hb + kWave + lane, j2 = j1 + kWave;
+        t1 = j1 < N ? t[s1] : 0;
+        s2 = j2 < N ? sigma[j2] : 0;
     }
-    if (p_item >= 0) cell_of[p_item] = p_cell;
     if (lane == 0) *ok = good;
 }
 
@@ -583,27 +615,6 @@ __global__ void __launch_bounds__(64) k_pack_fit(TrialArgs a, PackFast pf) {
         const int32_t c = cellk[i];
         ml[atomicAdd(&cur[c], 1)] = i;
     }
-}
-
-// Lane i's value becomes lane i + 1's (lane 63: 0), or lane i - 1's (lane 0: 0).
-__device__ inline int32_t lane_up(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xF, 0xF, true); }
-__device__ inline int32_t lane_down(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, true); }
-__device__ inline uint64_t lane_up64(uint64_t v) {
-    return (uint64_t)(uint32_t)lane_up((int32_t)(uint32_t)v) |
-           (uint64_t)(uint32_t)lane_up((int32_t)(uint32_t)(v >> 32)) << 32;
-}
-__device__ inline uint64_t lane_down64(uint64_t v) {
-    return (uint64_t)(uint32_t)lane_down((int32_t)(uint32_t)v) |
-           (uint64_t)(uint32_t)lane_down((int32_t)(uint32_t)(v >> 32)) << 32;
-}
-__device__ inline uint64_t low_lanes(int n) { return n >= kWave ? ~(uint64_t)0 : ((uint64_t)1 << n) - 1; }
-__device__ inline bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
-
-// Orders a wave's LDS accesses before its later ones by other lanes.
-__device__ inline void lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // WindowShuffle of one trial, one wave: lane x < wsize of (win, wint) holds
@@ -1662,8 +1673,12 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
     int64_t R = -1;
     for (int64_t r = r_lb; r <= r_max; ++r) {
         if (r * D > kMaxCells) return ROUTEPACK_E_UNSUPPORTED;
-        hipLaunchKernelGGL(k_ffd, dim3(1), dim3(64), 0, stream, lengths, sigma, N, C, (int32_t)(r * D),
-                           x_len, flag);
+        if (C < ((int64_t)1 << 31))
+            hipLaunchKernelGGL(k_ffd<int32_t>, dim3(1), dim3(64), (size_t)(4 * r * D), stream, lengths, sigma, N, C,
+                               (int32_t)(r * D), x_len, flag);
+        else
+            hipLaunchKernelGGL(k_ffd<int64_t>, dim3(1), dim3(64), (size_t)(8 * r * D), stream, lengths, sigma, N, C,
+                               (int32_t)(r * D), x_len, flag);
         int32_t ok = 0;
         RP_HIP(hipMemcpyAsync(&ok, flag, sizeof(ok), hipMemcpyDeviceToHost, stream));
         RP_HIP(hipStreamSynchronize(stream));

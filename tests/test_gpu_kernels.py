@@ -158,3 +158,21 @@ def test_pack_pairing_shapes(L, P, D, G, R, width, ties):
     kw["min_rows"] = R
     kw["dp_to_edp"] = np.sort(np.concatenate([np.arange(G), rng.integers(0, G, size=D - G)])).astype(np.int32)
     _check_pack(t, q, kw, width, trials=4)
+
+
+@gpu
+@pytest.mark.parametrize("K,N", [(1, 5), (64, 65), (65, 130), (128, 900), (200, 200), (4096, 4300)])
+@pytest.mark.parametrize("scale", [1, 1 << 22])
+def test_pack_first_fit(K, N, scale):
+    """FixedRowFFD over one chunk of cells, a part-filled last chunk and the
+    most chunks, with a cap below and above 2^31 (x_length and x_paired
+    only)."""
+    _log(f"first fit K={K} N={N} scale={scale}")
+    rng = np.random.default_rng([17, K, N])
+    t = np.sort(rng.integers(1, 400, size=N))[::-1]
+    t = rng.permutation(t)
+    cap = max(int(-(-t.sum() // K) * 1.02) + 1, int(t.max())) * scale
+    t, q, kw = _pack_case(N, 1, 1, cap, t * scale, L=1)
+    q[:] = rng.integers(0, 9, size=q.shape)
+    kw.update(min_rows=K, frac_bits=0, alpha_fp=np.array([1]), beta_fp=np.array([0]))
+    _check_pack(t, q, kw, 1, trials=2)
