@@ -107,8 +107,9 @@ inline int64_t run_blob_bytes(int32_t lds_member) { return ((int64_t)lds_member 
 
 // Chain kernels: rows of L x P int32 are kept chunk-major, [P/4][L][4], so a
 // 16-byte access of every lane of a half-wave (lane = layer) is contiguous.
-// Rewrites the W rows of every slab in place and writes qt (N rows).
-int chain_prepare(AnnealArgs &a, int32_t *qt, hipStream_t stream);
+// Writes qt (N rows) and, unless they were built so (w_chunked), rewrites the W
+// rows of every slab in place.
+int chain_prepare(AnnealArgs &a, int32_t *qt, bool w_chunked, hipStream_t stream);
 // Chain kernel plan and launchers (rp_anneal_chain.hip).
 bool chain_plan(AnnealArgs &a, int32_t n_cu, int32_t max_count, int32_t *pv_out, int32_t *dv_out);
 int launch_anneal_chain(const AnnealArgs &a, int32_t pv, int32_t dv, hipStream_t stream);

@@ -30,6 +30,7 @@
 #include "rp_anneal.h"
 #include "rp_device.h"
 #include "rp_internal.h"
+#include "rp_rows.h"
 
 namespace rp {
 
@@ -432,22 +433,45 @@ __global__ void __launch_bounds__(kThreads) k_layout_hash(const int32_t *layouts
     }
 }
 
-__global__ void __launch_bounds__(64) k_leader(const int32_t *layouts, int32_t N, const uint64_t *hash,
-                                               int32_t *leader) {
-    const int m = blockIdx.x, lane = lane_id();
+// The leader of every member: a workgroup's first wave finds the earlier
+// members with an equal hash, 64 at a time, and all its threads compare the
+// layouts.  Leaders are collected in list (any order), counted in *n_list
+// (zero on entry).
+__global__ void __launch_bounds__(kThreads) k_leader(const int32_t *layouts, int32_t N, const uint64_t *hash,
+                                                     int32_t *leader, int32_t *list, int32_t *n_list) {
+    __shared__ int32_t s_cand;
+    const int m = blockIdx.x, tid = threadIdx.x, lane = lane_id();
     const int32_t *lay = layouts + (int64_t)m * N;
-    int32_t found = m;
-    for (int u = 0; u < m; ++u) {
-        if (hash[u] != hash[m]) continue;
-        const int32_t *o = layouts + (int64_t)u * N;
-        bool diff = false;
-        for (int32_t i = lane; i < N; i += kWave) diff |= (o[i] != lay[i]);
-        if (!__ballot(diff)) {
-            found = u;
+    const uint64_t hm = hash[m];
+    int32_t from = 0, found = m;
+    while (from < m) {
+        if (tid < kWave) {
+            int32_t cand = m;
+            for (int32_t u = from; u < m; u += kWave) {
+                const uint64_t eq = __ballot(u + lane < m && hash[u + lane] == hm);
+                if (eq) {
+                    cand = u + first_lane(eq);
+                    break;
+                }
+            }
+            if (lane == 0) s_cand = cand;
+        }
+        __syncthreads();
+        const int32_t cand = s_cand;
+        if (cand == m) break;  // uniform
+        const int32_t *o = layouts + (int64_t)cand * N;
+        int diff = 0;
+        for (int32_t i = tid; i < N; i += kThreads) diff |= o[i] ^ lay[i];
+        if (!__syncthreads_or(diff)) {
+            found = cand;
             break;
         }
+        from = cand + 1;
     }
-    if (lane == 0) leader[m] = found;
+    if (tid == 0) {
+        leader[m] = found;
+        if (found == m) list[atomicAdd(n_list, 1)] = m;
+    }
 }
 
 // Cell statistics, validation, start offsets and the sorted member pool of
@@ -501,6 +525,22 @@ __global__ void __launch_bounds__(kThreads) k_build_cells(AnnealArgs a, const in
         T[c] = cT[c];
         Q[c] = cQ[c];
     }
+    // A of every row-shard (J starts from it: k_build_rowsums adds the rest)
+    for (int32_t h = tid; h < a.RG; h += kThreads) {
+        const int32_t r = h / a.G, g = h - r * a.G, cnt = a.count[g];
+        int64_t A = 0;
+        for (int s = 0; s < a.S; ++s) {
+            int64_t mx = 0;
+            for (int32_t x = 0; x < cnt; ++x) {
+                const int32_t c = r * a.D + a.slots[g * a.D + x];
+                const int64_t cost = a.alpha[s] * cT[c] + a.beta[s] * cQ[c];
+                if (x == 0 || cost > mx) mx = cost;
+            }
+            A += mx;
+        }
+        at<int64_t>(dst, a.off.J)[h] = A;
+        at<int64_t>(dst, a.off.A)[h] = A;
+    }
     __syncthreads();
     const int32_t st = *flag;
     if (tid == 0) status[m] = st;
@@ -542,6 +582,49 @@ __global__ void __launch_bounds__(kThreads) k_build_cells(AnnealArgs a, const in
         __syncthreads();  // every read of off[] for this chunk is done
         if (i < N && rank == tot - 1) off[c] += tot;
         __syncthreads();
+    }
+}
+
+// W rows of the leaders and their J (which holds A on entry), by waves
+// (rp_rows.h): item (leader, row-shard) x piece, on a fixed grid, since the
+// leaders are counted on the device.  For ranks a power of two from 4 to 64;
+// chunked: W rows as [P/4][L][4], the chain kernels' layout.  The 15 distinct
+// start layouts of 32768 samples (64 x 64, 62 row-shards) took 23 ms with a
+// workgroup per row-shard adding one row at a time, now 1.3 ms.
+template <bool ONE>
+__global__ void __launch_bounds__(kThreads) k_build_rowsums(AnnealArgs a, RowPieces pc, const int32_t *list,
+                                                            const int32_t *n_list, const int32_t *status, bool chunked) {
+    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const int32_t items = *n_list * a.RG, per = (items + 3) / 4, groups = per * pc.n_pieces;
+    const int32_t LP = a.LP, L = a.L, D = a.D, G = a.G;
+    for (int32_t gi = blockIdx.x; gi < groups; gi += gridDim.x) {
+        const int32_t piece = pc.spread ? gi % pc.n_pieces : gi / per;
+        const int32_t it = (pc.spread ? gi / pc.n_pieces : gi % per) * 4 + wv;
+        if (it >= items) continue;
+        const int32_t m = list[it / a.RG], h = it % a.RG, r = h / G, g = h - r * G;
+        if (status[m] != 0) continue;
+        char *dst = a.dst + (int64_t)m * a.off.bytes;
+        const int32_t *pool = at<int32_t>(dst, a.off.pool), *start = at<int32_t>(dst, a.off.start);
+        const RowLane<ONE> rl(piece, pc.lay_piece, L, a.P);
+        int32_t acc[4] = {0, 0, 0, 0};
+        for (int32_t x = 0; x < a.count[g];) {  // (adjacent slots are one range of the pool)
+            const int32_t d = a.slots[g * D + x];
+            int32_t n = 1;
+            while (x + n < a.count[g] && a.slots[g * D + x + n] == d + n) ++n;
+            const int32_t lo = start[r * D + d], hi = start[r * D + d + n];
+            rl.add(a.q, (int64_t)LP, a.P, pool + lo, hi - lo, acc);
+            x += n;
+        }
+        rl.fold(acc);
+        if (lane < rl.w4) {
+            int32_t *W = at<int32_t>(dst, a.off.W) + (int64_t)h * LP;
+            const int32_t l = rl.layer(), p = rl.rank();
+            *reinterpret_cast<int4 *>(W + (chunked ? p * L + l * 4 : l * a.P + p)) = make_int4(acc[0], acc[1], acc[2], acc[3]);
+        }
+        const int64_t mx = rl.layer_max(acc);  // (every lane takes part)
+        const int64_t part = wave_sum(rl.head() ? mx : 0);
+        if (lane == 0)
+            atomicAdd(reinterpret_cast<unsigned long long *>(at<int64_t>(dst, a.off.J) + h), (unsigned long long)part << a.F);
     }
 }
 
@@ -1028,22 +1111,62 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
     a.best = best; a.results = results;
     a.seed = prm->seed; a.p_guide = prm->p_guide_u32; a.rho = prm->rho_u32;
 
+    // Kernel choice: one wave per member when its state fits LDS (members
+    // updated in place, slabs handed over at resampling) -- the chain kernels
+    // when the shape fits their lane layout (the whole schedule in one
+    // cooperative launch when every workgroup can stay resident, else one
+    // launch per level), else the flat wave kernel --, else one workgroup per
+    // member over double-buffered slabs.
+    // ROUTEPACK_ANNEAL_KERNEL=chain_run|chain|wave|workgroup requests one
+    // kernel; a request the problem does not fit fails with
+    // ROUTEPACK_E_UNSUPPORTED.
+    int32_t mpw = 0, chain_pv = 0, chain_dv = 0;
+    bool tlds = false;
+    const char *force = getenv("ROUTEPACK_ANNEAL_KERNEL");
+    const bool want_run = !force || strcmp(force, "chain_run") == 0;
+    const bool want_chain = !force || strcmp(force, "chain") == 0;
+    const bool want_wave = !force || strcmp(force, "wave") == 0;
+    const bool want_group = !force || strcmp(force, "workgroup") == 0;
+    a.pop = pop_size;
+    int dev = 0, n_cu = 256, coop = 0;
+    RP_HIP(hipGetDevice(&dev));
+    RP_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+    RP_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
+    const bool chain_fits = (want_run || want_chain) && chain_plan(a, n_cu, topo.max_count, &chain_pv, &chain_dv);
+    RunArgs run;
+    memset(&run, 0, sizeof(run));
+    int run_rc = ROUTEPACK_E_UNSUPPORTED;
+    if (chain_fits && want_run && coop && prm->n_sweeps > 0)
+        run_rc = chain_run(a, run, chain_pv, chain_dv, n_cu, false, stream);
+    const bool whole = run_rc == ROUTEPACK_OK;
+    const bool chain = chain_fits && !whole && want_chain;
+
     // Build member slabs from the population (each distinct layout once) and
     // validate them.
     a.dst = slabA;
     uint64_t *hash = scr.get<uint64_t>(pop_size);
     int32_t *leader = scr.get<int32_t>(pop_size);
+    int32_t *lead_list = scr.get<int32_t>(pop_size), *n_lead = scr.get<int32_t>(1);
     if (scr.failed()) return ROUTEPACK_E_DEVICE;
     const size_t lds_build = (size_t)B64 * 24 + kThreads * 4 + 4 + 8 + 32 + 8;
     if (lds_build > 160 * 1024) return ROUTEPACK_E_UNSUPPORTED;
     RP_HIP(hipFuncSetAttribute((const void *)k_build_cells, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)lds_build));
     hipLaunchKernelGGL(k_layout_hash, dim3(pop_size), dim3(kThreads), 0, stream, population, N, hash);
-    hipLaunchKernelGGL(k_leader, dim3(pop_size), dim3(64), 0, stream, population, N, hash, leader);
+    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, stream, n_lead, (int64_t)1, 0);
+    hipLaunchKernelGGL(k_leader, dim3(pop_size), dim3(kThreads), 0, stream, population, N, hash, leader, lead_list,
+                       n_lead);
     hipLaunchKernelGGL(k_build_cells, dim3(pop_size), dim3(kThreads), lds_build, stream, a, population,
                        leader, status);
-    hipLaunchKernelGGL(k_build_rows, dim3((unsigned)(pop_size * RG64)), dim3(kThreads), 0, stream, a,
-                       leader, status);
+    const bool by_waves = P >= 4 && LP64 > 0 && ((uintptr_t)q & 15) == 0;
+    if (by_waves) {
+        const RowPieces pc = row_pieces(N, L, P);
+        hipLaunchKernelGGL(pc.one ? k_build_rowsums<true> : k_build_rowsums<false>, dim3(2048), dim3(kThreads), 0,
+                           stream, a, pc, lead_list, n_lead, status, whole || chain);
+    } else {
+        hipLaunchKernelGGL(k_build_rows, dim3((unsigned)(pop_size * RG64)), dim3(kThreads), 0, stream, a, leader,
+                           status);
+    }
     hipLaunchKernelGGL(k_build_final, dim3(pop_size), dim3(kThreads), 0, stream, a, leader, status);
     RP_HIP(hipGetLastError());
     std::vector<int32_t> hstat(pop_size);
@@ -1101,43 +1224,13 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
     }
     (void)xscore_in;
 
-    // Kernel choice: one wave per member when its state fits LDS (members
-    // updated in place, slabs handed over at resampling) -- the chain kernels
-    // when the shape fits their lane layout (the whole schedule in one
-    // cooperative launch when every workgroup can stay resident, else one
-    // launch per level), else the flat wave kernel --, else one workgroup per
-    // member over double-buffered slabs.
-    // ROUTEPACK_ANNEAL_KERNEL=chain_run|chain|wave|workgroup requests one
-    // kernel; a request the problem does not fit fails with
-    // ROUTEPACK_E_UNSUPPORTED.
-    int32_t mpw = 0, chain_pv = 0, chain_dv = 0;
-    bool tlds = false;
-    const char *force = getenv("ROUTEPACK_ANNEAL_KERNEL");
-    const bool want_run = !force || strcmp(force, "chain_run") == 0;
-    const bool want_chain = !force || strcmp(force, "chain") == 0;
-    const bool want_wave = !force || strcmp(force, "wave") == 0;
-    const bool want_group = !force || strcmp(force, "workgroup") == 0;
     if (!want_run && !want_chain && !want_wave && !want_group) return ROUTEPACK_E_INVALID;
-    a.pop = pop_size;
-    int dev = 0, n_cu = 256, coop = 0;
-    RP_HIP(hipGetDevice(&dev));
-    RP_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-    RP_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
-    const bool chain_fits = (want_run || want_chain) && chain_plan(a, n_cu, topo.max_count, &chain_pv, &chain_dv);
-    RunArgs run;
-    memset(&run, 0, sizeof(run));
-    bool whole = false;
-    if (chain_fits && want_run && coop && prm->n_sweeps > 0) {
-        const int rc = chain_run(a, run, chain_pv, chain_dv, n_cu, false, stream);
-        if (rc != ROUTEPACK_OK && rc != ROUTEPACK_E_UNSUPPORTED) return rc;
-        whole = rc == ROUTEPACK_OK;
-    }
-    const bool chain = chain_fits && !whole && want_chain;
+    if (run_rc != ROUTEPACK_OK && run_rc != ROUTEPACK_E_UNSUPPORTED) return run_rc;
     if (whole || chain) {
         a.slabs = slabA;
         int32_t *qt = scr.get<int32_t>(LP64 > 0 ? (size_t)N * LP64 : 1);
         if (scr.failed()) return ROUTEPACK_E_DEVICE;
-        RP_TRY(chain_prepare(a, qt, stream));
+        RP_TRY(chain_prepare(a, qt, by_waves, stream));
         if (a.hq) {  // (64 ranks: the members' cost prefixes live in HBM)
             a.gcp = scr.get<int64_t>((size_t)pop_size * (size_t)a.cp_stride);
             if (scr.failed()) return ROUTEPACK_E_DEVICE;

@@ -1890,14 +1890,14 @@ __global__ void __launch_bounds__(256) k_rows_to_chunks(const int32_t *src, int3
     }
 }
 
-int chain_prepare(AnnealArgs &a, int32_t *qt, hipStream_t stream) {
+int chain_prepare(AnnealArgs &a, int32_t *qt, bool w_chunked, hipStream_t stream) {
     if (a.L * a.P > 4096 || (a.P & 3) != 0) return ROUTEPACK_E_UNSUPPORTED;
     if (a.LP > 0) {
         hipLaunchKernelGGL(k_rows_to_chunks, dim3((unsigned)a.N), dim3(256), 0, stream, a.q, qt, (int64_t)a.N,
                            (int64_t)a.LP, (int64_t)1, (int64_t)a.LP, a.L, a.P);
         int32_t *w = reinterpret_cast<int32_t *>(a.slabs + a.off.W);
         const int64_t rows = (int64_t)a.pop * a.RG;
-        hipLaunchKernelGGL(k_rows_to_chunks, dim3((unsigned)rows), dim3(256), 0, stream, w, w, rows, (int64_t)a.LP,
+        if (!w_chunked) hipLaunchKernelGGL(k_rows_to_chunks, dim3((unsigned)rows), dim3(256), 0, stream, w, w, rows, (int64_t)a.LP,
                            (int64_t)a.RG, a.off.bytes / (int64_t)sizeof(int32_t), a.L, a.P);
         if (hipGetLastError() != hipSuccess) return ROUTEPACK_E_DEVICE;
     }

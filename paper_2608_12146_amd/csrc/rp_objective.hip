@@ -15,6 +15,7 @@
 
 #include "rp_device.h"
 #include "rp_internal.h"
+#include "rp_rows.h"
 
 namespace rp {
 
@@ -238,12 +239,10 @@ struct RowArgs {
 constexpr int kEvalWaves = 4;
 
 // Bound by reading q rows (each of the n layouts reads all of q) from
-// wherever they are kept: a lane holds four ranks of one layer, eight rows
-// are in flight, and the pieces (whole layers) are laid out so that the
-// slice of q that an XCD reads stays in its L2 when it fits, and in the last
-// level cache otherwise (see eval_layouts).  A piece narrower than half a
-// wave (ONE false) is read by several groups of lanes, each taking every
-// ng-th member.  Sum is uint32_t when no sum of q entries passes 2^32.
+// wherever they are kept: the pieces are laid out so that the slice of q that
+// an XCD reads stays in its L2 when it fits, and in the last level cache
+// otherwise (row_pieces).  Sum is uint32_t when no sum of q entries passes
+// 2^32.
 template <bool ONE, typename Sum>
 __global__ void __launch_bounds__(kEvalWaves *kWave) k_eval_rows(RowArgs a) {
     const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
@@ -256,64 +255,17 @@ __global__ void __launch_bounds__(kEvalWaves *kWave) k_eval_rows(RowArgs a) {
     const int32_t h = (int32_t)(it - lay * (uint32_t)a.RG);
     const int32_t *list = a.list + (int64_t)lay * a.N, *hs = a.hstart + (int64_t)lay * (a.RG + 1) + h;
     const int32_t lo = hs[0], n = hs[1] - lo;
-    const int32_t l0 = piece * a.lay_piece, nl = a.lay_piece < a.L - l0 ? a.lay_piece : a.L - l0;
-    const int32_t g4 = a.P >> 2, w4 = nl * g4;  // 16-byte words of a layer, of the piece
-    const int32_t ng = ONE ? 1 : kWave / w4, grp = ONE ? 0 : lane / w4, col = lane - grp * w4;
-    const bool act = ONE ? lane < w4 : grp < ng;
-    const int64_t stride = (int64_t)a.L * a.P;
-    const int32_t *base = a.q + (int64_t)l0 * a.P + 4 * (act ? col : 0);
+    const RowLane<ONE> rl(piece, a.lay_piece, a.L, a.P);
     Sum acc[4] = {0, 0, 0, 0};
-    constexpr int U = 8;
-    for (int32_t mb = 0; mb < n; mb += kWave) {
-        const int32_t lim = n - mb < kWave ? n - mb : kWave;
-        const int32_t ids = list[lo + (mb + lane < n ? mb + lane : 0)];
-        for (int32_t m = 0; m < lim; m += U * ng) {
-            int4 v[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t x = m + u * ng + grp;
-                if (ONE) {
-                    const int32_t i = __builtin_amdgcn_readlane(ids, x < lim ? x : 0);
-                    v[u] = *reinterpret_cast<const int4 *>(base + i * stride);
-                } else {
-                    const int32_t i = __shfl(ids, x < lim ? x : 0, kWave);
-                    v[u] = *reinterpret_cast<const int4 *>(base + i * stride);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (m + u * ng + grp < lim) {
-                    acc[0] += (Sum)v[u].x;
-                    acc[1] += (Sum)v[u].y;
-                    acc[2] += (Sum)v[u].z;
-                    acc[3] += (Sum)v[u].w;
-                }
-            }
-        }
-    }
+    rl.add(a.q, (int64_t)a.L * a.P, a.P, list + lo, n, acc);
     int64_t s4[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) s4[c] = (int64_t)acc[c];
-    if (!ONE)
-        for (int32_t k = 1; k < ng; ++k) {
-            const int src = lane + k * w4;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int64_t o = (int64_t)__shfl(acc[c], src < kWave ? src : lane, kWave);
-                s4[c] += lane < w4 ? o : 0;
-            }
-        }
-    int64_t mx = s4[0], sm = s4[0] + s4[1] + s4[2] + s4[3];
-#pragma unroll
-    for (int c = 1; c < 4; ++c) mx = s4[c] > mx ? s4[c] : mx;
-    int64_t o;
-    if (g4 >= 2) { o = dpp64<kDppXor1>(mx, mx); mx = o > mx ? o : mx; sm += dpp64<kDppXor1>(sm, 0); }
-    if (g4 >= 4) { o = dpp64<kDppXor2>(mx, mx); mx = o > mx ? o : mx; sm += dpp64<kDppXor2>(sm, 0); }
-    if (g4 >= 8) { o = dpp64<kDppHalfMirror>(mx, mx); mx = o > mx ? o : mx; sm += dpp64<kDppHalfMirror>(sm, 0); }
-    if (g4 >= 16) { o = dpp64<kDppMirror>(mx, mx); mx = o > mx ? o : mx; sm += dpp64<kDppMirror>(sm, 0); }
-    const bool head = lane < w4 && (lane & (g4 - 1)) == 0;
+    rl.fold(s4);
+    const int64_t mx = rl.layer_max(s4), sm = rl.layer_sum(s4);
+    const bool head = rl.head();
     if (a.wmax && head) {
-        const int64_t at = (int64_t)it * a.L + l0 + lane / g4;
+        const int64_t at = (int64_t)it * a.L + rl.layer();
         a.wmax[at] = mx;
         a.wsum[at] = sm;
     }
@@ -507,18 +459,10 @@ int eval_layouts(const routepack_problem *p, const Topology &topo, const DeviceP
         la.alpha = dp.alpha; la.beta = dp.beta;
         RowArgs ra;
         ra.q = q; ra.N = (int32_t)N; ra.L = (int32_t)L; ra.P = (int32_t)P; ra.RG = (int32_t)RG; ra.F = p->frac_bits;
-        // Workgroups go round the 8 XCDs: with 2, 4 or 8 pieces and
-        // consecutive workgroups on different ones, an XCD reads only its
-        // piece's slice of q, worth it when that slice stays in a 4 MiB L2
-        // (up to 2 MiB: the lists pass through it too); else one piece at a
-        // time, whose slice all XCDs share in the last level cache.
-        const int64_t most = 256 / P;
-        int32_t np = 1;
-        while (np <= 8 && ((L + np - 1) / np > most || N * ((L + np - 1) / np) * P * 4 > (int64_t)2 << 20)) np *= 2;
-        ra.spread = np <= 8 ? 1 : 0;
-        if (!ra.spread) np = (int32_t)((L + most - 1) / most);
-        ra.lay_piece = (int32_t)((L + np - 1) / np);
-        ra.n_pieces = (int32_t)((L + ra.lay_piece - 1) / ra.lay_piece);
+        const RowPieces pc = row_pieces(N, L, P);
+        ra.spread = pc.spread ? 1 : 0;
+        ra.lay_piece = pc.lay_piece;
+        ra.n_pieces = pc.n_pieces;
         // the sample lists of at most 64 Mi entries at a time
         int64_t nb = ((int64_t)64 << 20) / N;
         nb = nb < 1 ? 1 : (nb > n ? n : nb);
@@ -541,7 +485,7 @@ int eval_layouts(const routepack_problem *p, const Topology &topo, const DeviceP
             ra.wmax = diag ? wmax + l0 * RG * L : nullptr;
             ra.wsum = diag ? wsum + l0 * RG * L : nullptr;
             const int64_t wgs = (ra.items + kEvalWaves - 1) / kEvalWaves * ra.n_pieces;
-            auto rows = ra.lay_piece * P > 128 ? (sum32 ? k_eval_rows<true, uint32_t> : k_eval_rows<true, int64_t>)
+            auto rows = pc.one ? (sum32 ? k_eval_rows<true, uint32_t> : k_eval_rows<true, int64_t>)
                                                : (sum32 ? k_eval_rows<false, uint32_t> : k_eval_rows<false, int64_t>);
             hipLaunchKernelGGL(rows, dim3((unsigned)wgs), dim3(kEvalWaves * kWave), 0, stream, ra);
         }

@@ -28,6 +28,7 @@
 
 #include "rp_device.h"
 #include "rp_internal.h"
+#include "rp_rows.h"
 
 namespace rp {
 
@@ -936,6 +937,37 @@ __global__ void __launch_bounds__(128) k_pack_cellsum(TrialArgs a, PackFast pf, 
     }
 }
 
+// k_pack_cellsum by waves, for ranks a power of two from 4 to 64 (rp_rows.h):
+// item (candidate, cell) x piece; peak starts at zero.  Every candidate reads
+// all of q once, so this is bound by where the pieces' slices of q are kept:
+// 15 candidates of 32768 samples (64 x 64, 512 MiB of q) take 8.2 ms with a
+// workgroup per cell and scalar loads in member order, 0.99 ms in pieces.
+template <bool ONE>
+__global__ void __launch_bounds__(256) k_pack_cellrows(TrialArgs a, PackFast pf, RowPieces pc, int32_t items,
+                                                       bool chunked) {
+    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const uint32_t per = (uint32_t)(items + 3) / 4, b = blockIdx.x, np = (uint32_t)pc.n_pieces;
+    const int32_t piece = (int32_t)(pc.spread ? b % np : b / per);
+    const int32_t it = (int32_t)((pc.spread ? b / np : b % per) * 4 + wv);
+    if (it >= items) return;
+    const int32_t K = a.K, L = a.L, tr = it / K, k = it - tr * K;
+    if (!a.ok[tr]) return;  // a failed trial has no layout
+    const int32_t *ms = pf.mstart + (int64_t)tr * (K + 1) + k;
+    const int32_t lo = ms[0], n = ms[1] - lo;
+    const RowLane<ONE> rl(piece, pc.lay_piece, L, a.P);
+    int32_t acc[4] = {0, 0, 0, 0};
+    rl.add(a.q, (int64_t)a.LP, a.P, pf.mlist + (int64_t)tr * a.N + lo, n, acc);
+    rl.fold(acc);
+    if (lane < rl.w4) {
+        int32_t *Qk = a.Qc + (int64_t)it * a.LP;
+        const int32_t l = rl.layer(), p = rl.rank();
+        *reinterpret_cast<int4 *>(Qk + (chunked ? p * L + l * 4 : l * a.P + p)) = make_int4(acc[0], acc[1], acc[2], acc[3]);
+    }
+    const int64_t mx = rl.layer_max(acc);  // (every lane takes part)
+    const int64_t part = wave_sum(rl.head() ? mx : 0);
+    if (lane == 0) atomicAdd(reinterpret_cast<unsigned long long *>(a.peak + it), (unsigned long long)part);
+}
+
 // ---------------------------------------------------------------------------
 // EDPAwarePair in batches of kPairBatch cells, for up to 64 layers and 64
 // ranks (a multiple of 4).  A step's choice needs sum_l max_p (W_h + Q_k) and
@@ -1759,7 +1791,17 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
         } else {
             hipLaunchKernelGGL(k_pack_fit, dim3(nb), dim3(64), fit_lds, stream, ta, pf);
         }
-        hipLaunchKernelGGL(k_pack_cellsum, dim3(K, nb), dim3(128), (size_t)4 * LP, stream, ta, pf, batched);
+        if (P >= 4 && P <= 64 && (P & (P - 1)) == 0 && ((uintptr_t)q & 15) == 0) {
+            const RowPieces pc = row_pieces(N, L, P);
+            const int32_t items = nb * K;
+            const unsigned wgs = (unsigned)((items + 3) / 4 * pc.n_pieces);
+            hipLaunchKernelGGL(k_fill_i32, dim3(64), dim3(256), 0, stream, reinterpret_cast<int32_t *>(ta.peak),
+                               (int64_t)2 * items, 0);
+            hipLaunchKernelGGL(pc.one ? k_pack_cellrows<true> : k_pack_cellrows<false>, dim3(wgs), dim3(256), 0, stream,
+                               ta, pf, pc, items, batched);
+        } else {
+            hipLaunchKernelGGL(k_pack_cellsum, dim3(K, nb), dim3(128), (size_t)4 * LP, stream, ta, pf, batched);
+        }
         if (batched) {
             PairArgs pa;
             pa.after = scr.get<int64_t>((size_t)nb * kPairBatch * RG);

@@ -176,3 +176,36 @@ def test_pack_first_fit(K, N, scale):
     q[:] = rng.integers(0, 9, size=q.shape)
     kw.update(min_rows=K, frac_bits=0, alpha_fp=np.array([1]), beta_fp=np.array([0]))
     _check_pack(t, q, kw, 1, trials=2)
+
+
+@gpu
+@pytest.mark.parametrize("P,L", [(2, 3), (4, 1), (8, 33), (16, 20), (64, 5)])
+@pytest.mark.parametrize("shards", ["one", "interleaved", "runs"])
+def test_anneal_start_state(P, L, shards):
+    """Two levels from a population of distinct and repeated layouts whose
+    shards hold adjacent slots, none adjacent, or runs of slots: every W row,
+    J and pool of the start state enters the trace."""
+    import oracle as O
+    import paper_2608_12146_amd as rp
+    _log(f"anneal start P={P} L={L} {shards}")
+    D, R = 6, 7
+    rng = np.random.default_rng([18, P, L])
+    N = 4 * R * D + 5
+    t = rng.integers(1, 60, size=N)
+    G = {"one": 1, "interleaved": 2, "runs": 3}[shards]
+    t, q, kw = _pack_case(N, D, G, int(-(-t.sum() // (R * D)) * 1.5) + 40, t, L=L, P=P)
+    kw["min_rows"] = R
+    kw["dp_to_edp"] = np.array({"one": [0] * 6, "interleaved": [0, 1] * 3, "runs": [2, 2, 0, 1, 1, 0]}[shards],
+                               dtype=np.int32)
+    pb, prob = O.Problem.from_dict(kw), rp.Problem.from_dict(kw)
+    pk = O.pack_rows(pb, t, q, 3, 8, 4, 20)
+    assert pk["rc"] == 0
+    pop = pk["population"].copy()
+    rows = rng.permutation(R)  # the rows in another order: further distinct layouts
+    pop[5:9] = rows[pop[5:9] // D] * D + pop[5:9] % D
+    temps = np.array([1e-2, 1e-3])
+    o = O.anneal(pb, t, q, pk["r_star"], pop, temps, 48, 9)
+    g = rp.anneal(prob, t, q, pk["r_star"], pop, temps, 48, 9)
+    assert np.array_equal(g["trace"].cpu().numpy(), o["trace"])
+    assert np.array_equal(g["population"].cpu().numpy(), o["population"])
+    assert np.array_equal(g["best_layout"].cpu().numpy(), o["best_layout"])
