@@ -205,7 +205,7 @@ extern "C" int routepack_row_lower_bound(const routepack_problem *prob, const in
     unsigned long long *best = scr.get<unsigned long long>(1);
     if (scr.failed()) return ROUTEPACK_E_DEVICE;
     RP_HIP(hipMemsetAsync(best, 0, sizeof(*best), stream));
-    RP_TRY(rank_sort_desc(lengths, N, sigma, stream));
+    RP_TRY(rank_sort_desc(lengths, N, sigma, scr, stream));
     hipLaunchKernelGGL(k_sorted_lengths, dim3((N + 255) / 256), dim3(256), 0, stream, lengths, sigma, N, ts);
     hipLaunchKernelGGL(k_prefix, dim3(1), dim3(1024), 0, stream, (const int64_t *)ts, N, ps);
     hipLaunchKernelGGL(k_cell_bounds, dim3((N + 255) / 256), dim3(256), 0, stream, (const int64_t *)ts,
@@ -247,7 +247,7 @@ extern "C" int routepack_fixed_bin_search(const routepack_problem *prob, const i
     int32_t *ts = scr.get<int32_t>(N);
     int64_t *out = scr.get<int64_t>(2);
     if (scr.failed()) return ROUTEPACK_E_DEVICE;
-    RP_TRY(rank_sort_desc(lengths, N, sigma, stream));
+    RP_TRY(rank_sort_desc(lengths, N, sigma, scr, stream));
     hipLaunchKernelGGL(k_sorted_lengths32, dim3((N + 255) / 256), dim3(256), 0, stream, lengths,
                        (const int32_t *)sigma, N, ts);
     if (hipFuncSetAttribute((const void *)k_fixed_bin, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=

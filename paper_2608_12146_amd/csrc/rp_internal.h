@@ -89,7 +89,7 @@ int overflow_check(const routepack_problem *p, int64_t n_rows, const WindowStats
                    bool w_as_int32);
 
 // sigma = the samples ordered by (-t, i) (rp_pack.hip).
-int rank_sort_desc(const int32_t *lengths, int32_t N, int32_t *sigma, hipStream_t stream);
+int rank_sort_desc(const int32_t *lengths, int32_t N, int32_t *sigma, Scratch &scr, hipStream_t stream);
 
 // Device copies of small per-problem tables.
 struct DeviceProblem {

@@ -1,7 +1,7 @@
 // Row-count search, FixedRowFFD and the feasible seed population (Sec. 3.2,
 // Sec. 4.1.1, Alg. 2) on gfx950.
 //
-//  k_rank_sort     sigma = samples ordered by (-t, i): the rank of sample i is
+//  k_rank_*        sigma = samples ordered by (-t, i): the rank of sample i is
 //                  the number of samples that precede it (exact, parallel).
 //  k_ffd           FixedRowFFD for K = R*D cells, one wave: the K longest
 //                  samples open the cells; every later sample goes to the
@@ -40,35 +40,50 @@ __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v);
 
 constexpr int kMaxCells = 4096;
 
-__global__ void __launch_bounds__(256) k_rank_sort(const int32_t *__restrict__ t, int32_t N,
-                                                   int32_t *__restrict__ sigma) {
-    __shared__ __align__(16) int32_t tile[1024];
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+// Ranks by counting: a workgroup counts, for 256 samples, those that precede
+// them among a slice of the others (tiles of 256; a whole tile of earlier
+// samples precedes at equal lengths too, a tile of later ones does not), and
+// adds its counts to rank (zero on entry).  N^2 compares: slices as well as
+// samples are spread over workgroups, about 2048 of them, since 128 or 16
+// workgroups left most of the chip idle (32768 samples: 0.86 ms, now 73 us;
+// 4096: 108 us, now 11 us).
+__global__ void __launch_bounds__(256) k_rank_count(const int32_t *__restrict__ t, int32_t N, int32_t tiles,
+                                                    int32_t *__restrict__ rank) {
+    __shared__ __align__(16) int32_t tile[256];
+    const int32_t ib = blockIdx.x, tid = threadIdx.x, i = ib * 256 + tid;
     const int32_t ti = i < N ? t[i] : 0;
-    int32_t rank = 0;
-    for (int32_t base = 0; base < N; base += 1024) {
-        for (int x = threadIdx.x; x < 1024; x += blockDim.x) tile[x] = base + x < N ? t[base + x] : -1;
+    int32_t n = 0;
+    const int32_t nt = (N + 255) / 256, j1 = ((int32_t)blockIdx.y + 1) * tiles < nt ? ((int32_t)blockIdx.y + 1) * tiles : nt;
+    for (int32_t jb = blockIdx.y * tiles; jb < j1; ++jb) {
         __syncthreads();
-        const int32_t lim = N - base < 1024 ? N - base : 1024;
-        // four lengths per 16-byte LDS read, several reads in flight
+        // (past the end: below every length, so counted nowhere)
+        tile[tid] = jb * 256 + tid < N ? t[jb * 256 + tid] : INT32_MIN;
+        __syncthreads();
         const int4 *t4 = reinterpret_cast<const int4 *>(tile);
-        const int32_t lim4 = lim >> 2;
+        if (jb < ib) {
+#pragma unroll 8
+            for (int x = 0; x < 64; ++x) {
+                const int4 v = t4[x];
+                n += (v.x >= ti) + (v.y >= ti) + (v.z >= ti) + (v.w >= ti);
+            }
+        } else if (jb > ib) {
+#pragma unroll 8
+            for (int x = 0; x < 64; ++x) {
+                const int4 v = t4[x];
+                n += (v.x > ti) + (v.y > ti) + (v.z > ti) + (v.w > ti);
+            }
+        } else {
 #pragma unroll 4
-        for (int x4 = 0; x4 < lim4; ++x4) {
-            const int4 v = t4[x4];
-            const int32_t x = base + 4 * x4;
-            rank += (v.x > ti) || (v.x == ti && x < i);
-            rank += (v.y > ti) || (v.y == ti && x + 1 < i);
-            rank += (v.z > ti) || (v.z == ti && x + 2 < i);
-            rank += (v.w > ti) || (v.w == ti && x + 3 < i);
+            for (int x = 0; x < 256; ++x) n += tile[x] > ti || (tile[x] == ti && x < tid);
         }
-        for (int x = 4 * lim4; x < lim; ++x) {
-            const int32_t tj = tile[x];
-            rank += (tj > ti) || (tj == ti && base + x < i);
-        }
-        __syncthreads();
     }
-    if (i < N) sigma[rank] = i;
+    if (i < N && n) atomicAdd(&rank[i], n);
+}
+
+__global__ void __launch_bounds__(256) k_rank_place(const int32_t *__restrict__ rank, int32_t N,
+                                                    int32_t *__restrict__ sigma) {
+    const int32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < N) sigma[rank[i]] = i;
 }
 
 // Lane i's value becomes lane i + 1's (lane 63: 0), or lane i - 1's (lane 0: 0).
@@ -1531,61 +1546,77 @@ __global__ void __launch_bounds__(1024) k_pack_pair(TrialArgs a, PackFast pf) {
     for (int32_t i = tid; i < N; i += nt) out[i] = cell_to[cellk[i]];
 }
 
-// Canonical form of layouts[b] (b < n) into canon[b].
-__global__ void __launch_bounds__(256) k_canonical(const int32_t *layouts, int32_t n, int32_t N, int32_t R,
-                                                   int32_t D, int32_t G, const int32_t *slots,
-                                                   const int32_t *count, const int32_t *slot_shard,
-                                                   int32_t *cellmin_g, int32_t *newcell_g, int32_t *rowkey_g,
-                                                   int32_t *canon) {
-    const int b = blockIdx.x;
-    const int tid = threadIdx.x;
+// 64-bit mix of a (sample, cell) pair (the finaliser of splitmix64).
+__device__ inline uint64_t mix64(uint64_t z) {
+    z += 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+}
+
+// Canonical form of layouts[b] (b < n) into canon[b], with an order-free hash
+// of it.  One workgroup per layout, cell tables in LDS; bound by the two
+// passes over the layout (a quarter of the threads and tables in global
+// memory: 168 us for 16 layouts of 32768 samples, now 35 us).
+__global__ void __launch_bounds__(1024) k_canonical(const int32_t *layouts, int32_t N, int32_t R, int32_t D,
+                                                    const int32_t *slots, const int32_t *count,
+                                                    const int32_t *slot_shard, int32_t *canon, uint64_t *hash) {
+    extern __shared__ __align__(16) int32_t scan_lds[];
+    __shared__ uint64_t part[16];
+    const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
     const int32_t B = R * D;
     const int32_t *lay = layouts + (int64_t)b * N;
-    int32_t *cmin = cellmin_g + (int64_t)b * B;
-    int32_t *newd = newcell_g + (int64_t)b * B;
-    int32_t *rkey = rowkey_g + (int64_t)b * R;
-    for (int32_t c = tid; c < B; c += blockDim.x) cmin[c] = INT32_MAX;
+    int32_t *cmin = scan_lds, *newd = cmin + B, *rkey = newd + B;  // [B], [B], [R]
+    for (int32_t c = tid; c < B; c += nt) cmin[c] = INT32_MAX;
     __syncthreads();
-    for (int32_t i = tid; i < N; i += blockDim.x) {
+    for (int32_t i = tid; i < N; i += nt) {
         const int32_t c = lay[i];
         if (c >= 0 && c < B) atomicMin(&cmin[c], i);
     }
     __syncthreads();
     // slot of each cell within its row-shard after ordering by smallest id
-    for (int32_t c = tid; c < B; c += blockDim.x) {
+    for (int32_t c = tid; c < B; c += nt) {
         const int32_t r = c / D, d = c % D, g = slot_shard[d];
         const int32_t v = cmin[c];
         int32_t rank = 0;
-        for (int32_t x = 0; x < count[g]; ++x) {
-            const int32_t u = cmin[r * D + slots[g * D + x]];
-            rank += u < v;
-        }
+        for (int32_t x = 0; x < count[g]; ++x) rank += cmin[r * D + slots[g * D + x]] < v;
         newd[c] = slots[g * D + rank];
     }
-    __syncthreads();
     // row key: smallest id of the cell that lands in slot 0
-    for (int32_t r = tid; r < R; r += blockDim.x) rkey[r] = INT32_MAX;
+    for (int32_t r = tid; r < R; r += nt) rkey[r] = INT32_MAX;
     __syncthreads();
-    for (int32_t c = tid; c < B; c += blockDim.x)
+    for (int32_t c = tid; c < B; c += nt)
         if (newd[c] == 0) rkey[c / D] = cmin[c];
     __syncthreads();
-    for (int32_t c = tid; c < B; c += blockDim.x) {
-        const int32_t r = c / D;
-        const int32_t v = rkey[r];
+    for (int32_t c = tid; c < B; c += nt) {
+        const int32_t v = rkey[c / D];
         int32_t rank = 0;
         for (int32_t x = 0; x < R; ++x) rank += rkey[x] < v;
         newd[c] = rank * D + newd[c];
     }
     __syncthreads();
-    for (int32_t i = tid; i < N; i += blockDim.x) {
+    uint64_t h = 0;
+    for (int32_t i = tid; i < N; i += nt) {
         const int32_t c = lay[i];
-        canon[(int64_t)b * N + i] = (c >= 0 && c < B) ? newd[c] : -1;
+        const int32_t v = (c >= 0 && c < B) ? newd[c] : -1;
+        canon[(int64_t)b * N + i] = v;
+        h += mix64(((uint64_t)(uint32_t)i << 32) | (uint32_t)v);
+    }
+    h = (uint64_t)wave_sum((int64_t)h);
+    if (lane_id() == 0) part[wave_id()] = h;
+    __syncthreads();
+    if (tid == 0) {
+        for (int w = 1; w < nt / kWave; ++w) h += part[w];
+        hash[b] = h;
     }
 }
 
 // Selection and cyclic fill.  cand m: 0 x_length, 1 x_paired (kept when
 // strictly better than x_length), m >= 2 trial m-1 (kept when it succeeded).
-__global__ void __launch_bounds__(256) k_pack_select(const int32_t *canon, const int64_t *scores,
+// Layouts are compared only when their hashes are equal (every pair, element
+// by element in one workgroup: 316 us for 15 layouts of 4096 samples and
+// 2.2 ms for 32768, now 32 us and 34 us).
+__global__ void __launch_bounds__(1024) k_pack_select(const int32_t *canon, const uint64_t *hash, const int64_t *scores,
                                                      const int32_t *ok, const int32_t *status,
                                                      int32_t M, int32_t N,
                                                      int32_t *keep_order, int32_t *meta) {
@@ -1608,7 +1639,7 @@ __global__ void __launch_bounds__(256) k_pack_select(const int32_t *canon, const
         if (!valid[m]) continue;
         bool dup = false;
         for (int u = 0; u < m && !dup; ++u) {
-            if (!kept[u]) continue;
+            if (!kept[u] || hash[u] != hash[m]) continue;  // (uniform)
             if (tid == 0) differ = 0;
             __syncthreads();
             for (int32_t i = tid; i < N; i += blockDim.x)
@@ -1659,8 +1690,17 @@ __global__ void k_pack_fill(const int32_t *canon, const int64_t *scores, const i
 }  // namespace rp
 
 namespace rp {
-int rank_sort_desc(const int32_t *lengths, int32_t N, int32_t *sigma, hipStream_t stream) {
-    hipLaunchKernelGGL(k_rank_sort, dim3((N + 255) / 256), dim3(256), 0, stream, lengths, N, sigma);
+int rank_sort_desc(const int32_t *lengths, int32_t N, int32_t *sigma, Scratch &scr, hipStream_t stream) {
+    int32_t *rank = scr.get<int32_t>(N);
+    if (scr.failed()) return ROUTEPACK_E_DEVICE;
+    const int32_t nt = (N + 255) / 256;
+    int32_t slices = 2048 / nt;
+    slices = slices < 1 ? 1 : (slices > nt ? nt : slices);
+    const int32_t tiles = (nt + slices - 1) / slices;
+    slices = (nt + tiles - 1) / tiles;
+    hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)(nt < 64 ? nt : 64)), dim3(256), 0, stream, rank, (int64_t)N, 0);
+    hipLaunchKernelGGL(k_rank_count, dim3((unsigned)nt, (unsigned)slices), dim3(256), 0, stream, lengths, N, tiles, rank);
+    hipLaunchKernelGGL(k_rank_place, dim3((unsigned)nt), dim3(256), 0, stream, (const int32_t *)rank, N, sigma);
     return hipGetLastError() == hipSuccess ? ROUTEPACK_OK : ROUTEPACK_E_DEVICE;
 }
 }  // namespace rp
@@ -1701,7 +1741,7 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
     int32_t *x_len = scr.get<int32_t>(N);
     int32_t *flag = scr.get<int32_t>(4);
     if (scr.failed()) return ROUTEPACK_E_DEVICE;
-    hipLaunchKernelGGL(k_rank_sort, dim3((N + 255) / 256), dim3(256), 0, stream, lengths, N, sigma);
+    RP_TRY(rank_sort_desc(lengths, N, sigma, scr, stream));
     int64_t R = -1;
     for (int64_t r = r_lb; r <= r_max; ++r) {
         if (r * D > kMaxCells) return ROUTEPACK_E_UNSUPPORTED;
@@ -1746,9 +1786,7 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
     int64_t *cscore = scr.get<int64_t>((size_t)M * 3);
     int32_t *cstat = scr.get<int32_t>(M);
     int32_t *okv = scr.get<int32_t>(M);
-    int32_t *cmin = scr.get<int32_t>((size_t)M * K);
-    int32_t *newc = scr.get<int32_t>((size_t)M * K);
-    int32_t *rkey = scr.get<int32_t>((size_t)M * R);
+    uint64_t *chash = scr.get<uint64_t>(M);
     int32_t *keep = scr.get<int32_t>(64);
     int32_t *meta = scr.get<int32_t>(2);
     if (scr.failed()) return ROUTEPACK_E_DEVICE;
@@ -1842,9 +1880,10 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
     // status is nonzero or they are ignored by the selection).
     RP_TRY(eval_layouts(prob, topo, dp, lengths, q, (int32_t)R, M, cand, cscore, cstat, nullptr,
                         nullptr, nullptr, sums_fit32(ws), stream));
-    hipLaunchKernelGGL(k_canonical, dim3(M), dim3(256), 0, stream, cand, M, N, (int32_t)R, D, G,
-                       dp.slots, dp.count, dp.slot_shard, cmin, newc, rkey, canon);
-    hipLaunchKernelGGL(k_pack_select, dim3(1), dim3(256), 0, stream, canon, cscore, okv, cstat, M, N, keep,
+    const int wide = N > 1024 ? 1024 : 256;
+    hipLaunchKernelGGL(k_canonical, dim3(M), dim3(wide), (size_t)4 * (2 * K + R), stream, cand, N, (int32_t)R, D,
+                       dp.slots, dp.count, dp.slot_shard, canon, chash);
+    hipLaunchKernelGGL(k_pack_select, dim3(1), dim3(wide), 0, stream, canon, chash, cscore, okv, cstat, M, N, keep,
                        meta);
     hipLaunchKernelGGL(k_pack_fill, dim3(pop_size), dim3(256), 0, stream, canon, cscore, keep, meta, N,
                        population, scores);
