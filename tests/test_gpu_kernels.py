@@ -209,3 +209,28 @@ def test_anneal_start_state(P, L, shards):
     assert np.array_equal(g["trace"].cpu().numpy(), o["trace"])
     assert np.array_equal(g["population"].cpu().numpy(), o["population"])
     assert np.array_equal(g["best_layout"].cpu().numpy(), o["best_layout"])
+
+
+@gpu
+@pytest.mark.parametrize("K,N,fill", [(1, 3, 0.5), (64, 64, 0.9), (65, 200, 0.99), (128, 129, 1.0), (300, 900, 0.97),
+                                      (4096, 4500, 0.9), (4097, 4300, 0.9)])
+@pytest.mark.parametrize("scale", [1, 1 << 23])
+def test_fixed_bin_chunks(K, N, fill, scale):
+    """The search over part-filled chunks of cells, equal lengths, dead ends
+    and backtracking over blocks of samples, the most chunked cells and the
+    first count past them, with a cap below and above 2^31."""
+    import oracle.fixedbin as F
+    import paper_2608_12146_amd as rp
+    _log(f"fixed bin K={K} N={N} fill={fill} scale={scale}")
+    rng = np.random.default_rng([19, K, N])
+    for rep in range(3):
+        t = rng.integers(1, 60, size=N) if rep else np.repeat(rng.integers(1, 60, size=(N + 2) // 3), 3)[:N]
+        cap = max(int(t.max()), int(t.sum() / (K * fill)) + 1)
+        t, cap = (t * scale).astype(np.int32), cap * scale
+        prob = rp.Problem(N, 0, 1, 1, 1, 1, 1, [0], cap, [1], [0])
+        got = rp.fixed_bin_search(prob, t, K, 3000)
+        want = F.search(t, cap, K, 3000)
+        assert got[:2] == want[:2]
+        assert (got[2] is None) == (want[2] is None)
+        if got[2] is not None:
+            assert np.array_equal(got[2].cpu().numpy(), want[2])
