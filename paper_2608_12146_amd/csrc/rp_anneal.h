@@ -67,6 +67,8 @@ struct AnnealArgs {
 // Wave kernel plan and launchers (rp_anneal_wave.hip).
 bool wave_plan(AnnealArgs &a, int32_t n_cu, int32_t *mpw_out, bool *tlds_out);
 int launch_anneal_wave(const AnnealArgs &a, bool tlds, hipStream_t stream);
+constexpr int kFlagStride = 32;  // (128 bytes: a line of its own)
+
 // Arguments of the whole-schedule chain kernel (rp_anneal_chain.hip).
 struct RunArgs {
     const double *temps;   // [n_sweeps] (device)
@@ -78,6 +80,7 @@ struct RunArgs {
     int32_t *xstar;        // [N]
     int64_t *xscore;       // [3]
     unsigned *bar;         // grid barrier arrivals (zero at launch)
+    unsigned *flags;       // [workgroups] kFlagStride apart: the last grid barrier completed (zero at launch)
     int32_t *err;          // set when a grid barrier times out
     int32_t *slab_of_out;  // [pop] slab of each member after the run
     double *energy;        // [2][pop] terminal energy of each member (by level parity)

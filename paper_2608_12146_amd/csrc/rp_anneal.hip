@@ -1286,6 +1286,8 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
         double *temps_d = scr.get<double>(prm->n_sweeps);
         uint32_t *vwords = scr.get<uint32_t>(prm->n_sweeps);
         unsigned *bar = scr.get<unsigned>(2);
+        const size_t n_flags = (size_t)((pop_size + a.mpw - 1) / a.mpw) * kFlagStride;
+        unsigned *bar_flags = scr.get<unsigned>(n_flags);
         int32_t *slab_final = scr.get<int32_t>(pop_size);
         // by level parity: a workgroup that runs ahead into the next level
         // writes the other half
@@ -1299,6 +1301,7 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
         RP_HIP(hipMemcpyAsync(temps_d, prm->temperatures, sizeof(double) * prm->n_sweeps, hipMemcpyHostToDevice,
                               stream));
         RP_HIP(hipMemsetAsync(bar, 0, 2 * sizeof(unsigned), stream));
+        RP_HIP(hipMemsetAsync(bar_flags, 0, sizeof(unsigned) * n_flags, stream));
         RP_HIP(hipMemsetAsync(flags, 0, 2 * sizeof(unsigned) * (size_t)pop_size, stream));
         RP_TRY(launch_resample_words(a.seed, prm->sweep_offset, prm->n_sweeps, vwords, stream));
         run.vwords = vwords;
@@ -1314,6 +1317,7 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
         run.xstar = best_layout;
         run.xscore = best_score;
         run.bar = bar;
+        run.flags = bar_flags;
         run.err = reinterpret_cast<int32_t *>(bar + 1);
         run.slab_of_out = slab_final;
         run.energy = energy_d;
