@@ -821,6 +821,8 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
     // Loads of one move: lane (half, hl) reads its layers of row-shard ha
     // (half 0) or hb (half 1), the q row that leaves that row-shard (qx) and
     // the one that enters it (qy), so every lane's new row is wr - qx + qy.
+    // 1 / (max(|e_cur|, 1) temp), for the bracket of the accept test
+    double inv_dt = 1.0 / ((fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0) * temp);
     // A relocation moves no sample back: its missing row is the zero row.
     // Rows are chunk-major ([P/4][L][4]): chunk x of layer ll is int4 x * L + ll.
     // Entry v * PV / 4 + x of wr, qx, qy is chunk x of the lane's layer v.
@@ -1077,21 +1079,22 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
             bool accept = lex_less(n0, n1, n2, s0, s1, s2);
             if (!accept && !(e_new > e_cur)) accept = true;  // delta <= 0 (the divisor is >= 1)
             if (!accept) {
-                const double den = fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0;
-                const double delta = (e_new - e_cur) / den;
-                if (!(delta > 0.0)) {
-                    accept = true;  // z = 0 and exp(0) = 1 > u
-                } else {
-                    const double z = delta / temp;
-                    const double u = (double)fw7 * (1.0 / 4294967296.0);
-                    // u < exp_det(-z), decided without the series when u is
-                    // clear of the bracket 1 - z <= exp(-z) <= 1 - z + z^2/2
-                    // (z >= 0); the 2^-40 margins exceed every rounding error
-                    // of the bounds and of exp_det (a few ulp).
-                    const double omz = 1.0 - z;
-                    if (z < 0.5 && u < omz * (1.0 - 0x1p-40)) accept = true;
-                    else if (z < 0.5 && u >= (omz + (0.5 * z) * z) * (1.0 + 0x1p-40)) accept = false;
-                    else accept = u < exp_det(-z);
+                // u < exp_det(-z) for z = (e_new - e_cur) / den / temp > 0,
+                // decided from single-precision exp2 when u is clear of it by
+                // 1e-5: z here is off by a few 2^-53, its conversion and the
+                // product by 2^-23 (below 7e-6 of the result for z < 30; beyond,
+                // exp(-z) is below 2^-43 and u is 0 or at least 2^-32), exp2 by
+                // an ulp.  Only the rest take the divisions and the series.
+                const double u = (double)fw7 * (1.0 / 4294967296.0);
+                const float ef = __builtin_amdgcn_exp2f(-1.44269504f * (float)((e_new - e_cur) * inv_dt));
+                const double ed = (double)ef;
+                if (u < ed * (1.0 - 1e-5)) {
+                    accept = true;
+                } else if (!(u > ed * (1.0 + 1e-5) + 1e-37)) {
+                    const double den = fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0;
+                    const double delta = (e_new - e_cur) / den;
+                    const double z = (delta > 0.0 ? delta : 0.0) / temp;
+                    accept = u < exp_det(-z);  // (z = 0: exp(0) = 1 > u)
                 }
             }
             if (!accept) {
@@ -1245,6 +1248,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                     for (int32_t x = lane; x < N; x += kWave) bl[x] = cell_of<CG>(M, x);
             }
         }
+            inv_dt = 1.0 / ((fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0) * temp);
     }
     R.Jr = Jr;
     R.Ar = Ar;
