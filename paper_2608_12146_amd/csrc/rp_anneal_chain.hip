@@ -707,14 +707,24 @@ __device__ inline void member_load(const AnnealArgs &a, const Lds &M, const Tabl
         const int32_t cnt = tb.hcnt[h];
         int64_t acc = 0;
         int64_t *cp = M.Cp + h * (a.dv + 1);
-        for (int32_t x = 0; x < a.dv; ++x) {
-            if (x < cnt) {
+        // (a batch of loads before its sums and stores: with HQ, Q comes from
+        // and the prefixes go to memory, and one cell at a time took 32 trips
+        // there, 25 us of a member's level in the largest window)
+        constexpr int U = HQ ? 16 : 8;
+        for (int32_t x0 = 0; x0 < a.dv; x0 += U) {
+            int64_t t[U], q[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t x = x0 + u < cnt ? x0 + u : cnt - 1;
                 const int32_t c = HQ && G == 1 ? h * a.D + x : tb.hcell[h * a.dv + x];
-                const int64_t t = M.T[c], q = M.Q[c];
-                for (int s = 0; s < a.S; ++s) acc += a.alpha[s] * t + a.beta[s] * q;
-                cp[x] = acc;
-            } else {
-                cp[x] = kInf;
+                t[u] = M.T[c];
+                q[u] = M.Q[c];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (x0 + u >= a.dv) break;
+                for (int s = 0; s < a.S; ++s) acc += x0 + u < cnt ? a.alpha[s] * t[u] + a.beta[s] * q[u] : 0;
+                cp[x0 + u] = x0 + u < cnt ? acc : kInf;
             }
         }
         M.Ctot[h] = acc;
@@ -811,6 +821,8 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
     }
     int64_t n_acc = 0, n_eval = 0;
     double e_cur = GV == 1 ? energy_pow2(a, s0, s1, s2) : energy_k(a, s0, s1, s2);
+    // 1 / (max(|e_cur|, 1) temp), for the bracket of the accept test
+    double inv_dt = 1.0 / ((fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0) * temp);
     const int half = lane >> 5, hl = lane & 31;
     // cells of a row-shard: lane (half, x) holds its x-th slot, x < 16 (all
     // 32 lanes of the half with up to 32 slots)
@@ -821,8 +833,6 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
     // Loads of one move: lane (half, hl) reads its layers of row-shard ha
     // (half 0) or hb (half 1), the q row that leaves that row-shard (qx) and
     // the one that enters it (qy), so every lane's new row is wr - qx + qy.
-    // 1 / (max(|e_cur|, 1) temp), for the bracket of the accept test
-    double inv_dt = 1.0 / ((fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0) * temp);
     // A relocation moves no sample back: its missing row is the zero row.
     // Rows are chunk-major ([P/4][L][4]): chunk x of layer ll is int4 x * L + ll.
     // Entry v * PV / 4 + x of wr, qx, qy is chunk x of the lane's layer v.
@@ -1238,6 +1248,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
             s1 = n1;
             s2 = n2;
             e_cur = e_new;
+            inv_dt = 1.0 / ((fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0) * temp);
             wsync();
             if (lex_less(s0, s1, s2, b0, b1, b2)) {
                 b0 = s0;
@@ -1248,7 +1259,6 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                     for (int32_t x = lane; x < N; x += kWave) bl[x] = cell_of<CG>(M, x);
             }
         }
-            inv_dt = 1.0 / ((fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0) * temp);
     }
     R.Jr = Jr;
     R.Ar = Ar;
