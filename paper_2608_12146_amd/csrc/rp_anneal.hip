@@ -1017,12 +1017,14 @@ static unsigned wait_spin_limit() {
     return x < 32 ? 32u : (x > (1ul << 30) ? (1u << 30) : (unsigned)x);
 }
 
-static SlabOffsets slab_layout(int64_t N, int64_t B, int64_t RG, int64_t LP) {
+// pool_places: N, or with `counts` (the chain kernel of 64 ranks) the places
+// of a pool with room; start then also holds the member counts and one word.
+static SlabOffsets slab_layout(int64_t N, int64_t B, int64_t RG, int64_t LP, int64_t pool_places, bool counts) {
     SlabOffsets o;
     int64_t p = 0;
     o.cell = p; p = align_up(p + 4 * N);
-    o.pool = p; p = align_up(p + 4 * N);
-    o.start = p; p = align_up(p + 4 * (B + 1));
+    o.pool = p; p = align_up(p + 4 * pool_places);
+    o.start = p; p = align_up(p + 4 * (counts ? 2 * B + 2 : B + 1));
     o.T = p; p = align_up(p + 8 * B);
     o.Q = p; p = align_up(p + 8 * B);
     o.W = p; p = align_up(p + 4 * RG * LP);
@@ -1071,8 +1073,6 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
     Scratch scr(stream);
     DeviceProblem dp;
     RP_TRY(upload_problem(prob, topo, scr, &dp, stream));
-    const SlabOffsets off = slab_layout(N, B64, RG64, LP64);
-    char *slabA = scr.get<char>((size_t)pop_size * off.bytes);
     int32_t *best = scr.get<int32_t>((size_t)pop_size * N);
     int64_t *results = scr.get<int64_t>((size_t)pop_size * kRes);
     int32_t *status = scr.get<int32_t>(pop_size + 1);
@@ -1107,7 +1107,6 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
     a.slots = dp.slots; a.count = dp.count; a.slot_shard = dp.slot_shard;
     a.qzero = qzero;
     a.sum32 = (long double)L * (long double)w_entry_bound(prob, ws) < 2147483648.0L ? 1 : 0;
-    a.off = off;
     a.best = best; a.results = results;
     a.seed = prm->seed; a.p_guide = prm->p_guide_u32; a.rho = prm->rho_u32;
 
@@ -1140,6 +1139,12 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
         run_rc = chain_run(a, run, chain_pv, chain_dv, n_cu, false, stream);
     const bool whole = run_rc == ROUTEPACK_OK;
     const bool chain = chain_fits && !whole && want_chain;
+
+    const bool room = chain && a.hq;
+    const SlabOffsets off = slab_layout(N, B64, RG64, LP64, room ? a.pool_cap : N, room);
+    char *slabA = scr.get<char>((size_t)pop_size * off.bytes);
+    if (scr.failed()) return ROUTEPACK_E_DEVICE;
+    a.off = off;
 
     // Build member slabs from the population (each distinct layout once) and
     // validate them.
@@ -1378,6 +1383,7 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
         if (!ev.empty()) RP_HIP(hipEventRecord(ev[2 * n], stream));
         if (fast) {
             a.slab_of = slab_of[cur];
+            a.fresh = n == 0 ? 1 : 0;
             if (chain) RP_TRY(launch_anneal_chain(a, chain_pv, chain_dv, stream));
             else RP_TRY(launch_anneal_wave(a, tlds, stream));
         } else {

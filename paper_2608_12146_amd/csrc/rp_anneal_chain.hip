@@ -73,7 +73,10 @@ __device__ inline int64_t row_head_max64(int64_t v) {
 struct Lds {
     uint16_t *cell, *pool, *start;
     int32_t *gcell;  // the cell array in the member's slab instead (CG layout)
-    int32_t *gpool;  // the pool in the member's slab instead (64 ranks)
+    // 64 ranks: the pool in the member's slab, cells where `start` says with
+    // cnt members each, not packed (see pool_rebuild)
+    int32_t *gpool;
+    uint16_t *cnt;
     int32_t *T;
     int64_t *Q;
     // [RG][DV + 1] prefix of the cell costs of each row-shard, slot order;
@@ -226,7 +229,7 @@ __device__ inline Screen screen(const AnnealArgs &a, const Lds &M, const Tables 
         vb[x] = M.Vpre[8 * k4 + x];
     }
     int32_t uT1 = M.T[uc1], uT2 = M.T[uc2];
-    int32_t us0 = M.start[uc1], us1 = M.start[uc1 + 1];
+    int32_t us0 = HP ? 0 : M.start[uc1], us1 = HP ? M.cnt[uc1] : M.start[uc1 + 1];
     stage_end(jb[0], jb[1], jb[2], jb[3], jb[4], jb[5], jb[6], jb[7], vb[0], vb[1], vb[2], vb[3], vb[4], vb[5],
               vb[6], vb[7], uT1, uT2, us0, us1);
     int32_t h1 = 8 * k1, h4 = 8 * k4;
@@ -279,12 +282,17 @@ __device__ inline Screen screen(const AnnealArgs &a, const Lds &M, const Tables 
         gc2 = clamp0(gc2, B - 1);
     }
     // stage 4: member ranges and loads of both cells
-    int32_t st1 = M.start[gc1], en1 = M.start[gc1 + 1];
-    int32_t st2 = M.start[gc2], en2 = M.start[gc2 + 1];
+    int32_t st1 = M.start[gc1], en1 = HP ? M.cnt[gc1] : M.start[gc1 + 1];
+    int32_t st2 = M.start[gc2], en2 = HP ? M.cnt[gc2] : M.start[gc2 + 1];
     int32_t gT1 = M.T[gc1], gT2 = M.T[gc2];
     stage_end(st1, en1, st2, en2, gT1, gT2);
-    const int32_t pi = clamp0(st1 + (int32_t)bounded_small(w3, (uint32_t)(en1 - st1)), N - 1);
-    const int32_t pj = clamp0(st2 + (int32_t)bounded_small(w6, (uint32_t)(en2 - st2)), N - 1);
+    if constexpr (HP) {
+        en1 += st1;
+        en2 += st2;
+    }
+    const int32_t last = HP ? a.pool_cap - 1 : N - 1;
+    const int32_t pi = clamp0(st1 + (int32_t)bounded_small(w3, (uint32_t)(en1 - st1)), last);
+    const int32_t pj = clamp0(st2 + (int32_t)bounded_small(w6, (uint32_t)(en2 - st2)), last);
     // stage 5: the samples; stage 6: their lengths
     int32_t gi = HP ? M.gpool[pi] : M.pool[pi], gj = HP ? M.gpool[pj] : M.pool[pj];
     stage_end(gi, gj);
@@ -299,10 +307,10 @@ __device__ inline Screen screen(const AnnealArgs &a, const Lds &M, const Tables 
         sz1 = en1 - st1;
         i = gi;
         ti = gti;
-        sc.pos_i = pi;
+        sc.pos_i = HP ? pi - st1 : pi;  // (64 ranks: in its cell, which may move)
         j = reloc ? -1 : gj;
         tj = reloc ? 0 : gtj;
-        sc.pos_j = reloc ? -1 : pj;
+        sc.pos_j = reloc ? -1 : (HP ? pj - st2 : pj);
     } else {
         c1 = uc1;
         c2 = uc2;
@@ -424,8 +432,7 @@ __device__ inline int32_t count_less_g(const int32_t *pool, int32_t lo, int32_t 
 // pool_move on an int32 pool in global memory (64 ranks): each batch loads
 // all of its entries before it stores any, and the batches walk in the
 // direction of the shift, so no load reads an entry an earlier batch wrote.
-// A batch is 2048 entries (32 per lane): a relocation across the pool of the
-// largest window shifts up to 32768 entries, one memory round trip a batch.
+// A batch is 2048 entries (32 per lane).
 __device__ inline void pool_move_g(int32_t *pool, int32_t from, int32_t to, int32_t v) {
     const int lane = lane_id();
     constexpr int U = 32;
@@ -489,6 +496,82 @@ __device__ inline void start_add(uint16_t *start16, int32_t lo, int32_t hi, int3
     }
 }
 
+// The pool of 64 ranks (in the slab).  A relocation grows one cell and
+// shrinks another; in a packed pool every member between the two moves, a
+// third of 32768 samples on average, through memory.  Here a shrinking cell
+// closes up where it is, and a growing one moves to a block of its own in the
+// spare room past the packed pool, whose size is rounded up to 8 so that it
+// seldom moves again: a relocation touches its two cells only.  Blocks are
+// cut from the room in order (R.bump is the next; 0: the pool is packed, in
+// cell order), and when it runs out the pool is packed again from the cells
+// of the samples.  20 levels of the largest window, with a workgroup per
+// member (chain_plan), by seed: 31-49 ms packed, 26-35 ms with the room.
+// One wave; ends packed, with the counts as they were.
+//
+// Samples 64 at a time in id order, each to the next place of its cell
+// (M.start holds those places meanwhile, M.cnt who came last to a cell):
+// lanes whose cell another lane of the 64 shares are placed one cell at a
+// time, by their order in the wave.
+__device__ inline void pool_rebuild(const AnnealArgs &a, const Lds &M) {
+    const int lane = lane_id();
+    const int32_t N = a.N, B = a.B;
+    wsync();
+    int32_t carry = 0;
+    for (int32_t b = 0; b < B; b += kWave) {
+        const int32_t c = b + lane, n = c < B ? M.cnt[c] : 0;
+        const int32_t incl = (int32_t)wave_incl_scan((int64_t)n);
+        if (c < B) M.start[c] = (uint16_t)(carry + incl - n);
+        carry += __builtin_amdgcn_readlane(incl, kWave - 1);
+    }
+    wsync();
+    constexpr int U = 16;
+    for (int32_t b = 0; b < N; b += U * kWave) {
+        int32_t cl[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int32_t i = b + u * kWave + lane;
+            cl[u] = i < N ? clamp0(M.gcell[i], B - 1) : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int32_t i = b + u * kWave + lane, c = cl[u];
+            if (c >= 0) M.cnt[c] = (uint16_t)lane;
+            wsync();
+            int32_t pos = c >= 0 ? M.start[c] : 0;
+            int32_t next = pos + 1;
+            bool last = c >= 0;  // the lane that leaves its cell's next place
+            uint64_t lost = __ballot(c >= 0 && M.cnt[c >= 0 ? c : 0] != lane);
+            while (lost) {
+                const int32_t cs = __builtin_amdgcn_readlane(c, first_lane(lost));
+                const uint64_t same = __ballot(c == cs);
+                if (c == cs) {
+                    pos += __popcll(same & ((1ull << lane) - 1));
+                    next = pos + 1;
+                    last = (same >> lane) == 1;
+                }
+                lost &= ~same;
+            }
+            if (c >= 0) M.gpool[clamp0(pos, a.pool_cap - 1)] = i;
+            wsync();
+            if (last) M.start[c] = (uint16_t)next;
+            wsync();
+        }
+    }
+    // places after the last member -> counts and starts
+    int32_t prev = 0;
+    for (int32_t b = 0; b < B; b += kWave) {
+        const int32_t c = b + lane, e = c < B ? M.start[c] : 0;
+        const int32_t up = __builtin_amdgcn_ds_bpermute(((lane + kWave - 1) & (kWave - 1)) * 4, e);
+        const int32_t s = lane == 0 ? prev : up;
+        prev = __builtin_amdgcn_readlane(e, kWave - 1);
+        if (c < B) {
+            M.start[c] = (uint16_t)s;
+            M.cnt[c] = (uint16_t)(e - s);
+        }
+    }
+    wsync();
+}
+
 // Prefixes of the roulette weights into LDS from J_pre (lane h holds
 // J_pre[h], and J_pre[h + 64] in Jp2 when RV == 2): J_pre and
 // V_h = (h + 1)(s2 + 1) - J_pre[h], with their pivot entries 8k+7; entries at
@@ -548,6 +631,7 @@ __device__ inline int64_t row_entry(int64_t v, int64_t v2, int32_t h) {
 struct Regs {
     int64_t Jr, Ar, Ur, s0, s1, s2;
     int64_t Jr2, Ar2;  // row-shards 64..127 (more than 64 row-shards only)
+    int32_t bump;      // 64 ranks: see pool_rebuild
 };
 
 // Member slab sections in HBM.
@@ -623,6 +707,7 @@ __device__ inline Lds member_lds(const AnnealArgs &a, char *smem, int wv) {
     Lds M;
     M.cell = reinterpret_cast<uint16_t *>(mine + a.o_cell);
     M.pool = reinterpret_cast<uint16_t *>(mine + a.o_pool);
+    M.cnt = M.pool;  // (64 ranks: the pool is in the slab)
     M.start = reinterpret_cast<uint16_t *>(mine + a.o_start);
     M.T = reinterpret_cast<int32_t *>(mine + a.o_T);
     M.Q = reinterpret_cast<int64_t *>(mine + a.o_Q);
@@ -675,12 +760,13 @@ __device__ inline void member_load(const AnnealArgs &a, const Lds &M, const Tabl
         }
     }
     for (int32_t base = 0; base <= B; base += U * kWave) {
-        int32_t sv[U];
+        int32_t sv[U], nv[U];
         int64_t tv[U], qv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int32_t x = base + u * kWave + lane;
             if (x <= B) sv[u] = g.start[x];
+            if (HQ && x < B) nv[u] = a.fresh ? g.start[x + 1] - sv[u] : g.start[B + 1 + x];
             if (x < B) {
                 tv[u] = g.T[x];
                 if (!HQ) qv[u] = g.Q[x];  // (HQ: Q is used in place in the slab)
@@ -690,12 +776,14 @@ __device__ inline void member_load(const AnnealArgs &a, const Lds &M, const Tabl
         for (int u = 0; u < U; ++u) {
             const int32_t x = base + u * kWave + lane;
             if (x <= B) M.start[x] = (uint16_t)sv[u];
+            if (HQ && x < B) M.cnt[x] = (uint16_t)nv[u];
             if (x < B) {
                 M.T[x] = (int32_t)tv[u];
                 if (!HQ) M.Q[x] = qv[u];
             }
         }
     }
+    R.bump = HQ && !a.fresh ? __builtin_amdgcn_readfirstlane(g.start[2 * B + 1]) : 0;
     const int32_t h2 = lane + kWave;  // the lane's second row-shard (more than 64 only)
     R.Jr = lane < RG ? g.J[lane] : 0;
     R.Ar = lane < RG ? g.A[lane] : 0;
@@ -770,6 +858,10 @@ __device__ inline void member_store(const AnnealArgs &a, const Lds &M, const Sla
         }
     }
     for (int32_t x = lane; x <= B; x += kWave) g.start[x] = M.start[x];
+    if constexpr (HQ) {
+        for (int32_t x = lane; x < B; x += kWave) g.start[B + 1 + x] = M.cnt[x];
+        if (lane == 0) g.start[2 * B + 1] = R.bump;
+    }
     for (int32_t x = lane; x < B; x += kWave) {
         g.T[x] = M.T[x];
         if (!HQ) g.Q[x] = M.Q[x];
@@ -802,6 +894,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                                         uint8_t *log_arg, int64_t *res, int64_t *trace_row, Regs &R) {
     constexpr int RV = GV == 2 ? 2 : 1;
     constexpr bool HP = PV == 64;  // (64 ranks: the pool is in the slab)
+    int32_t bump = HP ? R.bump : 0;
     uint8_t *const log = GV == 1 ? nullptr : log_arg;  // (the common shape is launched without a step log)
     const int lane = lane_id();
     const int32_t N = a.N, B = a.B, RG = a.RG, D = a.D, G = GV == 1 ? 1 : a.G, L = a.L;
@@ -819,6 +912,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
         for (int32_t x = lane; x < N; x += kWave) bl[x] = cell_of<CG>(M, x);
         best_is_start = 0;
     }
+    const int32_t last = HP ? a.pool_cap - 1 : N - 1;  // last place of the pool
     int64_t n_acc = 0, n_eval = 0;
     double e_cur = GV == 1 ? energy_pow2(a, s0, s1, s2) : energy_k(a, s0, s1, s2);
     // 1 / (max(|e_cur|, 1) temp), for the bracket of the accept test
@@ -961,8 +1055,8 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                 stage_end(cnt, cc);
             }
             const bool cact = cell_lane && cx < cnt && (half == 0 || two);
-            int32_t st1 = M.start[c1], en1 = M.start[c1 + 1];
-            int32_t st2 = M.start[c2], en2 = M.start[c2 + 1];
+            int32_t st1 = M.start[c1], en1 = HP ? M.cnt[c1] : M.start[c1 + 1];
+            int32_t st2 = M.start[c2], en2 = HP ? M.cnt[c2] : M.start[c2 + 1];
             int64_t Tc = 0, Qc = 0;
             if (cact) {
                 Tc = M.T[cc];
@@ -970,6 +1064,10 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
             }
             int64_t T1 = M.T[c1], T2 = M.T[c2], Q1 = M.Q[c1], Q2v = M.Q[c2];
             stage_end(st1, en1, st2, en2, Tc, Qc, T1, T2, Q1, Q2v);
+            if constexpr (HP) {
+                en1 += st1;
+                en2 += st2;
+            }
             const int32_t sz1 = en1 - st1, sz2 = en2 - st2;
             const bool small = sz1 <= 32 && sz2 <= 32;
             int32_t y = -1;
@@ -1150,12 +1248,14 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                         else pool_move(M.pool, from, to, (uint32_t)v);
                     };
                     if (pos_i < 0) pos_i = st1 + cl(st1, en1, i, -1);
+                    else if (HP) pos_i += st1;
                     if (pos_j < 0) pos_j = st2 + cl(st2, en2, j, -1);
+                    else if (HP) pos_j += st2;
                     const int32_t to1 = st1 + cl(st1, en1, j, i);
                     const int32_t to2 = st2 + cl(st2, en2, i, j);
                     wsync();
-                    mv(clamp0(pos_i, N - 1), clamp0(to1, N - 1), j);
-                    mv(clamp0(pos_j, N - 1), clamp0(to2, N - 1), i);
+                    mv(clamp0(pos_i, last), clamp0(to1, last), j);
+                    mv(clamp0(pos_j, last), clamp0(to2, last), i);
                 }
             } else {
                 int32_t rk;
@@ -1163,18 +1263,71 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                     const uint64_t b1 = __ballot(yv && half == 0 && y < i);
                     const uint64_t b2 = __ballot(yv && half == 1 && y < i);
                     if (pos_i < 0) pos_i = st1 + __popcll(b1);
+                    else if (HP) pos_i += st1;
                     rk = __popcll(b2);
                 } else {
                     if (pos_i < 0)
                         pos_i = st1 + (HP ? count_less_g(M.gpool, st1, en1, i, -1) : count_less(M.pool, st1, en1, i, -1));
+                    else if (HP)
+                        pos_i += st1;
                     rk = HP ? count_less_g(M.gpool, st2, en2, i, -1) : count_less(M.pool, st2, en2, i, -1);
                 }
-                const int32_t to = c1 < c2 ? st2 - 1 + rk : st2 + rk;
-                wsync();
-                if constexpr (HP) pool_move_g(M.gpool, clamp0(pos_i, N - 1), clamp0(to, N - 1), i);
-                else pool_move(M.pool, clamp0(pos_i, N - 1), clamp0(to, N - 1), (uint32_t)i);
-                if (c1 < c2) start_add(M.start, c1, c2, -1);
-                else start_add(M.start, c2, c1, 1);
+                if constexpr (HP) {
+                    // the block that the growing cell goes to (see pool_rebuild)
+                    int32_t dst = st2, blk = 0;
+                    if (st2 < a.pool_ovf || (sz2 & 7) == 0) {
+                        blk = (sz2 + 8) & ~7;
+                        dst = bump ? bump : a.pool_ovf;
+                        if (dst + blk > a.pool_cap && bump) {
+                            pool_rebuild(a, M);
+                            pos_i -= st1;
+                            st1 = M.start[c1];
+                            st2 = M.start[c2];
+                            pos_i += st1;
+                            bump = 0;
+                            dst = a.pool_ovf;
+                        }
+                    }
+                    wsync();
+                    if (dst + blk > a.pool_cap) {
+                        // no room for it in a packed pool: every member between moves
+                        const int32_t to = c1 < c2 ? st2 - 1 + rk : st2 + rk;
+                        pool_move_g(M.gpool, clamp0(pos_i, last), clamp0(to, last), i);
+                        if (c1 < c2) start_add(M.start, c1, c2, -1);
+                        else start_add(M.start, c2, c1, 1);
+                    } else {
+                        bump = blk ? dst + blk : bump;
+                        if (small) {
+                            // half 0: c1's members above i; half 1: c2's (all of
+                            // them to a new block, else those above i)
+                            if (yv && half == 0 && y > i) M.gpool[st1 + hl - 1] = y;
+                            if (yv && half == 1 && (blk || y > i)) M.gpool[dst + hl + (y > i ? 1 : 0)] = y;
+                            if (lane == 0) M.gpool[dst + rk] = i;
+                        } else {
+                            pool_move_g(M.gpool, clamp0(pos_i, last), clamp0(st1 + sz1 - 1, last), i);
+                            if (blk) {
+                                for (int32_t x = lane; x < sz2; x += kWave) {
+                                    const int32_t v = M.gpool[st2 + x];
+                                    M.gpool[dst + x + (v > i ? 1 : 0)] = v;
+                                }
+                                if (lane == 0) M.gpool[dst + rk] = i;
+                            } else {
+                                pool_move_g(M.gpool, st2 + sz2, st2 + rk, i);
+                            }
+                        }
+                        if (blk && lane == 0) M.start[c2] = (uint16_t)dst;
+                    }
+                    if (lane == 0) {
+                        M.cnt[c1] = (uint16_t)(sz1 - 1);
+                        M.cnt[c2] = (uint16_t)(sz2 + 1);
+                    }
+                } else {
+                    const int32_t to = c1 < c2 ? st2 - 1 + rk : st2 + rk;
+                    wsync();
+                    pool_move(M.pool, clamp0(pos_i, last), clamp0(to, last), (uint32_t)i);
+                    if (c1 < c2) start_add(M.start, c1, c2, -1);
+                    else start_add(M.start, c2, c1, 1);
+                }
             }
             if (lane == 0) {
                 if constexpr (CG) {
@@ -1222,7 +1375,8 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                 // one of its picks.  A pick keeps its row-shard when it lies
                 // in the interval after the move's J deltas; V_pre moves by
                 // (h + 1)(n2 - s2) besides.  A relocation shifts the members
-                // of the cells strictly between its two cells by one place.
+                // of the cells strictly between its two cells by one place
+                // (64 ranks: places count from the cell's own start).
                 const int64_t ds2 = n2 - s2;
                 sc.jlo += shift(sc.h1 - 1);
                 sc.jhi += shift(sc.h1);
@@ -1235,7 +1389,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                     keep = keep && sc.h1 != ha && sc.h1 != hb && (uint64_t)sc.jlo <= pk1 &&
                            pk1 < (uint64_t)sc.jhi && (uint64_t)sc.vlo <= pk4 && pk4 < (uint64_t)sc.vhi;
                 }
-                if (reloc) {
+                if (!HP && reloc) {
                     const int32_t lo = c1 < c2 ? c1 : c2, hi = c1 < c2 ? c2 : c1, d = c1 < c2 ? -1 : 1;
                     if (sc.pos_i >= 0 && sc.c1 > lo && sc.c1 < hi) sc.pos_i += d;
                     if (sc.pos_j >= 0 && sc.c2 > lo && sc.c2 < hi) sc.pos_j += d;
@@ -1267,6 +1421,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
         R.Ar2 = Ar2;
     }
     R.Ur = Ur;
+    R.bump = bump;
     R.s0 = s0;
     R.s1 = s1;
     R.s2 = s2;
@@ -1977,7 +2132,7 @@ bool chain_plan(AnnealArgs &a, int32_t n_cu, int32_t max_count, int32_t *pv_out,
     auto layout = [&](bool cg, int64_t *shared_out) -> int64_t {
         int64_t o = 0;
         a.o_cell = (int32_t)o; o = up16(o + (cg ? 0 : 2 * (int64_t)a.N));
-        a.o_pool = (int32_t)o; o = up16(o + (hq && cg ? 0 : 2 * up8e(a.N)));
+        a.o_pool = (int32_t)o; o = up16(o + 2 * up8e(hq ? a.B : a.N));  // (hq: member counts)
         a.o_start = (int32_t)o; o = up16(o + 2 * up8e((int64_t)a.B + 1));
         a.o_T = (int32_t)o; o = up16(o + 4 * (int64_t)a.B);
         a.o_Q = (int32_t)o; o = up16(o + (hq ? 0 : 8 * (int64_t)a.B));
@@ -2019,9 +2174,23 @@ bool chain_plan(AnnealArgs &a, int32_t n_cu, int32_t max_count, int32_t *pv_out,
         }
     }
     if (cap < 1 || (P == 64 && !a.cg)) return false;
-    a.mpw = (int32_t)(want < cap ? want : cap);
+    want = want < cap ? want : cap;
+    // HBM layout: a workgroup per member where as many fit a CU as waves
+    // would (its shared tables are small), so that a member with few moves to
+    // evaluate makes room for the next one at once.
+    a.mpw = (int32_t)(a.cg && lim / (shared + member) >= want ? 1 : want);
     a.lds_shared = (int32_t)shared;
     a.lds_member = (int32_t)member;
+    // Room past a packed pool for cells that grow (64 ranks, see
+    // pool_rebuild): a quarter of the pool, packed again after that many
+    // places, as far as 16-bit starts reach; past 61000 samples that would be
+    // so little that it is left out (every relocation shifts the packed pool).
+    a.pool_ovf = (a.N + 7) & ~7;
+    a.pool_cap = a.pool_ovf;
+    if (hq) {
+        const int32_t room = (a.N / 4 < 65528 - a.pool_ovf ? a.N / 4 : 65528 - a.pool_ovf) & ~7;
+        if (room >= a.N / 16) a.pool_cap += room;
+    }
     *pv_out = P;
     *dv_out = dv;
     return true;

@@ -212,6 +212,33 @@ def test_anneal_start_state(P, L, shards):
 
 
 @gpu
+@pytest.mark.parametrize("N,D,R,shards", [(200, 4, 2, 1), (203, 2, 2, 1), (600, 4, 2, 1), (900, 4, 7, 2), (37, 4, 3, 1)])
+def test_anneal_pool_room(N, D, R, shards):
+    """64 ranks: the pool's spare room under hot levels of relocations --
+    blocks that fit and grow in place, the room running out and the pool
+    packed again, cells above and below 32 members, blocks larger than the
+    room (cells of a quarter of the samples) and no room at all."""
+    import oracle as O
+    import paper_2608_12146_amd as rp
+    _log(f"pool room N={N} D={D} R={R} shards={shards}")
+    rng = np.random.default_rng([20, N, D])
+    t = rng.integers(1, 60, size=N)
+    t, q, kw = _pack_case(N, D, shards, int(-(-t.sum() // (R * D)) * 1.6) + 60, t, L=33, P=64)
+    kw["min_rows"] = R
+    pb, prob = O.Problem.from_dict(kw), rp.Problem.from_dict(kw)
+    pk = O.pack_rows(pb, t, q, 3, 8, 4, 12)
+    assert pk["rc"] == 0
+    temps = np.array([3.0, 1.0, 0.1, 1e-2, 1e-3, 1e-4])
+    o = O.anneal(pb, t, q, pk["r_star"], pk["population"], temps, 200, 9)
+    g = rp.anneal(prob, t, q, pk["r_star"], pk["population"], temps, 200, 9)
+    assert g["level_kernel"] == "chain"
+    assert o["trace"][..., 6].sum() > 100 * 12  # accepted moves
+    assert np.array_equal(g["trace"].cpu().numpy(), o["trace"])
+    assert np.array_equal(g["population"].cpu().numpy(), o["population"])
+    assert np.array_equal(g["best_layout"].cpu().numpy(), o["best_layout"])
+
+
+@gpu
 @pytest.mark.parametrize("K,N,fill", [(1, 3, 0.5), (64, 64, 0.9), (65, 200, 0.99), (128, 129, 1.0), (300, 900, 0.97),
                                       (4096, 4500, 0.9), (4097, 4300, 0.9)])
 @pytest.mark.parametrize("scale", [1, 1 << 23])
