@@ -740,15 +740,24 @@ struct LevelEndArgs {
     int32_t *slab_next;       // [pop]
     int32_t *copy_src, *copy_dst, *n_copies;  // [pop], [pop], [1]
     int32_t stage_lds;        // hand-over bookkeeping in dynamic LDS (3 pop int32)
+    uint64_t *fbuf;           // [pop] energies, then the weights' prefix, when not in LDS
 };
 
 // After a level: the incumbent update (strict lexicographic improvement,
 // ascending member order), the trace, and systematic resampling of the
-// terminal states with quantised Boltzmann weights.  One workgroup.
+// terminal states with quantised Boltzmann weights.  One workgroup, bound by
+// its double-precision arithmetic: each member's energy (three divisions) and
+// weight are formed once and kept (F), not again for the minimum, the sum and
+// every member's search (populations of 2048 and 4096: 41 -> 25 and
+// 79 -> 39 us).
+template <bool FLDS>
 __global__ void __launch_bounds__(1024) k_level_end(LevelEndArgs a) {
-    extern __shared__ int32_t lend_par[];  // [3 pop] when a.stage_lds: parents, flags, freed slabs
+    // [pop] F (FLDS), then [3 pop] when a.stage_lds: parents, flags, freed slabs
+    extern __shared__ __align__(16) char lend_smem[];
+    uint64_t *F = FLDS ? reinterpret_cast<uint64_t *>(lend_smem) : a.fbuf;
+    int32_t *lend_par = reinterpret_cast<int32_t *>(lend_smem + (FLDS ? 8 * (size_t)a.pop : 0));
     __shared__ int64_t sk[16][4];
-    __shared__ uint64_t su[16];
+    __shared__ uint64_t su[16], s_v;
     __shared__ double sd[16];
     __shared__ int32_t win;
     const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
@@ -756,11 +765,30 @@ __global__ void __launch_bounds__(1024) k_level_end(LevelEndArgs a) {
     // 1. argmin over trajectory bests (lowest index on ties).
     int64_t k0 = LLONG_MAX, k1 = LLONG_MAX, k2 = LLONG_MAX, kj = LLONG_MAX;
     const int bo = a.init_mode ? 0 : 3;
+    double emin = __builtin_inf();
     for (int j = tid; j < a.pop; j += blockDim.x) {
         const int64_t *r = a.results + (int64_t)j * kRes + bo;
         if (lex_less(r[0], r[1], r[2], k0, k1, k2) ||
             (r[0] == k0 && r[1] == k1 && r[2] == k2 && j < kj)) {
             k0 = r[0]; k1 = r[1]; k2 = r[2]; kj = j;
+        }
+        if (a.resample) {
+            const int64_t *x = a.results + (int64_t)j * kRes;
+            const double e = energy(x[0], x[1], x[2], a.scale);
+            F[j] = __builtin_bit_cast(uint64_t, e);
+            emin = e < emin ? e : emin;
+        }
+    }
+    if (a.resample) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            const double o = __shfl_xor(emin, d, kWave);
+            emin = o < emin ? o : emin;
+        }
+        if (lane == 0) sd[wv] = emin;
+        if (wv == nw - 1) {  // (one wave draws the resampling offset)
+            const U64x4 blk = philox4x64_10(0, (uint64_t)(uint32_t)a.level, 0xFFFFFFFFull, 2, a.seed, 0);
+            if (lane == 0) s_v = blk.v[0] >> 32;
         }
     }
 #pragma unroll
@@ -805,8 +833,7 @@ __global__ void __launch_bounds__(1024) k_level_end(LevelEndArgs a) {
     if (a.init_mode) return;
     // 2. trace
     if (a.trace)
-        for (int j = tid; j < a.pop; j += blockDim.x)
-            for (int f = 0; f < 8; ++f) a.trace[(int64_t)j * 8 + f] = a.results[(int64_t)j * kRes + f];
+        for (int x = tid; x < 8 * a.pop; x += blockDim.x) a.trace[x] = a.results[(int64_t)(x >> 3) * kRes + (x & 7)];
     // 3. resampling
     if (!a.resample) {
         for (int j = tid; j < a.pop; j += blockDim.x) {
@@ -817,19 +844,6 @@ __global__ void __launch_bounds__(1024) k_level_end(LevelEndArgs a) {
         if (a.slab_cur && tid == 0) *a.n_copies = 0;
         return;
     }
-    double emin = __builtin_inf();
-    for (int j = tid; j < a.pop; j += blockDim.x) {
-        const int64_t *r = a.results + (int64_t)j * kRes;
-        const double e = energy(r[0], r[1], r[2], a.scale);
-        emin = e < emin ? e : emin;
-    }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        const double o = __shfl_xor(emin, d, kWave);
-        emin = o < emin ? o : emin;
-    }
-    if (lane == 0) sd[wv] = emin;
-    __syncthreads();
     emin = sd[0];
     for (int w = 1; w < nw; ++w) emin = sd[w] < emin ? sd[w] : emin;
     const double den = fabs(emin) > 1.0 ? fabs(emin) : 1.0;
@@ -839,10 +853,10 @@ __global__ void __launch_bounds__(1024) k_level_end(LevelEndArgs a) {
     const int lo = tid * per, hi = lo + per < a.pop ? lo + per : a.pop;
     uint64_t local = 0;
     for (int j = lo; j < hi; ++j) {
-        const int64_t *r = a.results + (int64_t)j * kRes;
-        const double en = (energy(r[0], r[1], r[2], a.scale) - emin) / den;
+        const double en = (__builtin_bit_cast(double, F[j]) - emin) / den;
         const double wh = exp_det(-(cfac * en));
         local += (uint64_t)floor(__builtin_ldexp(wh, 40));
+        F[j] = local;
     }
     const uint64_t incl = wave_incl_scan_u(local);
     if (lane == kWave - 1) su[wv] = incl;
@@ -851,44 +865,37 @@ __global__ void __launch_bounds__(1024) k_level_end(LevelEndArgs a) {
     for (int w = 0; w < wv; ++w) base += su[w];
     uint64_t total = 0;
     for (int w = 0; w < nw; ++w) total += su[w];
-    // F_j written to the trace-free scratch: reuse next_parent as staging is
-    // not possible (int32), so keep the prefix in the results column 9 of a
-    // private copy: recompute per lookup instead (binary search over chunks).
-    // Write F into shared per-thread boundaries and do the lookup from them.
-    __shared__ uint64_t chunk_lo[1024];
-    chunk_lo[tid] = base;
+    for (int j = lo; j < hi; ++j) F[j] += base;
+    const uint64_t V = s_v;
     __syncthreads();
-    const U64x4 blk = philox4x64_10(0, (uint64_t)(uint32_t)a.level, 0xFFFFFFFFull, 2, a.seed, 0);
-    const uint64_t V = blk.v[0] >> 32;
+    // Parent of m: the first j with F_j P 2^32 >= total (V + m 2^32), so with
+    // F_j P >= the right side over 2^32, rounded up.  A thread's members are
+    // consecutive and their parents do not decrease: a bisection for the
+    // first, then doubling steps from the one before.
     const uint64_t P = (uint64_t)a.pop;
-    for (int mm = tid; mm < a.pop; mm += blockDim.x) {
+    int from = 0;
+    for (int mm = lo; mm < hi; ++mm) {
         const unsigned __int128 rhs = (unsigned __int128)total * (V + ((uint64_t)mm << 32));
-        // F_j * P * 2^32 >= rhs, F nondecreasing: find the first chunk whose
-        // end prefix satisfies it, then scan inside the chunk.
-        int lo_t = 0, hi_t = (int)blockDim.x - 1;
-        // chunk t covers [t*per, min((t+1)*per, pop)); its end prefix is chunk_lo[t+1] (or total)
-        while (lo_t < hi_t) {
-            const int mid = (lo_t + hi_t) / 2;
-            const uint64_t endp = (mid + 1 < (int)blockDim.x) ? chunk_lo[mid + 1] : total;
-            if ((unsigned __int128)endp * P * ((uint64_t)1 << 32) >= rhs) hi_t = mid;
-            else lo_t = mid + 1;
-        }
-        uint64_t F = chunk_lo[lo_t];
-        int j = lo_t * per;
-        int jend = j + per < a.pop ? j + per : a.pop;
-        int chosen = a.pop - 1;
-        for (; j < jend; ++j) {
-            const int64_t *r = a.results + (int64_t)j * kRes;
-            const double en = (energy(r[0], r[1], r[2], a.scale) - emin) / den;
-            F += (uint64_t)floor(__builtin_ldexp(exp_det(-(cfac * en)), 40));
-            if ((unsigned __int128)F * P * ((uint64_t)1 << 32) >= rhs) {
-                chosen = j;
-                break;
+        const unsigned __int128 up = (rhs + 0xFFFFFFFFull) >> 32;
+        int l = from, h = a.pop - 1;
+        if (mm > lo) {
+            int step = 1, x = l;
+            while (x < a.pop - 1 && !((unsigned __int128)F[x] * P >= up)) {
+                l = x + 1;
+                x = x + step < a.pop - 1 ? x + step : a.pop - 1;
+                step *= 2;
             }
+            h = x;
         }
-        a.next_parent[mm] = chosen;
-        if (a.parents_out) a.parents_out[mm] = chosen;
-        if (a.stage_lds) lend_par[mm] = chosen;
+        while (l < h) {
+            const int mid = (l + h) >> 1;
+            if ((unsigned __int128)F[mid] * P >= up) h = mid;
+            else l = mid + 1;
+        }
+        from = l;
+        a.next_parent[mm] = l;
+        if (a.parents_out) a.parents_out[mm] = l;
+        if (a.stage_lds) lend_par[mm] = l;
     }
     if (!a.slab_cur) return;
     // Slab hand-over: parents are non-decreasing in m.  The first child of a
@@ -1196,12 +1203,18 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
     }
     LevelEndArgs le;
     memset(&le, 0, sizeof(le));
-    const size_t lend_lds = (size_t)12 * pop_size;
-    const bool lend_stage = lend_lds <= 112 * 1024;
-    if (lend_stage && lend_lds > 0)
-        RP_HIP(hipFuncSetAttribute((const void *)k_level_end, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)lend_lds));
-    const size_t lend_shm = lend_stage ? lend_lds : 0;
+    // Parents, flags and freed slabs of the level end in LDS, and the weights'
+    // prefix too, as far as they fit.
+    const bool lend_stage = (size_t)12 * pop_size <= 112 * 1024, lend_f = (size_t)20 * pop_size <= 144 * 1024;
+    const size_t lend_shm = lend_stage ? (size_t)(lend_f ? 20 : 12) * pop_size : 0;
+    auto *const level_end = lend_f ? k_level_end<true> : k_level_end<false>;
+    if (lend_shm > 0)
+        RP_HIP(hipFuncSetAttribute((const void *)level_end, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)lend_shm));
+    if (!lend_f) {
+        le.fbuf = scr.get<uint64_t>(pop_size);
+        if (scr.failed()) return ROUTEPACK_E_DEVICE;
+    }
     le.pop = pop_size; le.N = N; le.results = results; le.best = best;
     le.slab_bytes = off.bytes; le.off_cell = off.cell;
     le.xstar = best_layout; le.xscore = best_score;
@@ -1209,7 +1222,7 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
     if (prm->init_incumbent) {
         le.init_mode = 1;
         le.start_layouts = population;
-        hipLaunchKernelGGL(k_level_end, dim3(1), dim3(1024), lend_shm, stream, le);
+        hipLaunchKernelGGL(level_end, dim3(1), dim3(1024), lend_shm, stream, le);
         RP_HIP(hipGetLastError());
         le.init_mode = 0;
         le.start_layouts = nullptr;
@@ -1412,7 +1425,7 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
             le.copy_dst = copy_dst;
             le.n_copies = n_copies;
         }
-        hipLaunchKernelGGL(k_level_end, dim3(1), dim3(1024), lend_shm, stream, le);
+        hipLaunchKernelGGL(level_end, dim3(1), dim3(1024), lend_shm, stream, le);
         RP_HIP(hipGetLastError());
         if (fast) {
             RP_TRY(launch_copy_slabs(slabA, off.bytes, copy_src, copy_dst, n_copies, pop_size, stream));

@@ -212,6 +212,31 @@ def test_anneal_start_state(P, L, shards):
 
 
 @gpu
+@pytest.mark.parametrize("pop", [1, 3, 1023, 1025, 2050, 7372, 7373, 9557, 9558])
+def test_level_end_populations(pop, monkeypatch):
+    """Resampling after each level of the per-level kernel with one member, a
+    ragged share per thread, and the populations at which the weights' prefix
+    and the hand-over tables leave LDS."""
+    import oracle as O
+    import paper_2608_12146_amd as rp
+    _log(f"level end pop={pop}")
+    monkeypatch.setenv("ROUTEPACK_ANNEAL_KERNEL", "chain")
+    rng = np.random.default_rng([21, pop])
+    t = rng.integers(1, 60, size=24)
+    t, q, kw = _pack_case(24, 4, 1, int(-(-t.sum() // 8) * 1.6) + 60, t, L=2, P=4)
+    kw["min_rows"] = 2
+    pb, prob = O.Problem.from_dict(kw), rp.Problem.from_dict(kw)
+    pk = O.pack_rows(pb, t, q, 3, 8, 4, pop)
+    assert pk["rc"] == 0
+    temps = np.array([1e-1, 1e-2, 1e-3])
+    o = O.anneal(pb, t, q, pk["r_star"], pk["population"], temps, 8, 9, t_next=1e-4)
+    g = rp.anneal(prob, t, q, pk["r_star"], pk["population"], temps, 8, 9, t_next=1e-4)
+    assert g["level_kernel"] == "chain"
+    for k in ("parents", "trace", "population", "best_layout"):
+        assert np.array_equal(g[k].cpu().numpy(), o[k])
+
+
+@gpu
 @pytest.mark.parametrize("N,D,R,shards", [(200, 4, 2, 1), (203, 2, 2, 1), (600, 4, 2, 1), (900, 4, 7, 2), (37, 4, 3, 1)])
 def test_anneal_pool_room(N, D, R, shards):
     """64 ranks: the pool's spare room under hot levels of relocations --
