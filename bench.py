@@ -159,13 +159,16 @@ def lds_probe():
     print(json.dumps({"lds_probe_bytes": nbytes, "ms": ms, "GB/s": nbytes / ms / 1e6, "dispatches": 4}))
 
 
-def occupancy(kernel, pop):
+def occupancy(kernel, pop, ranks):
     """Launch shape of the level kernel at this population on the 256 CUs
     (1024 SIMDs): the chain kernels run one wave per member and spread the
     members over the CUs, at most four per workgroup (the member state fills
-    the LDS)."""
+    the LDS), or one with the layout that keeps the cells in HBM (windows of
+    32 and 64 ranks that run a launch per level)."""
     if kernel in ("chain_run", "chain"):
         mpw = max(1, min(4, -(-pop // 256)))  # members per workgroup
+        if kernel == "chain" and ranks >= 32:
+            mpw = 1
         wgs = -(-pop // mpw)
         per_cu = -(-wgs // 256)
         return {"workgroups": wgs, "waves_per_workgroup": mpw, "workgroups_per_cu": per_cu,
@@ -522,7 +525,7 @@ def main():
                      "kernel": "k_anneal_" + level_kernel, "avg_launch_ms": float(kms.sum()) / launches,
                      "launches": launches, "bytes_per_eval": bytes_per_eval,
                      "algorithmic_bytes_per_launch": evals * bytes_per_eval / launches,
-                     "lds": lds, "occupancy": occupancy(level_kernel, w.pop)},
+                     "lds": lds, "occupancy": occupancy(level_kernel, w.pop, w.n_ranks)},
         "cpu_baseline": cpu,
         "attempted_per_s": attempted / dt,
         "evals_per_step": evals // args.steps,
