@@ -35,6 +35,25 @@ def test_place_edges(E, P, values):
 
 
 @gpu
+@pytest.mark.parametrize("E,P", [(8190, 30), (8192, 64), (13312, 64), (13504, 32)])
+@pytest.mark.parametrize("low", [0, 50, 52])
+def test_place_many_heavy_experts(E, P, low):
+    """Loads of 2^low and up to 2^52 (2^30 with low = 0) for as many experts
+    as the LDS holds: capped at 2^50 each, 8192 of them sum to 2^63."""
+    import oracle as O
+    import paper_2608_12146_amd as rp
+    _log(f"place E={E} P={P} loads from 2^{low}")
+    rng = np.random.default_rng([22, E, low])
+    agg = rng.integers(1 << low, (1 << 52 if low else 1 << 30) + 1, size=(2, E), dtype=np.int64)
+    agg[1] = 1 << low
+    prob = rp.Problem(1, 2, E, 1, P, 1, 1, [0], 1 << 20, [4096], [1])
+    slot, load, _ = rp.place_experts(prob, agg)
+    o_slot, o_load = O.place(agg, P)
+    assert np.array_equal(slot.cpu().numpy(), o_slot)
+    assert np.array_equal(load.cpu().numpy(), o_load)
+
+
+@gpu
 @pytest.mark.parametrize("P", [1, 2, 4, 6, 8, 16, 32, 64, 128])
 @pytest.mark.parametrize("L,G,D,R,N", [(1, 1, 1, 1, 1), (1, 2, 3, 5, 40), (3, 1, 4, 17, 257), (5, 3, 7, 9, 130),
                                        (17, 2, 8, 33, 1025), (9, 1, 8, 400, 3300)])
