@@ -212,10 +212,10 @@ struct TrialArgs {
     const uint64_t *words;   // [M-2][2N+K]
     // per-block scratch
     int32_t *cellk;          // [M-1][N]
-    int32_t *Qc;             // [M-1][K][LP]
+    int32_t *Qc;             // [M-1][K][LP] (int64_t for k_pack_trials<int64_t>)
     int64_t *peak;           // [M-1][K]
     int32_t *order;          // [M-1][K]
-    int32_t *Wt;             // [M-1][RG][LP]
+    int32_t *Wt;             // [M-1][RG][LP] (as Qc)
     int64_t *base, *after, *pkv;  // [M-1][RG]
     int32_t *filled;         // [M-1][RG]
     int32_t *cell_to;        // [M-1][K]
@@ -237,6 +237,10 @@ __device__ inline bool pair_before(int64_t ia, int64_t pa, int32_t ha, int64_t i
     return ha < hb;
 }
 
+// Sum: the type of the cell sums Qc and the row-shard loads Wt; int64_t when a
+// load may reach 2^31 (the only kernel that then runs; its buffers hold
+// int64_t).
+template <typename Sum>
 __global__ void __launch_bounds__(64) k_pack_trials(TrialArgs a) {
     __shared__ int64_t sT[kMaxCells];
     __shared__ int32_t sN[kMaxCells];
@@ -244,10 +248,10 @@ __global__ void __launch_bounds__(64) k_pack_trials(TrialArgs a) {
     const int b = blockIdx.x;  // 0: x_paired; >= 1: trial b
     const int32_t N = a.N, K = a.K, RG = a.RG, LP = a.LP, L = a.L, P = a.P, G = a.G, D = a.D;
     int32_t *cellk = a.cellk + (int64_t)b * N;
-    int32_t *Qc = a.Qc + (int64_t)b * K * LP;
+    Sum *Qc = reinterpret_cast<Sum *>(a.Qc) + (int64_t)b * K * LP;
     int64_t *peak = a.peak + (int64_t)b * K;
     int32_t *order = a.order + (int64_t)b * K;
-    int32_t *Wt = a.Wt + (int64_t)b * RG * LP;
+    Sum *Wt = reinterpret_cast<Sum *>(a.Wt) + (int64_t)b * RG * LP;
     int64_t *base = a.base + (int64_t)b * RG, *after = a.after + (int64_t)b * RG, *pkv = a.pkv + (int64_t)b * RG;
     int32_t *filled = a.filled + (int64_t)b * RG;
     int32_t *cell_to = a.cell_to + (int64_t)b * K;
@@ -355,7 +359,7 @@ __global__ void __launch_bounds__(64) k_pack_trials(TrialArgs a) {
     for (int32_t k = lane; k < K; k += kWave) {
         int64_t pk = 0;
         for (int l = 0; l < L; ++l) {
-            int32_t mx = Qc[(int64_t)k * LP + l * P];
+            Sum mx = Qc[(int64_t)k * LP + l * P];
             for (int p = 1; p < P; ++p) mx = max(mx, Qc[(int64_t)k * LP + l * P + p]);
             pk += mx;
         }
@@ -379,16 +383,16 @@ __global__ void __launch_bounds__(64) k_pack_trials(TrialArgs a) {
     __syncthreads();
     for (int32_t pos = 0; pos < K; ++pos) {
         const int32_t k = order[pos];
-        const int32_t *Qk = Qc + (int64_t)k * LP;
+        const Sum *Qk = Qc + (int64_t)k * LP;
         int32_t cnt = 0;
         for (int32_t hb = 0; hb < RG; hb += kWave) {
             const int32_t h = hb + lane;
             const bool cand = h < RG && filled[h] < a.count[h % G];
             int64_t af = 0, pk = 0;
             if (cand) {
-                const int32_t *Wh = Wt + (int64_t)h * LP;
+                const Sum *Wh = Wt + (int64_t)h * LP;
                 for (int l = 0; l < L; ++l) {
-                    int32_t mx = Wh[l * P] + Qk[l * P];
+                    Sum mx = Wh[l * P] + Qk[l * P];
                     for (int p = 1; p < P; ++p) mx = max(mx, Wh[l * P + p] + Qk[l * P + p]);
                     af += mx;
                     pk = mx > pk ? mx : pk;
@@ -438,7 +442,7 @@ __global__ void __launch_bounds__(64) k_pack_trials(TrialArgs a) {
         const int32_t h = pH;
         const int32_t r = h / G, g = h % G;
         const int32_t d = a.slots[g * D + filled[h]];
-        int32_t *Wh = Wt + (int64_t)h * LP;
+        Sum *Wh = Wt + (int64_t)h * LP;
         for (int32_t e = lane; e < LP; e += kWave) Wh[e] += Qk[e];
         __syncthreads();
         if (lane == 0) {
@@ -453,9 +457,10 @@ __global__ void __launch_bounds__(64) k_pack_trials(TrialArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Seed trials in three launches for the common shapes (C < 2^31, N and K
-// below 2^16, the pairing's tables other than W within LDS); the
-// single-kernel path above covers the rest.  Same draws, same decisions.
+// Seed trials in stages for the common shapes (C < 2^31, N and K below 2^16,
+// every row-shard load below 2^31, the pairing's tables other than W within
+// LDS); the single-kernel path above covers the rest.  Same draws, same
+// decisions.
 //
 //  k_pack_fit      one wave per candidate: WindowShuffle and
 //                  RandomizedBestFit with the draws, window items and their
@@ -1771,10 +1776,13 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
     ta.K = K; ta.RG = RG; ta.LP = (int32_t)LP; ta.w = choice_width; ta.C = C;
     ta.slots = dp.slots; ta.count = dp.count; ta.words = words;
     ta.cellk = scr.get<int32_t>((size_t)nb * N);
-    ta.Qc = scr.get<int32_t>((size_t)nb * K * (LP ? LP : 1));
+    // Cell sums and row-shard loads are int32 while every load stays below 2^31.
+    const bool wide = w_entry_bound(prob, ws) > INT32_MAX;
+    const size_t per_sum = wide ? 2 : 1;
+    ta.Qc = scr.get<int32_t>(per_sum * nb * K * (LP ? LP : 1));
     ta.peak = scr.get<int64_t>((size_t)nb * K);
     ta.order = scr.get<int32_t>((size_t)nb * K);
-    ta.Wt = scr.get<int32_t>((size_t)nb * RG * (LP ? LP : 1));
+    ta.Wt = scr.get<int32_t>(per_sum * nb * RG * (LP ? LP : 1));
     ta.base = scr.get<int64_t>((size_t)nb * RG);
     ta.after = scr.get<int64_t>((size_t)nb * RG);
     ta.pkv = scr.get<int64_t>((size_t)nb * RG);
@@ -1816,7 +1824,7 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
     const bool batched = !pw_force && L <= kWave && P % 4 == 0 && P <= 64 && RG <= kPairMaxShards;
     const bool one_wg = P >= 4 && P <= 256 && (P & (P - 1)) == 0 && pair_lds <= 150 * 1024;
     const bool fast = !(pk_force && strcmp(pk_force, "single") == 0) && C < ((int64_t)1 << 31) && N < 65536 &&
-                      LP > 0 && (batched || one_wg);
+                      LP > 0 && !wide && (batched || one_wg);
     if (fast) {
         PackFast pf;
         pf.mstart = scr.get<int32_t>((size_t)nb * (K + 1));
@@ -1873,17 +1881,17 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
             else hipLaunchKernelGGL(k_pack_pair<false>, dim3(nb), dim3(1024), (size_t)pair_lds, stream, ta, pf);
         }
     } else {
-        hipLaunchKernelGGL(k_pack_trials, dim3(nb), dim3(64), 0, stream, ta);
+        hipLaunchKernelGGL(wide ? k_pack_trials<int64_t> : k_pack_trials<int32_t>, dim3(nb), dim3(64), 0, stream, ta);
     }
     RP_HIP(hipGetLastError());
     // Score every candidate (failed trials leave garbage layouts: their
     // status is nonzero or they are ignored by the selection).
     RP_TRY(eval_layouts(prob, topo, dp, lengths, q, (int32_t)R, M, cand, cscore, cstat, nullptr,
                         nullptr, nullptr, sums_fit32(ws), stream));
-    const int wide = N > 1024 ? 1024 : 256;
-    hipLaunchKernelGGL(k_canonical, dim3(M), dim3(wide), (size_t)4 * (2 * K + R), stream, cand, N, (int32_t)R, D,
+    const int threads = N > 1024 ? 1024 : 256;
+    hipLaunchKernelGGL(k_canonical, dim3(M), dim3(threads), (size_t)4 * (2 * K + R), stream, cand, N, (int32_t)R, D,
                        dp.slots, dp.count, dp.slot_shard, canon, chash);
-    hipLaunchKernelGGL(k_pack_select, dim3(1), dim3(wide), 0, stream, canon, chash, cscore, okv, cstat, M, N, keep,
+    hipLaunchKernelGGL(k_pack_select, dim3(1), dim3(threads), 0, stream, canon, chash, cscore, okv, cstat, M, N, keep,
                        meta);
     hipLaunchKernelGGL(k_pack_fill, dim3(pop_size), dim3(256), 0, stream, canon, cscore, keep, meta, N,
                        population, scores);

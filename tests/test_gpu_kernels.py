@@ -180,6 +180,27 @@ def test_pack_pairing_shapes(L, P, D, G, R, width, ties):
 
 
 @gpu
+@pytest.mark.parametrize("L,P,D,G,R", [(1, 1, 1, 1, 1), (1, 4, 2, 1, 6), (3, 16, 4, 2, 5), (2, 6, 3, 3, 7)])
+@pytest.mark.parametrize("load", [(1 << 31) - 1, 1 << 31, 1 << 33, 1 << 37])
+def test_pack_large_loads(L, P, D, G, R, load):
+    """Cell sums and row-shard loads on both sides of 2^31.  `load` is the
+    largest layer total, which bounds a load in the first shape; in the others
+    a row-shard's capacity times the largest entry per token is smaller."""
+    _log(f"pack loads up to {load} L={L} P={P} D={D} G={G} R={R}")
+    N = 5 * R * D + (1 if R > 1 else 0)
+    rng = np.random.default_rng([23, L, P, load & 0xFFFF])
+    t, q, kw = _pack_case(N, D, G, 9, np.ones(N), L=L, P=P)
+    share = min(load // N, (1 << 31) - 1)
+    q[:] = rng.integers(0, max(1, share // P // 2), size=q.shape)
+    q[:, 0, :] = 0
+    q[:, 0, 0] = share  # layer 0: all on rank 0, its total made exact on sample 0
+    q[0, 0, 0] += min(load - share * N, (1 << 31) - 1 - share)
+    assert q.min() >= 0 and q[:, 0].sum(dtype=np.int64) == min(load, N * ((1 << 31) - 1))
+    kw.update(min_rows=R, frac_bits=0, alpha_fp=np.array([1]), beta_fp=np.array([0]))
+    assert _check_pack(t, q, kw, 3) is not None
+
+
+@gpu
 @pytest.mark.parametrize("K,N", [(1, 5), (64, 65), (65, 130), (128, 900), (200, 200), (4096, 4300)])
 @pytest.mark.parametrize("scale", [1, 1 << 22])
 def test_pack_first_fit(K, N, scale):
