@@ -30,6 +30,7 @@ struct EvalArgs {
     int32_t *status;                        // [n]
     int64_t *Jbuf, *Abuf;                   // [n][R*G]
     int64_t *wmax, *wsum;                   // [n][R*G][L]
+    int64_t items;                          // n * R*G
 };
 
 __global__ void __launch_bounds__(256) k_eval_rowshard(EvalArgs a) {
@@ -45,8 +46,10 @@ __global__ void __launch_bounds__(256) k_eval_rowshard(EvalArgs a) {
     int32_t *stat = nmem + 1;                           // [1]
     int64_t *red = reinterpret_cast<int64_t *>(((uintptr_t)(stat + 1) + 7) & ~(uintptr_t)7);  // [4]
 
-    const int64_t lay_idx = blockIdx.x / RG;
-    const int64_t h = blockIdx.x % RG;
+    const int64_t item = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (item >= a.items) return;
+    const int64_t lay_idx = item / RG;
+    const int64_t h = item % RG;
     const int32_t r = (int32_t)(h / a.G), g = (int32_t)(h % a.G);
     const int32_t *lay = a.layouts + lay_idx * a.N;
     const int64_t B = (int64_t)a.R * a.D;
@@ -437,12 +440,6 @@ int eval_layouts(const routepack_problem *p, const Topology &topo, const DeviceP
     if (n == 0) return ROUTEPACK_OK;
     const int64_t RG = (int64_t)R * topo.G, LP = (int64_t)p->n_layers * p->n_ranks;
     if (LP > 16384) return ROUTEPACK_E_UNSUPPORTED;
-    Scratch scr(stream);
-    int64_t *Jbuf = scr.get<int64_t>(n * RG);
-    int64_t *Abuf = scr.get<int64_t>(n * RG);
-    int64_t *wmax = scr.get<int64_t>(n * RG * (p->n_layers ? p->n_layers : 1));
-    int64_t *wsum = scr.get<int64_t>(n * RG * (p->n_layers ? p->n_layers : 1));
-    if (scr.failed()) return ROUTEPACK_E_DEVICE;
     const int64_t B = (int64_t)R * topo.D, L = p->n_layers, P = p->n_ranks, N = p->n_samples;
     // The list path: a power-of-two rank count from 4 to 64 (a layer's ranks
     // on up to 16 adjacent lanes), 16-byte rows and cell statistics that fit
@@ -452,64 +449,75 @@ int eval_layouts(const routepack_problem *p, const Topology &topo, const DeviceP
     // and 2.1 ms.
     const bool lists = L > 0 && P >= 4 && P <= 64 && (P & (P - 1)) == 0 && ((uintptr_t)q & 15) == 0 &&
                        eval_lists_lds(B, RG) <= 60 * 1024;
+    const RowPieces pc = lists ? row_pieces(N, L, P) : RowPieces{};
+    // Layouts per pass.  A launch of 2^32 threads and more is cut short
+    // without an error, so every kernel's grid stays below 2^24 workgroups of
+    // 256; sample lists of at most 64 Mi entries.
+    constexpr int64_t kMostWgs = ((int64_t)1 << 24) - 1;
+    int64_t nb = n < kMostWgs ? n : kMostWgs;
     if (lists) {
-        ListArgs la;
-        la.t = t; la.N = (int32_t)N; la.D = topo.D; la.G = topo.G; la.R = R; la.S = p->n_stages; la.C = p->capacity;
-        la.slots = dp.slots; la.count = dp.count; la.slot_shard = dp.slot_shard;
-        la.alpha = dp.alpha; la.beta = dp.beta;
-        RowArgs ra;
-        ra.q = q; ra.N = (int32_t)N; ra.L = (int32_t)L; ra.P = (int32_t)P; ra.RG = (int32_t)RG; ra.F = p->frac_bits;
-        const RowPieces pc = row_pieces(N, L, P);
-        ra.spread = pc.spread ? 1 : 0;
-        ra.lay_piece = pc.lay_piece;
-        ra.n_pieces = pc.n_pieces;
-        // the sample lists of at most 64 Mi entries at a time
-        int64_t nb = ((int64_t)64 << 20) / N;
-        nb = nb < 1 ? 1 : (nb > n ? n : nb);
-        nb = nb * RG * ra.n_pieces < ((int64_t)1 << 31) ? nb : ((int64_t)1 << 31) / (RG * ra.n_pieces);
-        int32_t *list = scr.get<int32_t>((size_t)(nb * N)), *hstart = scr.get<int32_t>((size_t)(nb * (RG + 1)));
-        if (scr.failed()) return ROUTEPACK_E_DEVICE;
-        la.list = list; la.hstart = hstart;
-        ra.list = list; ra.hstart = hstart;
-        for (int64_t l0 = 0; l0 < n; l0 += nb) {
-            const int64_t m = nb < n - l0 ? nb : n - l0;
-            la.layouts = layouts + l0 * N;
-            la.status = status + l0;
-            la.Jbuf = Jbuf + l0 * RG;
-            la.Abuf = Abuf + l0 * RG;
+        const int64_t by_list = ((int64_t)64 << 20) / N, by_rows = kMostWgs / pc.n_pieces * kEvalWaves / RG;
+        nb = by_list < nb ? by_list : nb;
+        nb = by_rows < nb ? by_rows : nb;
+        nb = nb < 1 ? 1 : nb;
+    }
+    Scratch scr(stream);
+    int64_t *Jbuf = scr.get<int64_t>(nb * RG);
+    int64_t *Abuf = scr.get<int64_t>(nb * RG);
+    int64_t *wmax = scr.get<int64_t>(nb * RG * (L ? L : 1));
+    int64_t *wsum = scr.get<int64_t>(nb * RG * (L ? L : 1));
+    int32_t *list = lists ? scr.get<int32_t>((size_t)(nb * N)) : nullptr;
+    int32_t *hstart = lists ? scr.get<int32_t>((size_t)(nb * (RG + 1))) : nullptr;
+    if (scr.failed()) return ROUTEPACK_E_DEVICE;
+    for (int64_t l0 = 0; l0 < n; l0 += nb) {
+        const int64_t m = nb < n - l0 ? nb : n - l0;
+        if (lists) {
+            ListArgs la;
+            la.t = t; la.layouts = layouts + l0 * N;
+            la.N = (int32_t)N; la.D = topo.D; la.G = topo.G; la.R = R; la.S = p->n_stages; la.C = p->capacity;
+            la.slots = dp.slots; la.count = dp.count; la.slot_shard = dp.slot_shard;
+            la.alpha = dp.alpha; la.beta = dp.beta;
+            la.status = status + l0; la.Jbuf = Jbuf; la.Abuf = Abuf; la.list = list; la.hstart = hstart;
             // few layouts: more threads for each
             const int threads = m >= 512 || N <= 1024 ? 256 : 1024;
             hipLaunchKernelGGL(k_eval_lists, dim3((unsigned)m), dim3(threads), eval_lists_lds(B, RG), stream, la);
+            RowArgs ra;
+            ra.q = q; ra.list = list; ra.hstart = hstart;
+            ra.N = (int32_t)N; ra.L = (int32_t)L; ra.P = (int32_t)P; ra.RG = (int32_t)RG; ra.F = p->frac_bits;
+            ra.lay_piece = pc.lay_piece;
+            ra.n_pieces = pc.n_pieces;
+            ra.spread = pc.spread ? 1 : 0;
             ra.items = m * RG;
-            ra.Jbuf = Jbuf + l0 * RG;
-            ra.wmax = diag ? wmax + l0 * RG * L : nullptr;
-            ra.wsum = diag ? wsum + l0 * RG * L : nullptr;
+            ra.Jbuf = Jbuf; ra.wmax = diag ? wmax : nullptr; ra.wsum = diag ? wsum : nullptr;
             const int64_t wgs = (ra.items + kEvalWaves - 1) / kEvalWaves * ra.n_pieces;
             auto rows = pc.one ? (sum32 ? k_eval_rows<true, uint32_t> : k_eval_rows<true, int64_t>)
-                                               : (sum32 ? k_eval_rows<false, uint32_t> : k_eval_rows<false, int64_t>);
+                               : (sum32 ? k_eval_rows<false, uint32_t> : k_eval_rows<false, int64_t>);
             hipLaunchKernelGGL(rows, dim3((unsigned)wgs), dim3(kEvalWaves * kWave), 0, stream, ra);
+        } else {
+            hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((m + 255) / 256 < 1024 ? (m + 255) / 256 : 1024)),
+                               dim3(256), 0, stream, status + l0, m, 0);
+            EvalArgs a;
+            a.t = t; a.q = q; a.layouts = layouts + l0 * N;
+            a.N = p->n_samples; a.L = p->n_layers; a.P = p->n_ranks; a.D = topo.D; a.G = topo.G; a.R = R;
+            a.S = p->n_stages; a.F = p->frac_bits; a.C = p->capacity; a.items = m * RG;
+            a.slots = dp.slots; a.count = dp.count; a.slot_shard = dp.slot_shard;
+            a.alpha = dp.alpha; a.beta = dp.beta;
+            a.status = status + l0; a.Jbuf = Jbuf; a.Abuf = Abuf; a.wmax = wmax; a.wsum = wsum;
+            const size_t lds = (size_t)LP * 8 + (size_t)topo.D * 20 + 256 * 4 + 64 + 64;
+            if (lds > 160 * 1024) return ROUTEPACK_E_UNSUPPORTED;
+            const int64_t gx = a.items < ((int64_t)1 << 23) ? a.items : (int64_t)1 << 23;
+            hipLaunchKernelGGL(k_eval_rowshard, dim3((unsigned)gx, (unsigned)((a.items + gx - 1) / gx)), dim3(256), lds,
+                               stream, a);
         }
-    } else {
-        hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024)),
-                           dim3(256), 0, stream, status, n, 0);
-        EvalArgs a;
-        a.t = t; a.q = q; a.layouts = layouts;
-        a.N = p->n_samples; a.L = p->n_layers; a.P = p->n_ranks; a.D = topo.D; a.G = topo.G; a.R = R;
-        a.S = p->n_stages; a.F = p->frac_bits; a.C = p->capacity;
-        a.slots = dp.slots; a.count = dp.count; a.slot_shard = dp.slot_shard;
-        a.alpha = dp.alpha; a.beta = dp.beta;
-        a.status = status; a.Jbuf = Jbuf; a.Abuf = Abuf; a.wmax = wmax; a.wsum = wsum;
-        const size_t lds = (size_t)LP * 8 + (size_t)topo.D * 20 + 256 * 4 + 64 + 64;
-        if (lds > 160 * 1024) return ROUTEPACK_E_UNSUPPORTED;
-        hipLaunchKernelGGL(k_eval_rowshard, dim3((unsigned)(n * RG)), dim3(256), lds, stream, a);
+        FinalArgs f;
+        f.L = p->n_layers; f.P = p->n_ranks; f.G = topo.G; f.R = R;
+        f.scale = ldexp((double)p->capacity, p->frac_bits);
+        f.status = status + l0; f.Jbuf = Jbuf; f.Abuf = Abuf; f.wmax = wmax; f.wsum = wsum;
+        f.rank_load = rank_load; f.scores = scores + l0 * 3; f.J = J ? J + l0 * RG : nullptr;
+        f.diag = diag ? diag + l0 * 8 : nullptr;
+        hipLaunchKernelGGL(k_eval_finalize, dim3((unsigned)m), dim3(256), 0, stream, f);
+        RP_HIP(hipGetLastError());
     }
-    FinalArgs f;
-    f.L = p->n_layers; f.P = p->n_ranks; f.G = topo.G; f.R = R;
-    f.scale = ldexp((double)p->capacity, p->frac_bits);
-    f.status = status; f.Jbuf = Jbuf; f.Abuf = Abuf; f.wmax = wmax; f.wsum = wsum;
-    f.rank_load = rank_load; f.scores = scores; f.J = J; f.diag = diag;
-    hipLaunchKernelGGL(k_eval_finalize, dim3((unsigned)n), dim3(256), 0, stream, f);
-    RP_HIP(hipGetLastError());
     return ROUTEPACK_OK;
 }
 

@@ -91,6 +91,33 @@ def test_score_edges(P, L, G, D, R, N, big):
             np.testing.assert_allclose(out["diag"][m].cpu().numpy(), dg, rtol=1e-11, atol=0)
 
 
+@gpu
+@pytest.mark.parametrize("N,L,P,D,G,R,n", [(64, 64, 64, 1, 1, 64, 70000), (64, 1, 6, 1, 1, 64, 262200),
+                                             ((1 << 20) + 3, 1, 4, 4, 2, 8, 66)])
+def test_score_pieces(N, L, P, D, G, R, n):
+    """More layouts than one launch takes: row pieces past 2^32 threads (70000
+    layouts x 64 row-shards x 16 pieces), row-shards past them on the general
+    kernel (6 ranks), and sample lists past 2^26 entries."""
+    import torch
+    import oracle as O
+    import paper_2608_12146_amd as rp
+    _log(f"score pieces N={N} L={L} P={P} R={R} layouts={n}")
+    rng = np.random.default_rng([24, N])
+    t = rng.integers(1, 50, size=N).astype(np.int32)
+    q = rng.integers(0, 60, size=(N, L, P)).astype(np.int32)
+    g = (np.arange(D) * G // D).astype(np.int32)
+    kw = dict(n_samples=N, n_layers=L, n_experts=P, top_k=1, n_ranks=P, n_dp=D, n_edp=G, dp_to_edp=g,
+              capacity=int(t.sum()), alpha_fp=np.array([3]), beta_fp=np.array([0]), frac_bits=0, min_rows=1)
+    base = np.stack([rng.permutation(np.arange(N) % (R * D)) for _ in range(3)]).astype(np.int32)
+    which = rng.integers(0, 3, size=n)
+    lays = torch.as_tensor(base, device="cuda")[torch.as_tensor(which, device="cuda")].contiguous()
+    out = rp.eval_objective(rp.Problem.from_dict(kw), t, q, R, lays, want_J=True)
+    want = [O.score(O.Problem.from_dict(kw), t, q, R, x, want_J=True) for x in base]
+    assert not out["status"].any()
+    assert np.array_equal(out["scores"].cpu().numpy(), np.stack([w[1] for w in want])[which])
+    assert np.array_equal(out["J"].cpu().numpy(), np.stack([w[2] for w in want])[which])
+
+
 def _pack_case(N, D, G, cap, lengths, L=2, P=4, seed=5):
     rng = np.random.default_rng([13, N, D, seed])
     q = rng.integers(0, 1000, size=(N, L, P)).astype(np.int32)
