@@ -29,7 +29,7 @@ struct EvalArgs {
     const int64_t *alpha, *beta;
     int32_t *status;                        // [n]
     int64_t *Jbuf, *Abuf;                   // [n][R*G]
-    int64_t *wmax, *wsum;                   // [n][R*G][L]
+    int64_t *wmax, *wsum;                   // [n][R*G][L] or null
     int64_t items;                          // n * R*G
 };
 
@@ -101,9 +101,11 @@ __global__ void __launch_bounds__(256) k_eval_rowshard(EvalArgs a) {
             sm += v;
         }
         esum += mx;
-        const int64_t o = (lay_idx * RG + h) * a.L + l;
-        a.wmax[o] = mx;
-        a.wsum[o] = sm;
+        if (a.wmax) {
+            const int64_t o = (lay_idx * RG + h) * a.L + l;
+            a.wmax[o] = mx;
+            a.wsum[o] = sm;
+        }
     }
     esum = wave_sum(esum);
     if (lane_id() == 0) red[wave_id()] = esum;
@@ -464,8 +466,8 @@ int eval_layouts(const routepack_problem *p, const Topology &topo, const DeviceP
     Scratch scr(stream);
     int64_t *Jbuf = scr.get<int64_t>(nb * RG);
     int64_t *Abuf = scr.get<int64_t>(nb * RG);
-    int64_t *wmax = scr.get<int64_t>(nb * RG * (L ? L : 1));
-    int64_t *wsum = scr.get<int64_t>(nb * RG * (L ? L : 1));
+    int64_t *wmax = diag ? scr.get<int64_t>(nb * RG * (L ? L : 1)) : nullptr;
+    int64_t *wsum = diag ? scr.get<int64_t>(nb * RG * (L ? L : 1)) : nullptr;
     int32_t *list = lists ? scr.get<int32_t>((size_t)(nb * N)) : nullptr;
     int32_t *hstart = lists ? scr.get<int32_t>((size_t)(nb * (RG + 1))) : nullptr;
     if (scr.failed()) return ROUTEPACK_E_DEVICE;
@@ -488,7 +490,7 @@ int eval_layouts(const routepack_problem *p, const Topology &topo, const DeviceP
             ra.n_pieces = pc.n_pieces;
             ra.spread = pc.spread ? 1 : 0;
             ra.items = m * RG;
-            ra.Jbuf = Jbuf; ra.wmax = diag ? wmax : nullptr; ra.wsum = diag ? wsum : nullptr;
+            ra.Jbuf = Jbuf; ra.wmax = wmax; ra.wsum = wsum;
             const int64_t wgs = (ra.items + kEvalWaves - 1) / kEvalWaves * ra.n_pieces;
             auto rows = pc.one ? (sum32 ? k_eval_rows<true, uint32_t> : k_eval_rows<true, int64_t>)
                                : (sum32 ? k_eval_rows<false, uint32_t> : k_eval_rows<false, int64_t>);
