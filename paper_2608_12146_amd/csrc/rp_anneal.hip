@@ -628,14 +628,15 @@ __global__ void __launch_bounds__(kThreads) k_build_rowsums(AnnealArgs a, RowPie
     }
 }
 
-// W row, A and J of row-shard h of leader m (grid: members x row-shards).
+// W row, A and J of row-shard h of leader m (grid: members x row-shards, over
+// two dimensions).
 __global__ void __launch_bounds__(kThreads) k_build_rows(AnnealArgs a, const int32_t *leader,
                                                          const int32_t *status) {
     __shared__ int64_t red[kThreads / kWave];
     const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
-    const int64_t m = blockIdx.x / a.RG;
-    const int32_t h = (int32_t)(blockIdx.x % a.RG);
-    if (leader[m] != m || status[m] != 0) return;
+    const int64_t item = (int64_t)blockIdx.y * gridDim.x + blockIdx.x, m = item / a.RG;
+    const int32_t h = (int32_t)(item % a.RG);
+    if (m >= a.pop || leader[m] != m || status[m] != 0) return;
     const int32_t LP = a.LP, D = a.D, G = a.G;
     char *dst = a.dst + m * a.off.bytes;
     const int32_t *pool = at<int32_t>(dst, a.off.pool);
@@ -1170,14 +1171,15 @@ extern "C" int routepack_anneal(const routepack_problem *prob, const int32_t *le
                        n_lead);
     hipLaunchKernelGGL(k_build_cells, dim3(pop_size), dim3(kThreads), lds_build, stream, a, population,
                        leader, status);
-    const bool by_waves = P >= 4 && LP64 > 0 && ((uintptr_t)q & 15) == 0;
+    const RowPieces pc = row_pieces(N, L > 0 ? L : 1, P);
+    // (k_build_rowsums counts its items in 32 bits)
+    const bool by_waves = P >= 4 && LP64 > 0 && ((uintptr_t)q & 15) == 0 &&
+                          pop_size * RG64 * pc.n_pieces < (int64_t)1 << 31;
     if (by_waves) {
-        const RowPieces pc = row_pieces(N, L, P);
         hipLaunchKernelGGL(pc.one ? k_build_rowsums<true> : k_build_rowsums<false>, dim3(2048), dim3(kThreads), 0,
                            stream, a, pc, lead_list, n_lead, status, whole || chain);
     } else {
-        hipLaunchKernelGGL(k_build_rows, dim3((unsigned)(pop_size * RG64)), dim3(kThreads), 0, stream, a, leader,
-                           status);
+        hipLaunchKernelGGL(k_build_rows, grid_of(pop_size * RG64), dim3(kThreads), 0, stream, a, leader, status);
     }
     hipLaunchKernelGGL(k_build_final, dim3(pop_size), dim3(kThreads), 0, stream, a, leader, status);
     RP_HIP(hipGetLastError());

@@ -2069,7 +2069,7 @@ __global__ void __launch_bounds__(256) k_rows_to_chunks(const int32_t *src, int3
                                                       int64_t row_stride, int64_t rows_per_group,
                                                       int64_t group_stride, int32_t L, int32_t P) {
     __shared__ int32_t row[4096];  // L * P <= 64 * 64
-    const int64_t rr = blockIdx.x;
+    const int64_t rr = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
     if (rr >= n_rows) return;
     const int64_t off = (rr / rows_per_group) * group_stride + (rr % rows_per_group) * row_stride;
     const int32_t LP = L * P;
@@ -2088,8 +2088,9 @@ int chain_prepare(AnnealArgs &a, int32_t *qt, bool w_chunked, hipStream_t stream
                            (int64_t)a.LP, (int64_t)1, (int64_t)a.LP, a.L, a.P);
         int32_t *w = reinterpret_cast<int32_t *>(a.slabs + a.off.W);
         const int64_t rows = (int64_t)a.pop * a.RG;
-        if (!w_chunked) hipLaunchKernelGGL(k_rows_to_chunks, dim3((unsigned)rows), dim3(256), 0, stream, w, w, rows, (int64_t)a.LP,
-                           (int64_t)a.RG, a.off.bytes / (int64_t)sizeof(int32_t), a.L, a.P);
+        if (!w_chunked)
+            hipLaunchKernelGGL(k_rows_to_chunks, grid_of(rows), dim3(256), 0, stream, w, w, rows, (int64_t)a.LP,
+                               (int64_t)a.RG, a.off.bytes / (int64_t)sizeof(int32_t), a.L, a.P);
         if (hipGetLastError() != hipSuccess) return ROUTEPACK_E_DEVICE;
     }
     a.qt = qt;

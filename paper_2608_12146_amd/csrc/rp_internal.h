@@ -35,6 +35,14 @@ struct Topology {
 // Validates the sizes, coefficients and partition of a problem.
 int check_problem(const routepack_problem *p, Topology *topo);
 
+// Grid of n >= 1 workgroups of up to 512 threads, over two dimensions: a
+// launch of 2^32 threads or more in one is cut short without an error.  Its
+// last row may be part-filled (item = blockIdx.y gridDim.x + blockIdx.x < n).
+inline dim3 grid_of(int64_t n) {
+    const int64_t x = n < ((int64_t)1 << 22) ? n : (int64_t)1 << 22;
+    return dim3((unsigned)x, (unsigned)((n + x - 1) / x));
+}
+
 struct Arena;
 
 // RAII device scratch for one call on one stream.  Each (device, stream)

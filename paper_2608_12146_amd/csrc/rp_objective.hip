@@ -507,9 +507,7 @@ int eval_layouts(const routepack_problem *p, const Topology &topo, const DeviceP
             a.status = status + l0; a.Jbuf = Jbuf; a.Abuf = Abuf; a.wmax = wmax; a.wsum = wsum;
             const size_t lds = (size_t)LP * 8 + (size_t)topo.D * 20 + 256 * 4 + 64 + 64;
             if (lds > 160 * 1024) return ROUTEPACK_E_UNSUPPORTED;
-            const int64_t gx = a.items < ((int64_t)1 << 23) ? a.items : (int64_t)1 << 23;
-            hipLaunchKernelGGL(k_eval_rowshard, dim3((unsigned)gx, (unsigned)((a.items + gx - 1) / gx)), dim3(256), lds,
-                               stream, a);
+            hipLaunchKernelGGL(k_eval_rowshard, grid_of(a.items), dim3(256), lds, stream, a);
         }
         FinalArgs f;
         f.L = p->n_layers; f.P = p->n_ranks; f.G = topo.G; f.R = R;

@@ -279,6 +279,25 @@ def test_anneal_start_state(P, L, shards):
 
 
 @gpu
+def test_anneal_many_row_shards():
+    """Start rows of 32800 distinct members with 512 row-shards each, 2^24 and
+    more in one call, on the general kernel (2 ranks)."""
+    import oracle as O
+    import paper_2608_12146_amd as rp
+    pop, N = 32800, 512
+    _log(f"anneal {pop} members of {N} row-shards")
+    rng = np.random.default_rng([25, pop])
+    t, q, kw = _pack_case(N, 1, 1, 60, rng.integers(1, 60, size=N), L=1, P=2)
+    layouts = rng.permuted(np.tile(np.arange(N, dtype=np.int32), (pop, 1)), axis=1)
+    temps = np.array([1e-2, 1e-3])
+    o = O.anneal(O.Problem.from_dict(kw), t, q, N, layouts, temps, 4, 9)
+    g = rp.anneal(rp.Problem.from_dict(kw), t, q, N, layouts, temps, 4, 9)
+    assert o["rc"] == 0 and o["trace"][..., 6].sum() > 0
+    for k in ("trace", "parents", "population", "best_layout"):
+        assert np.array_equal(g[k].cpu().numpy(), o[k])
+
+
+@gpu
 @pytest.mark.parametrize("pop", [1, 3, 1023, 1025, 2050, 7372, 7373, 9557, 9558])
 def test_level_end_populations(pop, monkeypatch):
     """Resampling after each level of the per-level kernel with one member, a
