@@ -1592,34 +1592,51 @@ __device__ inline uint64_t ld_dev(const void *p) {
     return __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Release at agent scope; the L2 has been written back when it returns.  The
+// wait is spelled out: the compiler takes the fence's own wait after the
+// write-back out when it sees no access of the wave pending before it.
+__device__ inline void release_dev() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __builtin_amdgcn_s_waitcnt(0);
+}
+
 // Grid-wide barrier; false if it timed out (then every workgroup stops).
 // Every thread of the workgroup takes part.  Workgroups count themselves in at
 // r.bar; the one that completes the count raises every workgroup's own flag
 // (128 bytes apart) to the epoch, and each polls only its own, so the last
 // arrivals and the waves still at work do not queue behind 256 polls of one
 // address: with all of them polling the count, 2000 levels of the ordinary
-// window took 104.3 ms (tight cells, 1.5 moves per member and level) and
-// 150 of two shards 23.9 ms; now 98.9 and 23.5 ms.
+// window took 104.3 ms on an input of tight cells (1.5 moves per member and
+// level) and 332 on one of loose cells, 150 of two shards 23.9 ms; now 98.9,
+// 330 and 23.5 ms.
 // FULL: release and acquire at agent scope (the XCD's L2 written back, then
 // invalidated), so ordinary stores before it are visible to ordinary loads
-// after it in every workgroup.  Otherwise only device-scope stores (st_dev)
-// made before it are visible after it, to device-scope loads (ld_dev).
+// after it in every workgroup.  The chain is arrival (release) -> the last
+// arrival's add -> its flag stores -> a poll (acquire): the last arrival reads
+// one object and writes others, so it acquires and releases between the two.
+// Otherwise only device-scope stores (st_dev) made before it are visible after
+// it, to device-scope loads (ld_dev): they have reached memory before their
+// workgroup's add, and nothing else is handed on.
 template <bool FULL>
 __device__ inline bool grid_sync(const RunArgs &r, unsigned epoch, int32_t *s_ok) {
-    if (!FULL) __builtin_amdgcn_s_waitcnt(0);  // this wave's st_dev stores have completed
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's stores have completed
     __syncthreads();
     if (threadIdx.x < kWave) {
         const int lane = lane_id();
         const unsigned nb = gridDim.x;
         unsigned last = 0;
         if (lane == 0) {
-            if (FULL) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            if (FULL) release_dev();
             const unsigned at = __hip_atomic_fetch_add(r.bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             last = at + 1 == nb * epoch ? 1 : 0;
         }
         last = (unsigned)__builtin_amdgcn_readfirstlane((int)last);
         int32_t good = 1;
         if (last) {
+            if (FULL) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                release_dev();
+            }
             for (unsigned b = lane; b < nb; b += kWave)
                 __hip_atomic_store(r.flags + (size_t)b * kFlagStride, epoch, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
@@ -2008,7 +2025,7 @@ __global__ void __launch_bounds__(kRunMaxWaves * kWave) k_anneal_chain_run(Annea
             if (publish) {
                 member_publish<GV == 2 ? 2 : 1>(a, smem + a.lds_shared + (int64_t)wv * a.lds_member, r.blobs + (int64_t)gw * r.blob_bytes, R);
                 if (!sync_b) {
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    release_dev();
                     if (lane == 0) __hip_atomic_store(r.pub + gw, token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
@@ -2023,7 +2040,7 @@ __global__ void __launch_bounds__(kRunMaxWaves * kWave) k_anneal_chain_run(Annea
                 if (!sync_b) {
                     wave_copy16(a.slabs + (int64_t)src_slab * a.off.bytes + a.off.W,
                                 a.slabs + (int64_t)gw * a.off.bytes + a.off.W, nW16);
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    release_dev();
                     if (lane == 0) __hip_atomic_fetch_add(r.got + src_slab, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }

@@ -4,6 +4,8 @@ are reported before any device work."""
 import ctypes as C
 import os
 import re
+import struct
+import subprocess
 
 import numpy as np
 import pytest
@@ -73,3 +75,48 @@ def test_noalloc_aggregation_rejects_oversized_shapes_without_device_work():
     big = rp.Problem(1, 1, (1 << 20) + 1, 1, 1, 1, 1, [0], 64, [4096], [1])
     assert lib.routepack_aggregate_demand_noalloc(big.ref, C.c_void_p(16), C.c_void_p(16), None) == -8
     assert lib.routepack_aggregate_demand_noalloc(None, None, None, None) == -1
+
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+def _device_images(lib):
+    """The gfx950 code objects bundled in a library built here."""
+    data = open(lib, "rb").read()
+    magic, at = b"__CLANG_OFFLOAD_BUNDLE__", 0
+    while (at := data.find(magic, at)) >= 0:
+        n = struct.unpack_from("<Q", data, at + 24)[0]
+        p = at + 32
+        for _ in range(n):
+            off, size, ln = struct.unpack_from("<QQQ", data, p)
+            if b"gfx950" in data[p + 24:p + 24 + ln]:
+                yield data[at + off:at + off + size]
+            p += 24 + ln
+        at += 24
+
+
+@pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="needs llvm-objdump")
+def test_l2_write_backs_are_waited_for(tmp_path):
+    """The release before a flag or a barrier count of the whole-schedule
+    kernel: in the code as compiled, no memory access follows an L2 write-back
+    before a wait for it."""
+    import paper_2608_12146_amd as rp
+    seen = 0
+    for x, image in enumerate(_device_images(rp.LIB_PATH)):
+        if b"k_anneal_chain_run" not in image:
+            continue
+        obj = tmp_path / f"{x}.co"
+        obj.write_bytes(image)
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(obj)], check=True, capture_output=True,
+                              text=True).stdout
+        pending = False
+        for line in text.splitlines():
+            op = line.split("//")[0].strip()
+            if op.startswith("buffer_wbl2"):
+                assert not pending
+                pending, seen = True, seen + 1
+            elif op.startswith("s_waitcnt") and "vmcnt(0)" in op:
+                pending = False
+            elif op.startswith(("global_", "flat_", "buffer_")):
+                assert not pending, op
+    assert seen > 0
