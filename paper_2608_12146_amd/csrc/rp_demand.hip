@@ -184,16 +184,16 @@ __global__ void __launch_bounds__(kLptThreads) k_lpt_place(const int64_t *__rest
     __syncthreads();
     if (tid >= kWave) return;  // (no barrier follows)
     // the layer's load, which bounds every rank's: the key below holds 58 bits
-    // (each lane's share saturates at 2^50, so that the sum of any number of
-    // experts stays below 2^57)
+    // (at most 2^14 experts of at most 2^50 each: a lane's share is below
+    // 2^58, and saturates at 2^50 so that the sum over the wave fits too)
     constexpr int64_t kMost = (int64_t)1 << 50;
     int64_t part = 0, low = 0;
     for (int e = lane; e < E; e += kWave) {
         part += Ll[e] < kMost ? Ll[e] : kMost;
-        part = part < kMost ? part : kMost;
         low = Ll[e] < low ? Ll[e] : low;
     }
-    const bool keyed = P <= kWave && E <= (1 << 20) && wave_min(low) >= 0 && wave_sum(part) < kMost;
+    part = part < kMost ? part : kMost;
+    const bool keyed = P <= kWave && E <= (1 << 14) && wave_min(low) >= 0 && wave_sum(part) < kMost;
     if (keyed) {
         // lane x < open ranks: the x-th open rank in (G_p, p) order, as the
         // key (2^58 - 1 - G_p) 2^6 + 63 - p (a larger key comes first; the
