@@ -8,9 +8,12 @@
 //                  lowest-index cell with room, found with a two-level ballot
 //                  (per-64-cell maximum room, then the cells of that chunk).
 //  k_seed_words    Philox4x64-10 words of every randomized draw, in parallel.
-//  k_pack_trials   one wave per candidate: block 0 pairs x_length's cells
-//                  with width 1; block b >= 1 runs trial b (WindowShuffle,
-//                  RandomizedBestFit, EDPAwarePair with width w).
+//  k_pack_fit*, k_pack_cell*, k_pair_*  the seed trials in stages: best fit,
+//                  cell sums, pairing (block 0 pairs x_length's cells with
+//                  width 1; block b >= 1 runs trial b: WindowShuffle,
+//                  RandomizedBestFit, EDPAwarePair with width w); below.
+//  k_pack_trials   the same trials in one kernel, one wave per candidate, for
+//                  the shapes and sizes the stages do not take.
 //  k_canonical     canonical form of every candidate: cells are disjoint, so
 //                  ordering the cells of a row-shard by their sorted id tuples
 //                  is ordering them by smallest id, and ordering rows by their
@@ -1807,21 +1810,21 @@ extern "C" int routepack_pack_rows(const routepack_problem *prob, const int32_t 
     hipLaunchKernelGGL(k_fill_i32, dim3(256), dim3(256), 0, stream, cand, (int64_t)M * N, 0);
     hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, stream, okv, (int64_t)M, 0);
     RP_HIP(hipMemcpyAsync(cand, x_len, sizeof(int32_t) * N, hipMemcpyDeviceToDevice, stream));
-    // Seed trials: three kernels for the common shapes, else one.
-    // ROUTEPACK_PACK_KERNEL=single requests the single-kernel path.
+    // Seed trials in stages for the common shapes, else k_pack_trials.
+    // ROUTEPACK_PACK_KERNEL=single requests the latter.
     const char *pk_force = getenv("ROUTEPACK_PACK_KERNEL");
-    // The pairing kernel keeps W in LDS when it fits (ROUTEPACK_PACK_W=hbm
-    // keeps it in HBM regardless), else in HBM.
+    // Batched pairing (k_pair_*) for layers that fit a wave and ranks that a
+    // lane holds.  k_pack_pair beyond 64 layers or ranks or 512 row-shards,
+    // for power-of-two ranks whose tables fit LDS: W there too when it fits,
+    // else in HBM.  ROUTEPACK_PACK_W=hbm requests k_pack_pair with W in HBM.
     const int64_t pair_rest = 8 * (3 * (int64_t)RG + K + 1) +
                               4 * (2 * LP + (int64_t)RG * prob->n_layers + 2 * (int64_t)RG + 2 * (int64_t)K);
     const char *pw_force = getenv("ROUTEPACK_PACK_W");
-    const bool w_hbm = (pw_force && strcmp(pw_force, "hbm") == 0) || pair_rest + 4 * (int64_t)RG * LP > 150 * 1024;
+    const bool force_hbm = pw_force && strcmp(pw_force, "hbm") == 0;
+    const bool w_hbm = force_hbm || pair_rest + 4 * (int64_t)RG * LP > 150 * 1024;
     const int64_t pair_lds = pair_rest + (w_hbm ? 0 : 4 * (int64_t)RG * LP);
     const int32_t P = prob->n_ranks, L = prob->n_layers;
-    // Batched pairing (k_pair_*) for layers that fit a wave and ranks that a
-    // lane holds; k_pack_pair beyond 64 layers or ranks or 512 row-shards (and
-    // on request), for power-of-two ranks whose tables fit LDS.
-    const bool batched = !pw_force && L <= kWave && P % 4 == 0 && P <= 64 && RG <= kPairMaxShards;
+    const bool batched = !force_hbm && L <= kWave && P % 4 == 0 && P <= 64 && RG <= kPairMaxShards;
     const bool one_wg = P >= 4 && P <= 256 && (P & (P - 1)) == 0 && pair_lds <= 150 * 1024;
     const bool fast = !(pk_force && strcmp(pk_force, "single") == 0) && C < ((int64_t)1 << 31) && N < 65536 &&
                       LP > 0 && !wide && (batched || one_wg);

@@ -499,9 +499,10 @@ def test_anneal_crowded_cells(G, kernel, monkeypatch):
 @pytest.mark.parametrize("path", ["default", "single", "w_hbm"])
 def test_pack_rows(name, G, S, path, monkeypatch):
     """Row count and seed population equal to the oracle's; "single" requests
-    the one-kernel seed trials, "default" the library's choice (three
-    kernels where the shape allows), "w_hbm" the three kernels with the
-    pairing's row-shard loads in HBM (the largest windows' path)."""
+    the one-kernel seed trials, "default" the library's choice (in stages,
+    with batched pairing, on all of these shapes), "w_hbm" the stages with one
+    workgroup per trial pairing on row-shard loads in HBM (the path of more
+    than 64 layers or ranks whose loads do not fit LDS)."""
     rp = _rp()
     monkeypatch.delenv("ROUTEPACK_PACK_W", raising=False)
     if path == "single":
