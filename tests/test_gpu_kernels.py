@@ -323,12 +323,53 @@ def test_level_end_populations(pop, monkeypatch):
 
 
 @gpu
-@pytest.mark.parametrize("N,D,R,shards", [(200, 4, 2, 1), (203, 2, 2, 1), (600, 4, 2, 1), (900, 4, 7, 2), (37, 4, 3, 1)])
+@pytest.mark.parametrize("P,L,shards", [(4, 5, 2), (8, 31, 1), (16, 40, 2), (32, 3, 1), (64, 6, 1)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_q_alignment(P, L, shards, offset):
+    """The whole path on a q that starts 4 bytes past a 16-byte boundary, which
+    the kernels without 16-byte loads take: window bounds, cell sums, scores,
+    the annealing's start rows and their rewrite to chunks."""
+    import torch
+    import oracle as O
+    import paper_2608_12146_amd as rp
+    _log(f"q alignment P={P} L={L} shards={shards} offset={offset}")
+    D, R = 4, 5
+    rng = np.random.default_rng([26, P, L])
+    t = rng.integers(1, 60, size=R * D * 4 + 3)
+    t, q, kw = _pack_case(len(t), D, shards, int(-(-t.sum() // (R * D)) * 1.5) + 40, t, L=L, P=P)
+    kw["min_rows"] = R
+    flat = torch.empty(q.size + 4, dtype=torch.int32, device="cuda")
+    qd = flat[offset:offset + q.size].view(q.shape)
+    assert flat.data_ptr() % 16 == 0
+    qd.copy_(torch.as_tensor(q))
+    pb, prob = O.Problem.from_dict(kw), rp.Problem.from_dict(kw)
+    o = O.pack_rows(pb, t, q, 3, 8, 4, 12)
+    g = rp.pack_rows(prob, t, qd, 3, 8, 4, 12)
+    assert o["rc"] == 0 and g["r_star"] == o["r_star"]
+    assert np.array_equal(g["population"].cpu().numpy(), o["population"])
+    assert np.array_equal(g["scores"].cpu().numpy(), o["scores"])
+    ev = rp.eval_objective(prob, t, qd, g["r_star"], g["population"], want_J=True)
+    assert np.array_equal(ev["scores"].cpu().numpy(), o["scores"])
+    for m in range(len(o["population"])):
+        assert np.array_equal(ev["J"][m].cpu().numpy(),
+                              O.score(pb, t, q, o["r_star"], o["population"][m], want_J=True)[2])
+    temps = np.array([1e-1, 1e-2, 1e-3])
+    oa = O.anneal(pb, t, q, o["r_star"], o["population"], temps, 64, 9)
+    ga = rp.anneal(prob, t, qd, o["r_star"], o["population"], temps, 64, 9)
+    assert ga["level_kernel"] in ("chain", "chain_run")
+    for k in ("trace", "parents", "population", "best_layout"):
+        assert np.array_equal(ga[k].cpu().numpy(), oa[k])
+
+
+@gpu
+@pytest.mark.parametrize("N,D,R,shards", [(200, 4, 2, 1), (203, 2, 2, 1), (600, 4, 2, 1), (900, 4, 7, 2), (37, 4, 3, 1),
+                                          (29, 2, 3, 1), (31, 2, 2, 2)])
 def test_anneal_pool_room(N, D, R, shards):
-    """64 ranks: the pool's spare room under hot levels of relocations --
-    blocks that fit and grow in place, the room running out and the pool
-    packed again, cells above and below 32 members, blocks larger than the
-    room (cells of a quarter of the samples) and no room at all."""
+    """64 ranks: the pool's spare room (N / 4 places, a multiple of 8) under
+    hot levels of relocations -- blocks that fit and grow in place, the room
+    running out and the pool packed again, cells above and below 32 members,
+    blocks larger than the room (cells of a quarter of the samples) and, below
+    32 samples, no room at all."""
     import oracle as O
     import paper_2608_12146_amd as rp
     _log(f"pool room N={N} D={D} R={R} shards={shards}")
