@@ -409,13 +409,6 @@ __global__ void __launch_bounds__(kThreads) k_anneal_level(AnnealArgs a) {
 // 64-bit mix of (sample, cell)), k_leader finds for each member the first
 // member with an equal layout (hash match confirmed element by element),
 // and only those leaders are built; duplicates copy the leader's slab.
-__device__ inline uint64_t mix64(uint64_t z) {
-    z += 0x9E3779B97F4A7C15ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
-}
-
 __global__ void __launch_bounds__(kThreads) k_layout_hash(const int32_t *layouts, int32_t N, uint64_t *hash) {
     __shared__ uint64_t part[kThreads / kWave];
     const int m = blockIdx.x;

@@ -33,12 +33,6 @@ namespace {
 
 constexpr int64_t kInf = INT64_MAX;  // J prefix entries beyond the last row-shard
 
-__device__ inline void wsync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Inclusive prefix sum over the first W lanes (W = 8 or 16) of each 16-lane
 // row; W = 32: over each 32-lane half (rows 1 and 3 add the last lane of
 // rows 0 and 2).
@@ -382,7 +376,7 @@ __device__ inline void pool_move(uint16_t *pool16, int32_t from, int32_t to, uin
                 }
                 *reinterpret_cast<uint4 *>(pw + w) = make_uint4(out[0], out[1], out[2], out[3]);
             }
-            wsync();
+            wave_sync();
         }
     } else if (from > to) {
         // new[x] = old[x - 1] for to < x <= from; new[to] = v (high chunks first)
@@ -405,11 +399,11 @@ __device__ inline void pool_move(uint16_t *pool16, int32_t from, int32_t to, uin
                 }
                 *reinterpret_cast<uint4 *>(pw + w) = make_uint4(out[0], out[1], out[2], out[3]);
             }
-            wsync();
+            wave_sync();
         }
     } else {
         if (lane == 0) pool16[to] = (uint16_t)v;
-        wsync();
+        wave_sync();
     }
 }
 
@@ -467,9 +461,9 @@ __device__ inline void pool_move_g(int32_t *pool, int32_t from, int32_t to, int3
             }
         }
     }
-    wsync();
+    wave_sync();
     if (lane == 0) pool[to] = v;
-    wsync();
+    wave_sync();
 }
 
 // start[c] += d for lo < c <= hi (16-bit entries, 32-bit words four per lane).
@@ -492,7 +486,7 @@ __device__ inline void start_add(uint16_t *start16, int32_t lo, int32_t hi, int3
             }
             *reinterpret_cast<uint4 *>(sw + w) = make_uint4(out[0], out[1], out[2], out[3]);
         }
-        wsync();
+        wave_sync();
     }
 }
 
@@ -515,7 +509,7 @@ __device__ inline void start_add(uint16_t *start16, int32_t lo, int32_t hi, int3
 __device__ inline void pool_rebuild(const AnnealArgs &a, const Lds &M) {
     const int lane = lane_id();
     const int32_t N = a.N, B = a.B;
-    wsync();
+    wave_sync();
     int32_t carry = 0;
     for (int32_t b = 0; b < B; b += kWave) {
         const int32_t c = b + lane, n = c < B ? M.cnt[c] : 0;
@@ -523,7 +517,7 @@ __device__ inline void pool_rebuild(const AnnealArgs &a, const Lds &M) {
         if (c < B) M.start[c] = (uint16_t)(carry + incl - n);
         carry += __builtin_amdgcn_readlane(incl, kWave - 1);
     }
-    wsync();
+    wave_sync();
     constexpr int U = 16;
     for (int32_t b = 0; b < N; b += U * kWave) {
         int32_t cl[U];
@@ -536,7 +530,7 @@ __device__ inline void pool_rebuild(const AnnealArgs &a, const Lds &M) {
         for (int u = 0; u < U; ++u) {
             const int32_t i = b + u * kWave + lane, c = cl[u];
             if (c >= 0) M.cnt[c] = (uint16_t)lane;
-            wsync();
+            wave_sync();
             int32_t pos = c >= 0 ? M.start[c] : 0;
             int32_t next = pos + 1;
             bool last = c >= 0;  // the lane that leaves its cell's next place
@@ -552,9 +546,9 @@ __device__ inline void pool_rebuild(const AnnealArgs &a, const Lds &M) {
                 lost &= ~same;
             }
             if (c >= 0) M.gpool[clamp0(pos, a.pool_cap - 1)] = i;
-            wsync();
+            wave_sync();
             if (last) M.start[c] = (uint16_t)next;
-            wsync();
+            wave_sync();
         }
     }
     // places after the last member -> counts and starts
@@ -569,7 +563,7 @@ __device__ inline void pool_rebuild(const AnnealArgs &a, const Lds &M) {
             M.cnt[c] = (uint16_t)(e - s);
         }
     }
-    wsync();
+    wave_sync();
 }
 
 // Prefixes of the roulette weights into LDS from J_pre (lane h holds
@@ -789,7 +783,7 @@ __device__ inline void member_load(const AnnealArgs &a, const Lds &M, const Tabl
     R.Ar = lane < RG ? g.A[lane] : 0;
     R.Jr2 = RV == 2 && h2 < RG ? g.J[h2] : 0;
     R.Ar2 = RV == 2 && h2 < RG ? g.A[h2] : 0;
-    wsync();
+    wave_sync();
     // cost prefix of each row-shard's cells, in slot order (lanes over row-shards)
     for (int32_t h = lane; h < (RV == 2 ? RG : (RG < kWave ? RG : kWave)); h += kWave) {
         const int32_t cnt = tb.hcnt[h];
@@ -830,7 +824,7 @@ __device__ inline void member_load(const AnnealArgs &a, const Lds &M, const Tabl
     const int64_t j1 = lane < RG ? R.Jr : LLONG_MIN, j2 = RV == 2 && h2 < RG ? R.Jr2 : LLONG_MIN;
     R.s2 = wave_max(j1 > j2 ? j1 : j2);
     write_jpre<RV>(M, R.Jr, R.Jr2, RG, R.s2);
-    wsync();
+    wave_sync();
 }
 
 // A member's state back to a slab (W is kept up to date in the slab, and Q
@@ -839,7 +833,7 @@ template <int RV, bool HQ = false>
 __device__ inline void member_store(const AnnealArgs &a, const Lds &M, const SlabPtrs &g, const Regs &R) {
     const int lane = lane_id();
     const int32_t N = a.N, B = a.B, RG = a.RG;
-    wsync();
+    wave_sync();
     const int32_t n4 = N >> 2;
     int4 *c4 = reinterpret_cast<int4 *>(g.cell), *p4 = reinterpret_cast<int4 *>(g.pool);
     const ushort4 *lc4 = reinterpret_cast<const ushort4 *>(M.cell), *lp4 = reinterpret_cast<const ushort4 *>(M.pool);
@@ -1212,7 +1206,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
             if (log && lane == f) log[k] = 2;
             n_acc += 1;
             // ---- commit
-            wsync();
+            wave_sync();
             if (two) {
 #pragma unroll
                 for (int v = 0; v < LV; ++v) {
@@ -1238,7 +1232,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                         if constexpr (HP) M.gpool[at] = val;
                         else M.pool[at] = (uint16_t)val;
                     }
-                    wsync();
+                    wave_sync();
                 } else {
                     auto cl = [&](int32_t lo, int32_t hi, int32_t v, int32_t skip) {
                         return HP ? count_less_g(M.gpool, lo, hi, v, skip) : count_less(M.pool, lo, hi, v, skip);
@@ -1253,7 +1247,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                     else if (HP) pos_j += st2;
                     const int32_t to1 = st1 + cl(st1, en1, j, i);
                     const int32_t to2 = st2 + cl(st2, en2, i, j);
-                    wsync();
+                    wave_sync();
                     mv(clamp0(pos_i, last), clamp0(to1, last), j);
                     mv(clamp0(pos_j, last), clamp0(to2, last), i);
                 }
@@ -1288,7 +1282,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                             dst = a.pool_ovf;
                         }
                     }
-                    wsync();
+                    wave_sync();
                     if (dst + blk > a.pool_cap) {
                         // no room for it in a packed pool: every member between moves
                         const int32_t to = c1 < c2 ? st2 - 1 + rk : st2 + rk;
@@ -1323,7 +1317,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
                     }
                 } else {
                     const int32_t to = c1 < c2 ? st2 - 1 + rk : st2 + rk;
-                    wsync();
+                    wave_sync();
                     pool_move(M.pool, clamp0(pos_i, last), clamp0(to, last), (uint32_t)i);
                     if (c1 < c2) start_add(M.start, c1, c2, -1);
                     else start_add(M.start, c2, c1, 1);
@@ -1403,7 +1397,7 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
             s2 = n2;
             e_cur = e_new;
             inv_dt = 1.0 / ((fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0) * temp);
-            wsync();
+            wave_sync();
             if (lex_less(s0, s1, s2, b0, b1, b2)) {
                 b0 = s0;
                 b1 = s1;
@@ -1516,7 +1510,7 @@ __device__ inline void wave_copy16(const char *src, char *dst, int32_t n) {
 template <int RV>
 __device__ inline void member_publish(const AnnealArgs &a, const char *mine, char *blob, const Regs &R) {
     const int lane = lane_id();
-    wsync();
+    wave_sync();
     const int32_t n16 = a.lds_member >> 4;
     const v4i *src = reinterpret_cast<const v4i *>(mine);
     v4i *dst = reinterpret_cast<v4i *>(blob);
@@ -1579,7 +1573,7 @@ __device__ inline void member_receive(const AnnealArgs &a, char *mine, const cha
             if (x < n16) dst[x] = v[u];
         }
     }
-    wsync();
+    wave_sync();
 }
 
 // Stores and loads at device scope (every XCD): the store writes through to

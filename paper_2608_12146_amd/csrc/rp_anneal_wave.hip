@@ -45,12 +45,6 @@
 
 namespace rp {
 
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 struct MemberLds {
     uint16_t *cell, *pool, *start;
     int32_t *T;

@@ -183,14 +183,6 @@ __global__ void __launch_bounds__(kWave) k_fixed_bin(const int32_t *__restrict__
         for (int32_t u = lane; u < n; u += kWave) cells[sigma[u]] = choice[u];
 }
 
-// Orders a wave's LDS accesses before its later ones by other lanes.
-__device__ inline void lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-__device__ inline uint64_t low_lanes(int n) { return n >= kWave ? ~(uint64_t)0 : ((uint64_t)1 << n) - 1; }
-
 constexpr int32_t kBinCells = kWave * kWave;  // cells of k_fixed_bin_chunks
 
 // The search for up to 4096 cells, one wave; bound by the cycles of a node,
@@ -213,7 +205,7 @@ __global__ void __launch_bounds__(kWave) k_fixed_bin_chunks(const int32_t *__res
     const int lane = lane_id();
     for (int32_t c = lane; c < K; c += kWave) room[c] = -1;
     for (int32_t u = lane; u < n; u += kWave) choice[u] = -1;
-    lds_order();
+    wave_sync();
     auto largest = [](Room v) -> Room {
         if constexpr (sizeof(Room) == 4) return wave_max32(v);
         else return wave_max(v);
@@ -223,7 +215,7 @@ __global__ void __launch_bounds__(kWave) k_fixed_bin_chunks(const int32_t *__res
     auto chunk = [&](int x) {  // makes x the current chunk
         if (x == cur) return;
         if (cur * kWave + lane < K) room[cur * kWave + lane] = row;
-        lds_order();
+        wave_sync();
         cur = x;
         row = x * kWave + lane < K ? room[x * kWave + lane] : (Room)-1;
     };
@@ -231,7 +223,7 @@ __global__ void __launch_bounds__(kWave) k_fixed_bin_chunks(const int32_t *__res
     auto samples = [&](int32_t h) {  // makes h's block the current one
         if (h - hb >= 0 && h - hb < kWave) return;
         if (hb + lane < n) choice[hb + lane] = c_l;
-        lds_order();
+        wave_sync();
         hb = h & ~(kWave - 1);
         t_l = hb + lane < n ? ts[hb + lane] : 0;
         c_l = hb + lane < n ? choice[hb + lane] : -1;
@@ -315,7 +307,7 @@ __global__ void __launch_bounds__(kWave) k_fixed_bin_chunks(const int32_t *__res
         }
     }
     if (hb + lane < n) choice[hb + lane] = c_l;
-    lds_order();
+    wave_sync();
     if (lane == 0) {
         out[0] = status;
         out[1] = nodes;

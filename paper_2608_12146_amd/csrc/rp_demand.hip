@@ -133,16 +133,6 @@ __global__ void __launch_bounds__(256) k_aggregate_cols(const int64_t *__restric
 
 constexpr int kLptThreads = 512;
 
-// Lane i's value becomes lane i + 1's; lane 63's becomes 0.
-__device__ inline int32_t wave_shl1(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xF, 0xF, true); }
-
-// Orders a wave's LDS writes before its later reads by other lanes.
-__device__ inline void lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Layer-local LPT (Alg. 1), one layer per workgroup.  Experts are ranked by
 // (-L_{l,e}, e) (ranking by counting: the rank of e is the number of experts
 // that precede it; every wave counts), then E greedy steps of the first wave
@@ -212,15 +202,14 @@ __global__ void __launch_bounds__(kLptThreads) k_lpt_place(const int64_t *__rest
             for (int x = 0; x < cnt; ++x) {
                 const uint64_t nk = readlane64(key, 0) - readlane64(ol, x);
                 const int32_t r0 = __builtin_amdgcn_readlane(rf, 0);
-                const uint64_t upk = (uint64_t)(uint32_t)wave_shl1((int32_t)(uint32_t)key) |
-                                     (uint64_t)(uint32_t)wave_shl1((int32_t)(uint32_t)(key >> 32)) << 32;
-                const int32_t uprf = wave_shl1(rf);
+                const uint64_t upk = lane_up64(key);
+                const int32_t uprf = lane_up(rf);
                 const bool full = (r0 >> 6) + 1 == H;
                 const uint64_t before = __ballot(key > nk) | 1;  // lanes 0 .. the new place
-                const bool shift = __builtin_amdgcn_inverse_ballot_w64(full ? ~(uint64_t)0 : before >> 1);
-                const bool here = __builtin_amdgcn_inverse_ballot_w64(full ? 0 : before ^ (before >> 1));
-                const bool mine = __builtin_amdgcn_inverse_ballot_w64((uint64_t)1 << x);
-                const bool done = __builtin_amdgcn_inverse_ballot_w64(full ? (uint64_t)1 << (r0 & (kWave - 1)) : 0);
+                const bool shift = lane_in(full ? ~(uint64_t)0 : before >> 1);
+                const bool here = lane_in(full ? 0 : before ^ (before >> 1));
+                const bool mine = lane_in((uint64_t)1 << x);
+                const bool done = lane_in(full ? (uint64_t)1 << (r0 & (kWave - 1)) : 0);
                 sv = mine ? r0 : sv;
                 fin = done ? nk : fin;
                 key = here ? nk : key;
@@ -244,7 +233,7 @@ __global__ void __launch_bounds__(kLptThreads) k_lpt_place(const int64_t *__rest
         G[p] = 0;
         nfill[p] = 0;
     }
-    lds_order();
+    wave_sync();
     for (int k = 0; k < E; ++k) {
         const int e = order[k];
         int64_t bg = LLONG_MAX;
@@ -271,7 +260,7 @@ __global__ void __launch_bounds__(kLptThreads) k_lpt_place(const int64_t *__rest
             G[bp] += Ll[e];
             nfill[bp] += 1;
         }
-        lds_order();
+        wave_sync();
     }
     for (int p = lane; p < P; p += kWave) rank_load[(int64_t)l * P + p] = G[p];
 }

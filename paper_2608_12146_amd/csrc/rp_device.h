@@ -121,6 +121,28 @@ __host__ __device__ inline bool lex_less(int64_t a0, int64_t a1, int64_t a2, int
 __device__ inline int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 __device__ inline int wave_id() { return (int)(threadIdx.x / kWave); }
 
+// Orders a wave's memory accesses before its later ones by other lanes.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ inline uint64_t low_lanes(int n) { return n >= kWave ? ~(uint64_t)0 : ((uint64_t)1 << n) - 1; }
+__device__ inline bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
+// Lane i's value becomes lane i + 1's (lane 63: 0), or lane i - 1's (lane 0: 0).
+__device__ inline int32_t lane_up(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xF, 0xF, true); }
+__device__ inline int32_t lane_down(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, true); }
+__device__ inline uint64_t lane_up64(uint64_t v) {
+    return (uint64_t)(uint32_t)lane_up((int32_t)(uint32_t)v) |
+           (uint64_t)(uint32_t)lane_up((int32_t)(uint32_t)(v >> 32)) << 32;
+}
+__device__ inline uint64_t lane_down64(uint64_t v) {
+    return (uint64_t)(uint32_t)lane_down((int32_t)(uint32_t)v) |
+           (uint64_t)(uint32_t)lane_down((int32_t)(uint32_t)(v >> 32)) << 32;
+}
+
 // DPP controls (GFX9 encoding).
 constexpr int kDppXor1 = 0xB1;        // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;        // quad_perm [2,3,0,1]
@@ -297,6 +319,15 @@ __device__ inline uint64_t wave_max_u64(uint64_t v) {
     a = b > a ? b : a;
     c = d > c ? d : c;
     return c > a ? c : a;
+}
+
+// 64-bit mix (the finaliser of splitmix64), for order-free hashes of layouts
+// as a sum over their (sample, cell) pairs.
+__device__ inline uint64_t mix64(uint64_t z) {
+    z += 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
 }
 
 __device__ inline int first_lane(uint64_t mask) { return mask ? __ffsll((long long)mask) - 1 : -1; }

@@ -89,27 +89,6 @@ __global__ void __launch_bounds__(256) k_rank_place(const int32_t *__restrict__ 
     if (i < N) sigma[rank[i]] = i;
 }
 
-// Lane i's value becomes lane i + 1's (lane 63: 0), or lane i - 1's (lane 0: 0).
-__device__ inline int32_t lane_up(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xF, 0xF, true); }
-__device__ inline int32_t lane_down(int32_t v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, true); }
-__device__ inline uint64_t lane_up64(uint64_t v) {
-    return (uint64_t)(uint32_t)lane_up((int32_t)(uint32_t)v) |
-           (uint64_t)(uint32_t)lane_up((int32_t)(uint32_t)(v >> 32)) << 32;
-}
-__device__ inline uint64_t lane_down64(uint64_t v) {
-    return (uint64_t)(uint32_t)lane_down((int32_t)(uint32_t)v) |
-           (uint64_t)(uint32_t)lane_down((int32_t)(uint32_t)(v >> 32)) << 32;
-}
-__device__ inline uint64_t low_lanes(int n) { return n >= kWave ? ~(uint64_t)0 : ((uint64_t)1 << n) - 1; }
-__device__ inline bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
-
-// Orders a wave's LDS accesses before its later ones by other lanes.
-__device__ inline void lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // FixedRowFFD (one wave).  ok = 1 and cell_of filled on success.  The N - K
 // steps are one serial chain, bound by its length in cycles.  Lane x keeps the
 // largest room of chunk x (cells 64x .. 64x + 63), and the rooms of the chunk
@@ -132,7 +111,7 @@ __global__ void __launch_bounds__(64) k_ffd(const int32_t *__restrict__ t, const
         room[c] = (Room)(C - t[i]);
         cell_of[i] = c;
     }
-    lds_order();
+    wave_sync();
     auto largest = [](Room v) -> Room {
         if constexpr (sizeof(Room) == 4) return wave_max32(v);
         else return wave_max(v);
@@ -171,7 +150,7 @@ __global__ void __launch_bounds__(64) k_ffd(const int32_t *__restrict__ t, const
                     break;
                 }
                 cur = first_lane(any);
-                lds_order();
+                wave_sync();
                 row = chunk_rooms(cur);
                 m = __ballot(row >= ti);
             }
@@ -853,7 +832,7 @@ __global__ void __launch_bounds__(kFitThreads) k_pack_fit_sorted(TrialArgs a, Pa
                     if (r2 != r) {
                         rows[r * kFitRow + lane] = e;
                         cnt -= lane_in((uint64_t)1 << r) ? 1 : 0;
-                        lds_order();
+                        wave_sync();
                         if (__builtin_amdgcn_readlane(cnt, r2) == kFitRow) {
                             // spread the K - 1 keys over the rows again
                             const int32_t pre = (int32_t)wave_incl_scan((int64_t)cnt) - cnt;
@@ -861,12 +840,12 @@ __global__ void __launch_bounds__(kFitThreads) k_pack_fit_sorted(TrialArgs a, Pa
                                 const int32_t nk_ = __builtin_amdgcn_readlane(cnt, k), ok_ = __builtin_amdgcn_readlane(pre, k);
                                 if (lane < nk_) lin[ok_ + lane] = rows[k * kFitRow + lane];
                             }
-                            lds_order();
+                            wave_sync();
                             for (int32_t k = lane; k < K - 1; k += kWave) rows[k / kFitFill * kFitRow + k % kFitFill] = lin[k];
                             const int32_t left = K - 1 - lane * kFitFill;
                             cnt = left < 0 ? 0 : (left < kFitFill ? left : kFitFill);
                             sep = lane == 0 ? 0 : (cnt > 0 ? lin[lane * kFitFill] : ~(uint64_t)0);
-                            lds_order();
+                            wave_sync();
                             r2 = __popcll(__ballot(sep <= nk)) - 1;
                         }
                         e = rows[r2 * kFitRow + lane];
@@ -880,7 +859,7 @@ __global__ void __launch_bounds__(kFitThreads) k_pack_fit_sorted(TrialArgs a, Pa
                     e = lane_in(~low_lanes(p2)) ? down : e;
                     e = lane_in((uint64_t)1 << p2) ? nk : e;
                     rows[r2 * kFitRow + lane] = e;
-                    lds_order();
+                    wave_sync();
                 }
             }
             if (wv == 0) {
@@ -1552,14 +1531,6 @@ __global__ void __launch_bounds__(1024) k_pack_pair(TrialArgs a, PackFast pf) {
     const int32_t *cellk = a.cellk + (int64_t)b * N;
     int32_t *out = a.out + (int64_t)b * N;
     for (int32_t i = tid; i < N; i += nt) out[i] = cell_to[cellk[i]];
-}
-
-// 64-bit mix of a (sample, cell) pair (the finaliser of splitmix64).
-__device__ inline uint64_t mix64(uint64_t z) {
-    z += 0x9E3779B97F4A7C15ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
 }
 
 // Canonical form of layouts[b] (b < n) into canon[b], with an order-free hash
