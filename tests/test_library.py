@@ -120,3 +120,37 @@ def test_l2_write_backs_are_waited_for(tmp_path):
             elif op.startswith(("global_", "flat_", "buffer_")):
                 assert not pending, op
     assert seen > 0
+
+
+HIPCC = "/opt/rocm/bin/hipcc"
+
+ROW_PIECES = """
+#include <stdio.h>
+#include "rp_rows.h"
+int main() {
+    for (int P = 4; P <= 64; P *= 2)
+        for (int L = 1; L <= 4096 / P; ++L)
+            for (int N = 64; N <= 32768; N *= 2) {
+                const rp::RowPieces r = rp::row_pieces(N, L, P);
+                printf("%d %d %d %d %d %d %d\\n", N, L, P, r.lay_piece, r.n_pieces, (int)r.one, (int)r.spread);
+            }
+}
+"""
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+def test_row_pieces(tmp_path):
+    """Every piece holds layers and fits a wave; pieces that consecutive
+    workgroups take in turn divide the 8 XCDs, and their slices fit an L2."""
+    src, exe = tmp_path / "pieces.hip", tmp_path / "pieces"
+    src.write_text(ROW_PIECES)
+    subprocess.run([HIPCC, "--cuda-host-only", "-std=c++17", "-I", os.path.join(ROOT, "paper_2608_12146_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True, capture_output=True)
+    rows = np.array([line.split() for line in subprocess.check_output([str(exe)], text=True).splitlines()], dtype=int)
+    N, L, P, lay, n, one, spread = rows.T
+    assert ((n - 1) * lay < L).all() and (n * lay >= L).all()
+    assert (lay * P <= 256).all() and (one == (lay * P > 128)).all()
+    s = spread == 1
+    assert s.any() and (~s).any()
+    assert np.isin(n[s], (1, 2, 4, 8)).all()
+    assert (N[s] * lay[s] * P[s] * 4 <= 2 << 20).all()
