@@ -909,8 +909,6 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
     const int32_t last = HP ? a.pool_cap - 1 : N - 1;  // last place of the pool
     int64_t n_acc = 0, n_eval = 0;
     double e_cur = GV == 1 ? energy_pow2(a, s0, s1, s2) : energy_k(a, s0, s1, s2);
-    // 1 / (max(|e_cur|, 1) temp), for the bracket of the accept test
-    double inv_dt = 1.0 / ((fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0) * temp);
     const int half = lane >> 5, hl = lane & 31;
     // cells of a row-shard: lane (half, x) holds its x-th slot, x < 16 (all
     // 32 lanes of the half with up to 32 slots)
@@ -1182,18 +1180,28 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
             if (!accept && !(e_new > e_cur)) accept = true;  // delta <= 0 (the divisor is >= 1)
             if (!accept) {
                 // u < exp_det(-z) for z = (e_new - e_cur) / den / temp > 0,
-                // decided from single-precision exp2 when u is clear of it by
-                // 1e-5: z here is off by a few 2^-53, its conversion and the
-                // product by 2^-23 (below 7e-6 of the result for z < 30; beyond,
-                // exp(-z) is below 2^-43 and u is 0 or at least 2^-32), exp2 by
-                // an ulp.  Only the rest take the divisions and the series.
+                // decided in single precision when u is clear of exp2's value
+                // by 2e-5 of it.  The error there: two conversions (2^-24
+                // each), v_rcp_f32 (2^-23), log2 e and two products (2^-24
+                // each), together below 4.2e-7 z, which is below 1e-5 up to
+                // z = 23 (beyond, exp(-z) is below 2^-33 and u is 0 or at
+                // least 2^-32), and exp2's 2^-23.  Energies differ by 1e-35 or
+                // more, so z is out of reach of u where den temp underflows
+                // (z inf) and next to 0 where it overflows (z 0).  Only the
+                // rest take the divisions and the series.
+                // Against a bracket 1 - z <= exp(-z) <= 1 - z + z^2 / 2 on the
+                // divided z, by input: whole plan of a tiny window 10.5 .. 36.7
+                // -> 10.0 .. 32.8 ms, 1000 levels of a small one 263 -> 252,
+                // 2000 of the ordinary one 83.7 .. 401 -> 82.7 .. 394.  (With
+                // 1 / (den temp) kept in double precision, a division for each
+                // accepted move, the last took up to 404.)
                 const double u = (double)fw7 * (1.0 / 4294967296.0);
-                const float ef = __builtin_amdgcn_exp2f(-1.44269504f * (float)((e_new - e_cur) * inv_dt));
-                const double ed = (double)ef;
-                if (u < ed * (1.0 - 1e-5)) {
+                const double den = fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0;
+                const float zf = (float)(e_new - e_cur) * __builtin_amdgcn_rcpf((float)(den * temp));
+                const double ed = (double)__builtin_amdgcn_exp2f(-1.44269504f * zf);
+                if (u < ed * (1.0 - 2e-5)) {
                     accept = true;
-                } else if (!(u > ed * (1.0 + 1e-5) + 1e-37)) {
-                    const double den = fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0;
+                } else if (!(u > ed * (1.0 + 2e-5) + 1e-37)) {
                     const double delta = (e_new - e_cur) / den;
                     const double z = (delta > 0.0 ? delta : 0.0) / temp;
                     accept = u < exp_det(-z);  // (z = 0: exp(0) = 1 > u)
@@ -1396,7 +1404,6 @@ __device__ inline LevelOut member_level(const AnnealArgs &a, const Lds &M, const
             s1 = n1;
             s2 = n2;
             e_cur = e_new;
-            inv_dt = 1.0 / ((fabs(e_cur) > 1.0 ? fabs(e_cur) : 1.0) * temp);
             wave_sync();
             if (lex_less(s0, s1, s2, b0, b1, b2)) {
                 b0 = s0;

@@ -323,6 +323,38 @@ def test_level_end_populations(pop, monkeypatch):
 
 
 @gpu
+@pytest.mark.parametrize("kernel", ["chain_run", "chain"])
+@pytest.mark.parametrize("cap,stages", [(512, 1), (500, 2)])
+def test_accept_temperatures(cap, stages, kernel, monkeypatch):
+    """The accept test's single-precision bracket: temperatures from which
+    every uphill move is taken to those from which none is, and those at and
+    past the ends of single precision, where z underflows or overflows there."""
+    import oracle as O
+    import paper_2608_12146_amd as rp
+    _log(f"accept cap={cap} stages={stages} {kernel}")
+    monkeypatch.setenv("ROUTEPACK_ANNEAL_KERNEL", kernel)
+    rng = np.random.default_rng([22, cap])
+    t = rng.integers(1, 60, size=160)
+    t, q, kw = _pack_case(160, 4, 1, cap, t, L=5, P=8)
+    kw["min_rows"] = 4
+    if stages == 2:
+        kw.update(alpha_fp=np.array([4096, 2048]), beta_fp=np.array([0, 1]))
+    pb, prob = O.Problem.from_dict(kw), rp.Problem.from_dict(kw)
+    pk = O.pack_rows(pb, t, q, 3, 8, 4, 64)
+    assert pk["rc"] == 0
+    temps = np.array([1e300, 4e38, 3e38, 1e20, 10.0, 1.0, 0.3, 0.1, 3e-2, 1e-2, 3e-3, 1e-3, 1e-4, 1e-6, 1e-20, 1e-37,
+                      1.2e-38, 1e-39, 1e-45, 1e-300])
+    o = O.anneal(pb, t, q, pk["r_star"], pk["population"], temps, 300, 9)
+    assert o["rc"] == 0
+    g = rp.anneal(prob, t, q, pk["r_star"], pk["population"], temps, 300, 9)
+    assert g["level_kernel"] == kernel
+    rate = o["trace"][..., 6].sum(axis=1) / o["trace"][..., 7].sum(axis=1)
+    assert rate[0] > 0.99 and rate[-1] < 0.2 and np.any((rate > 0.3) & (rate < 0.7))
+    for k in ("parents", "trace", "population", "best_layout"):
+        assert np.array_equal(g[k].cpu().numpy(), o[k])
+
+
+@gpu
 @pytest.mark.parametrize("P,L,shards", [(4, 5, 2), (8, 31, 1), (16, 40, 2), (32, 3, 1), (64, 6, 1)])
 @pytest.mark.parametrize("offset", [0, 1])
 def test_q_alignment(P, L, shards, offset):
