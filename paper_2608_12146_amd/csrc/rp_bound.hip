@@ -190,20 +190,25 @@ constexpr int32_t kBinCells = kWave * kWave;  // cells of k_fixed_bin_chunks
 // not opened) in chunks of 64: lane x keeps an upper bound of chunk x's
 // largest room, the rooms of the chunk last used stay in the lanes, and so do
 // the lengths and choices of the 64 samples around h.  A node whose cell is
-// in the same chunk touches no memory; a chunk found to have no room gets its
-// exact bound.  4112 nodes over 400 cells took 2.94 ms scanning the open
-// cells' loads in LDS from the first and reading lengths from memory; now
-// 1.75 ms.  Room is int32 when the cap fits.
+// in the same chunk touches no memory; a chunk with no room at all for a
+// sample gets its exact bound.  Everything that steers the search is uniform
+// and kept in scalars.  Whole calls, scanning the open cells' loads in LDS from
+// the first and reading lengths from memory -> now: 4116 nodes over 416 cells,
+// nearly all forward, 3.21 -> 1.49 ms; 200000 nodes, nearly all backtracking,
+// 162 -> 148 ms in 20 cells, 171 -> 172 in 130, 260 -> 168 in 400, 354 -> 154
+// in 4000.
+// Room is int32 when the cap fits.
 template <typename Room>
 __global__ void __launch_bounds__(kWave) k_fixed_bin_chunks(const int32_t *__restrict__ ts, int32_t n, int64_t C,
                                                             int32_t K, int64_t budget,
                                                             const int32_t *__restrict__ sigma, int64_t *out,
                                                             int32_t *cells) {
     extern __shared__ __align__(16) char sbin[];
-    Room *room = reinterpret_cast<Room *>(sbin);                // [K]
-    int32_t *choice = reinterpret_cast<int32_t *>(room + K);  // [n] cell of sample h, -1 none
+    const int32_t kc = (K + kWave - 1) & ~(kWave - 1);
+    Room *room = reinterpret_cast<Room *>(sbin);               // [kc]
+    int32_t *choice = reinterpret_cast<int32_t *>(room + kc);  // [n] cell of sample h, -1 none
     const int lane = lane_id();
-    for (int32_t c = lane; c < K; c += kWave) room[c] = -1;
+    for (int32_t c = lane; c < kc; c += kWave) room[c] = -1;
     for (int32_t u = lane; u < n; u += kWave) choice[u] = -1;
     wave_sync();
     auto largest = [](Room v) -> Room {
@@ -214,97 +219,114 @@ __global__ void __launch_bounds__(kWave) k_fixed_bin_chunks(const int32_t *__res
     int cur = 0;
     auto chunk = [&](int x) {  // makes x the current chunk
         if (x == cur) return;
-        if (cur * kWave + lane < K) room[cur * kWave + lane] = row;
-        wave_sync();
-        cur = x;
-        row = x * kWave + lane < K ? room[x * kWave + lane] : (Room)-1;
+        room[cur * kWave + lane] = row;
+        cur = __builtin_amdgcn_readfirstlane(x);
+        row = room[cur * kWave + lane];  // (its own entries only: nothing to wait for but the load)
     };
-    int32_t hb = 0, t_l = lane < n ? ts[lane] : 0, c_l = -1;  // samples hb + lane: lengths, choices
+    // samples hb + lane: lengths and choices; those as long as the sample
+    // before; the choice of sample hb - 1
+    int32_t hb = 0, t_l = 0, c_l = -1, c_before = -1;
+    uint64_t equal = 0;
+    auto block = [&](int32_t b) {  // makes the samples from b on the current ones
+        hb = b;
+        const int32_t u = b + lane;
+        t_l = u < n ? ts[u] : 0;
+        equal = __ballot(u > 0 && u < n && ts[u > 0 ? u - 1 : 0] == t_l);
+        c_l = u < n ? choice[u] : -1;
+        c_before = b > 0 ? __builtin_amdgcn_readfirstlane(choice[b - 1]) : -1;
+    };
     auto samples = [&](int32_t h) {  // makes h's block the current one
-        if (h - hb >= 0 && h - hb < kWave) return;
+        if ((uint32_t)(h - hb) < (uint32_t)kWave) return;
         if (hb + lane < n) choice[hb + lane] = c_l;
         wave_sync();
-        hb = h & ~(kWave - 1);
-        t_l = hb + lane < n ? ts[hb + lane] : 0;
-        c_l = hb + lane < n ? choice[hb + lane] : -1;
+        block(h & ~(kWave - 1));
     };
+    block(0);
     int32_t h = 0, opened = 0;
     int64_t nodes = 0, status = 0;
     for (;;) {
-        if (h == n) {  // every sample placed; the cut leaves no cell unopened
-            status = 1;
-            break;
-        }
         samples(h);
         const int32_t x = h - hb;
         const int32_t th = __builtin_amdgcn_readlane(t_l, x), ch = __builtin_amdgcn_readlane(c_l, x);
         int32_t lo = ch + 1;
-        if (ch < 0 && h > 0) {  // a sample as long as the previous one goes to no lower cell
-            const int32_t tp = x > 0 ? __builtin_amdgcn_readlane(t_l, x - 1) : ts[h - 1];
-            if (tp == th) lo = x > 0 ? __builtin_amdgcn_readlane(c_l, x - 1) : choice[h - 1];
-        }
+        // a sample as long as the previous one goes to no lower cell
+        if (ch < 0 && ((equal >> x) & 1)) lo = x > 0 ? __builtin_amdgcn_readlane(c_l, x - 1) : c_before;
         int32_t b = -1;
         const int x0 = lo >> 6;
         uint64_t cm = __ballot(top >= (Room)th) & ~low_lanes(x0);
         while (cm) {
             const int c = first_lane(cm);
             chunk(c);
-            const int from = c == x0 ? lo & (kWave - 1) : 0;
-            const uint64_t fit = __ballot(row >= (Room)th) & ~low_lanes(from);
+            const uint64_t all = __ballot(row >= (Room)th);
+            const uint64_t fit = c == x0 ? all & ~low_lanes(lo & (kWave - 1)) : all;
             if (fit) {
                 b = c * kWave + first_lane(fit);
                 break;
             }
-            const Room mx = largest(row);
-            top = lane == c ? mx : top;
+            if (!all) {
+                const Room mx = largest(row);
+                top = lane_in((uint64_t)1 << c) ? mx : top;
+            }
             cm &= cm - 1;
         }
-        const bool fresh = b < 0 && lo <= opened && opened < K;
-        if (fresh) b = opened;
-        if (b >= 0) {
+        if (b >= 0) {  // (in the current chunk)
             if (nodes == budget) {  // the next placement would exceed the budget
                 status = 2;
                 break;
             }
             ++nodes;
-            c_l = lane == x ? b : c_l;
+            c_l = lane_in((uint64_t)1 << x) ? b : c_l;
             // kept unless fewer samples remain than unopened cells (then the
             // next cell for h)
-            if (n - (h + 1) >= K - opened - (fresh ? 1 : 0)) {
-                const int bc = b >> 6;
-                chunk(bc);
-                row = lane == (b & (kWave - 1)) ? (fresh ? (Room)C : row) - (Room)th : row;
-                if (fresh) {
-                    ++opened;
-                    const Room left = (Room)C - (Room)th;
-                    top = lane == bc && left > top ? left : top;
+            if (n - (h + 1) >= K - opened) {
+                row = lane_in((uint64_t)1 << (b & (kWave - 1))) ? row - (Room)th : row;
+                if (++h == n) {  // every sample placed; the cut leaves no cell unopened
+                    status = 1;
+                    break;
                 }
-                ++h;
+            }
+            continue;
+        }
+        if (lo <= opened && opened < K) {  // the first unopened cell
+            if (nodes == budget) {
+                status = 2;
+                break;
+            }
+            ++nodes;
+            c_l = lane_in((uint64_t)1 << x) ? opened : c_l;
+            if (n - (h + 1) >= K - opened - 1) {
+                const int bc = opened >> 6;
+                chunk(bc);
+                const Room left = (Room)C - (Room)th;
+                row = lane_in((uint64_t)1 << (opened & (kWave - 1))) ? left : row;
+                top = lane_in((uint64_t)1 << bc) && left > top ? left : top;
+                ++opened;
+                if (++h == n) {
+                    status = 1;
+                    break;
+                }
             }
             continue;
         }
         // backtrack: sample h has no cell left
-        c_l = lane == x ? -1 : c_l;
+        c_l = lane_in((uint64_t)1 << x) ? -1 : c_l;
         if (--h < 0) {
             status = 0;
             break;
         }
         samples(h);
         const int32_t pb = __builtin_amdgcn_readlane(c_l, h - hb), tb = __builtin_amdgcn_readlane(t_l, h - hb);
-        const int pc = pb >> 6;
-        chunk(pc);
-        const bool own = lane == (pb & (kWave - 1));
-        row = own ? row + (Room)tb : row;
-        if (__ballot(own && row == (Room)C)) {  // it was the last cell opened
-            row = own ? (Room)-1 : row;
+        chunk(pb >> 6);
+        const int own = pb & (kWave - 1);
+        Room left;
+        if constexpr (sizeof(Room) == 4) left = __builtin_amdgcn_readlane(row, own) + tb;
+        else left = (Room)readlane64((uint64_t)row, own) + tb;
+        if (left == (Room)C) {  // it was the last cell opened
+            left = -1;
             --opened;
-        } else {
-            const uint64_t mine = (uint64_t)1 << (pb & (kWave - 1));
-            Room left;
-            if constexpr (sizeof(Room) == 4) left = __builtin_amdgcn_readlane(row, first_lane(mine));
-            else left = (Room)readlane64((uint64_t)row, first_lane(mine));
-            top = lane == pc && left > top ? left : top;
         }
+        row = lane_in((uint64_t)1 << own) ? left : row;
+        top = lane_in((uint64_t)1 << cur) && left > top ? left : top;
     }
     if (hb + lane < n) choice[hb + lane] = c_l;
     wave_sync();
@@ -373,8 +395,7 @@ extern "C" int routepack_fixed_bin_search(const routepack_problem *prob, const i
         return ROUTEPACK_OK;
     }
     const int32_t K = (int32_t)K64;
-    const size_t lds = 8 * (size_t)K + 4 * (size_t)N;
-    if (lds > 150 * 1024) return ROUTEPACK_E_UNSUPPORTED;
+    if (8 * (size_t)K + 4 * (size_t)N > 150 * 1024) return ROUTEPACK_E_UNSUPPORTED;
     Scratch scr(stream);
     int32_t *sigma = scr.get<int32_t>(N);
     int32_t *ts = scr.get<int32_t>(N);
@@ -383,9 +404,10 @@ extern "C" int routepack_fixed_bin_search(const routepack_problem *prob, const i
     RP_TRY(rank_sort_desc(lengths, N, sigma, scr, stream));
     hipLaunchKernelGGL(k_sorted_lengths32, dim3((N + 255) / 256), dim3(256), 0, stream, lengths,
                        (const int32_t *)sigma, N, ts);
-    auto search = K > kBinCells            ? k_fixed_bin
-                  : C < ((int64_t)1 << 31) ? k_fixed_bin_chunks<int32_t>
-                                           : k_fixed_bin_chunks<int64_t>;
+    const bool chunks = K <= kBinCells, narrow = chunks && C < ((int64_t)1 << 31);
+    auto search = narrow ? k_fixed_bin_chunks<int32_t> : chunks ? k_fixed_bin_chunks<int64_t> : k_fixed_bin;
+    const size_t cells = chunks ? ((size_t)K + kWave - 1) & ~(size_t)(kWave - 1) : (size_t)K;
+    const size_t lds = (narrow ? 4 : 8) * cells + 4 * (size_t)N;
     if (hipFuncSetAttribute((const void *)search, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return ROUTEPACK_E_DEVICE;
     hipLaunchKernelGGL(search, dim3(1), dim3(kWave), lds, stream, (const int32_t *)ts, N, C, K, node_budget,

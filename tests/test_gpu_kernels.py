@@ -445,3 +445,28 @@ def test_fixed_bin_chunks(K, N, fill, scale):
         assert (got[2] is None) == (want[2] is None)
         if got[2] is not None:
             assert np.array_equal(got[2].cpu().numpy(), want[2])
+
+
+@gpu
+@pytest.mark.parametrize("K,N,fill,hi", [(8, 24, 0.999, 200), (20, 60, 0.999, 1000), (30, 129, 0.9999, 300),
+                                         (65, 200, 0.999, 5000), (130, 500, 0.9995, 300)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_fixed_bin_backtracking(K, N, fill, hi, wide):
+    """Searches that go back and forth for thousands of nodes: within one chunk
+    of cells, over the ends of the blocks of samples and over chunks, with a
+    cap below and above 2^31."""
+    import oracle.fixedbin as F
+    import paper_2608_12146_amd as rp
+    _log(f"fixed bin backtracking K={K} N={N} wide={wide}")
+    rng = np.random.default_rng([K, N])
+    t = rng.integers(max(1, hi // 8), hi, size=N)
+    cap = max(int(t.max()), int(t.sum() / (K * fill)) + 1)
+    scale = (2**31 - 1) // int(t.max()) if wide else 1
+    t, cap = (t * scale).astype(np.int32), cap * scale
+    assert (cap >= 2**31) == wide
+    prob = rp.Problem(N, 0, 1, 1, 1, 1, 1, [0], cap, [1], [0])
+    got, want = rp.fixed_bin_search(prob, t, K, 20000), F.search(t, cap, K, 20000)
+    assert want[1] > 10 * N and got[:2] == want[:2]
+    assert (got[2] is None) == (want[2] is None)
+    if got[2] is not None:
+        assert np.array_equal(got[2].cpu().numpy(), want[2])
