@@ -163,11 +163,14 @@ def occupancy(kernel, pop, ranks):
     """Launch shape of the level kernel at this population on the 256 CUs
     (1024 SIMDs): the chain kernels run one wave per member and spread the
     members over the CUs, at most four per workgroup (the member state fills
-    the LDS), or one with the layout that keeps the cells in HBM (windows of
-    32 and 64 ranks that run a launch per level)."""
+    the LDS), or one per workgroup with 64 ranks, whose cells stay in HBM.
+    None for a launch per level with 32 ranks: the library keeps the cells in
+    LDS or in HBM by population and LDS, and does not report which."""
     if kernel in ("chain_run", "chain"):
+        if kernel == "chain" and ranks == 32:
+            return None
         mpw = max(1, min(4, -(-pop // 256)))  # members per workgroup
-        if kernel == "chain" and ranks >= 32:
+        if kernel == "chain" and ranks == 64:
             mpw = 1
         wgs = -(-pop // mpw)
         per_cu = -(-wgs // 256)

@@ -23,3 +23,12 @@ def test_profile_hash_covers_compile_flags(monkeypatch):
 def test_committed_mid_profile_matches_the_sources():
     pmc = bench.read_pmc("chain_run", "mid")
     assert pmc is not None and pmc > 0
+
+
+def test_occupancy():
+    """Members per workgroup as the library launches them; None where it
+    depends on a layout that is not reported."""
+    mid = bench.occupancy("chain_run", 1024, 16)
+    assert (mid["workgroups"], mid["waves_per_workgroup"], mid["waves_per_simd"]) == (256, 4, 1)
+    assert bench.occupancy("chain", 4096, 64)["waves_per_workgroup"] == 1
+    assert bench.occupancy("chain", 2048, 32) is None and bench.occupancy("workgroup", 64, 8) is None
