@@ -120,7 +120,14 @@ __global__ void __launch_bounds__(kThreads) k_row_sketch(SelArgs s) {
         for (int32_t e = tid; e < GLP; e += kThreads) {
             const int32_t g = e / LP, lp = e - g * LP;
             int64_t a = 0;
-            constexpr int U = 8;  // rows in flight (one at a time: 268 us at 12 candidates of 4096 samples, now 91 us)
+            // Eight rows in flight, loaded whichever shard they belong to: with
+            // G shards that reads G times the entries, but a load behind the
+            // shard test takes longer at every count.  12 candidates, a call
+            // with one row at a time / loads behind the test / this: 4096
+            // samples of 24 x 16 on 1, 4, 8 shards 187 / 160 / 155, 200 / 201 /
+            // 187, 238 / 245 / 233 us; 32768 of 64 x 64 on 1 and 4 shards 3.71 /
+            // 1.71 / 1.47 and 13.8 / 10.6 / 9.7 ms.
+            constexpr int U = 8;
             for (int32_t u = 0; u < n; u += U) {
                 int32_t v[U], w[U];
 #pragma unroll
