@@ -1606,10 +1606,11 @@ __device__ inline void release_dev() {
 // r.bar; the one that completes the count raises every workgroup's own flag
 // (128 bytes apart) to the epoch, and each polls only its own, so the last
 // arrivals and the waves still at work do not queue behind 256 polls of one
-// address: with all of them polling the count, 2000 levels of the ordinary
-// window took 104.3 ms on an input of tight cells (1.5 moves per member and
-// level) and 332 on one of loose cells, 150 of two shards 23.9 ms; now 98.9,
-// 330 and 23.5 ms.
+// address.  Same inputs, all polling the count -> now: 2000 levels of the
+// ordinary window 86.4 -> 83.1 ms with tight cells (1.5 moves per member and
+// level), 161 -> 158 and 400 -> 396 with looser ones, 1000 of a small one
+// 254.1 -> 252.7, 150 of two shards 24.3 -> 23.9; a single hop is faster by at
+// most 1% up to 32 workgroups (11.7 -> 11.8 ms for a plan on 8).
 // FULL: release and acquire at agent scope (the XCD's L2 written back, then
 // invalidated), so ordinary stores before it are visible to ordinary loads
 // after it in every workgroup.  The chain is arrival (release) -> the last
