@@ -255,9 +255,9 @@ MANY_LAYERS = {
 
 
 # A GPU memory fault was reported once during this case (per-level chain
-# kernel, 32 ranks, 40 layers) in a build that differed from the current
-# sources only in register allocation; the cause has not been found, so the
-# case stays off the GPU until it is.
+# kernel, 32 ranks, 40 layers, cells in LDS) in a build that differed from the
+# sources of its time only in register allocation; the cause has not been
+# found, so the case stays off the GPU until it is.
 _FAULT_SEEN = {("l40_p32", "chain")}
 
 
